@@ -313,8 +313,11 @@ quapi_status quapi_restore(quapi_ctx *ctx, int step, const double *tensor, size_
 /* Number of entries in the current tensor (N^min(c+1, L)). */
 quapi_status quapi_tensor_size(const quapi_ctx *ctx, size_t *entries);
 
-/* Full-window steps that one launch advances for this context (3, 2 or 1),
- * the group size of the determinism rule of quapi_propagate.
+/* Full-window steps of one group of this context (3, 2 or 1): the group size
+ * of the determinism rule of quapi_propagate.  An undriven M = 2 context with
+ * dk_max >= 8 that pins no width runs up to four steps in one launch, grouped
+ * from step dk_max + 1; its results do not depend on the split into calls (at
+ * QUAPI_C64_F64: into calls that end at whole groups).
  * Errors: QUAPI_ERR_INVALID for NULL arguments. */
 quapi_status quapi_fused_steps(const quapi_ctx *ctx, int *steps);
 
@@ -327,7 +330,7 @@ quapi_status quapi_fused_steps(const quapi_ctx *ctx, int *steps);
  * another call runs on the context. */
 quapi_status quapi_set_fused_steps(quapi_ctx *ctx, int steps);
 
-/* Mirror mode of the full-window kernels: the three-step kernel (M = 2,
+/* Mirror mode of the full-window kernels: the four- and three-step kernels (M = 2,
  * L >= 4), the two-step kernel (M = 2, L >= 3) and the single step (M = 2, 3,
  * 4; L >= 2).  Swapping the forward and
  * backward path of every point maps the path sum of Sec. II to its complex
@@ -339,7 +342,7 @@ quapi_status quapi_set_fused_steps(quapi_ctx *ctx, int steps);
  * up to rounding.  On by default where available.  The single step and the
  * two-step kernel use it for tensors above 2^22 entries only (smaller steps
  * are bound by their launches, and mirror mode takes three); the three-step
- * kernel always.  The entries above their mirror are filled in (one pass
+ * and four-step kernels always.  The entries above their mirror are filled in (one pass
  * over the tensor) before anything that reads the whole tensor: a kernel
  * that does not take mirror mode, quapi_read_tensor.
  *   quapi_mirror:      *enabled = the mode: 0 off, 1 on (default), 2 on at every size.
@@ -355,14 +358,16 @@ typedef struct {
     double setup_ms;          /* device time of the setup kernels in quapi_create */
     double step_ms;           /* summed duration of full-window step kernels (n >= L) */
     long long step_launches;  /* number of those launches (in mirror mode: of their groups of three) */
-    long long step_steps;     /* full-window steps they covered (a fused launch covers two or three) */
+    long long step_steps;     /* full-window steps they covered (a fused launch covers two to four) */
     double grow_ms;           /* summed duration of growth-step kernels (n < L) */
     long long grow_launches;
-    double finalize_ms;       /* summed duration of the kernels that sum rho over blocks */
+    double finalize_ms;       /* summed duration of the kernels that sum rho over blocks (the four-step
+                                 launches sum it themselves: no record) */
     long long finalize_launches;
     /* step_ms / step_launches split by the full-window steps a launch covers:
      * index 1 single steps, 2 two-step launches, 3 three-step launches (index
-     * 0 unused).  A launch in mirror mode counts its group of three kernels. */
+     * 0 unused).  A launch in mirror mode counts its group of three kernels; one
+     * over more steps than a group counts as its groups and the rest. */
     double width_ms[4];
     long long width_launches[4];
 } quapi_timing;

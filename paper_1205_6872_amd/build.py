@@ -16,7 +16,7 @@ CSRC = PKG / "csrc"
 LIB_DIR = PKG / "_lib"
 OBJ_DIR = LIB_DIR / "obj"
 LIB = LIB_DIR / "libquapi.so"
-SOURCES = [CSRC / "quapi_kernels.hip", CSRC / "quapi_step2.hip", CSRC / "quapi_step3.hip",
+SOURCES = [CSRC / "quapi_kernels.hip", CSRC / "quapi_step2.hip", CSRC / "quapi_step3.hip", CSRC / "quapi_tile.hip",
            CSRC / "quapi_host.hip", CSRC / "quapi_copy.hip",
            CSRC / "quapi_small.hip", CSRC / "quapi_filter.hip"]
 

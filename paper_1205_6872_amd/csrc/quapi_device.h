@@ -91,6 +91,23 @@ template <> struct TraceSum<float2> {
     __device__ __forceinline__ float2 rounded() const { return make_float2((float)s.x, (float)s.y); }
 };
 
+// ------------------------------------------------ compensated summation
+// Neumaier's variant of Kahan summation: s + c carries the running sum.
+__device__ __forceinline__ void neumaier(double &s, double &c, double x) {
+    const double t = s + x;
+    if (fabs(s) >= fabs(x)) c += (s - t) + x;
+    else c += (x - t) + s;
+    s = t;
+}
+// (s1, c1) += (s2, c2) with the rounding error of s1 + s2 kept (Knuth's two-sum).
+__device__ __forceinline__ void two_sum_combine(double &s1, double &c1, double s2, double c2) {
+    const double s = s1 + s2;
+    const double bp = s - s1;
+    const double e = (s1 - (s - bp)) + (s2 - bp);
+    s1 = s;
+    c1 = c1 + c2 + e;
+}
+
 // ------------------------------------------------------------------- LDS
 // Carve `bytes` (16-byte aligned) out of a dynamic LDS block at offset `off`.
 __host__ __device__ inline unsigned lds_take(unsigned &off, unsigned bytes) {

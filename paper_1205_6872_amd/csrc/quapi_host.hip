@@ -112,7 +112,10 @@ bool fused_ok(int N, int L) { return N == 4 && L >= 3; }
 // step-n group factors at lags L-1 and L-2 >= 2, for the same reason).
 bool triple_ok(int N, int L) { return N == 4 && L >= 4; }
 
-// Full-window steps per launch chosen by default: three from L = 13 at
+// Full-window steps per launch of the fused kernels, the group of the
+// determinism rule.  (From L = kTileMinL a context that pins no width runs the
+// four-step tile kernel, whose results do not depend on how a run is split,
+// down to these groups.)  Three from L = 13 at
 // complex128 and at complex64 with FP32 arithmetic (4^10 items and more; the
 // step is HBM bound there, and a third step in registers saves a third of
 // the traffic); two otherwise.  A three-step item runs one wave per SIMD
@@ -126,6 +129,29 @@ int fusion_width(int N, int L, int prec) {
     if (triple_ok(N, L) && L >= from) return 3;
     return fused_ok(N, L) ? 2 : 1;
 }
+
+// The four-step tile kernel (quapi_tile.hip) runs every full-window step past
+// n = L of a dense, undriven M = 2 context from L = kTileMinL that pins no
+// launch width.  Below, at N^L <= 2^14, the persistent path does better (L = 7:
+// 11 us per step, one launch); a tile needs the digits d0 .. d3, w0, w1 and at
+// least one more.
+bool tile_ok(int N, int L) { return N == 4 && L >= kTileMinL; }
+// Its outer digits past w0, w1: the middle ones share a table of at most 256
+// values, the rest another.
+int tile_mid_digits(int L) { return std::min(4, L - kTileSteps - 2); }
+int tile_top_digits(int L) { return L - kTileSteps - 2 - tile_mid_digits(L); }
+
+size_t tile_table_entries(int L) {
+    return (size_t)kTileSets * (32 + ((size_t)1 << (2 * tile_mid_digits(L))) + ((size_t)1 << (2 * tile_top_digits(L))));
+}
+// Tiles of a pass (of the kept half: those not above their mirror), and the
+// most blocks that run them (the rho rows of a step).
+long long tile_count(int L, bool mirror) {
+    const int k = L - kTileSteps - 2;
+    const long long all = 1LL << (2 * k);
+    return mirror ? (all + (1LL << k)) / 2 : all;
+}
+int tile_blocks(int L) { return (int)std::min<long long>(tile_count(L, false), kTileBlocks); }
 
 int max_grid(int N, int L) {
     int g = 1;
@@ -292,7 +318,7 @@ struct Layout {
     size_t off_a0, off_a1, off_bank, off_bankf, off_g, off_eta, off_U, off_s, off_H, off_Ht, off_Ut, off_rho0;
     size_t off_pa, off_ph, off_pseg, off_tw, off_tJ, off_glx, off_glw, off_partials, off_stage;
     size_t off_plan, off_plan2, off_coef, off_plan3, off_coef3, off_blk3, off_low3, off_blk2, off_low2, off_blk1,
-        off_low1, off_pairs, off_sink;
+        off_low1, off_pairs, off_sink, off_ttab, off_tcoef, off_trows;
     // filtered contexts: keys and values of the two tensors, flags, segment
     // starts, scan partials, counters, rho partials, factor-level tables
     size_t off_fkeys[2], off_fvals[2], off_fmask, off_fbofs, off_fctr, off_fpart, off_fplan;
@@ -461,6 +487,10 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_low2 = take((size_t)l.n_low2 * sizeof(int));
     l.off_blk1 = take((size_t)(l.n_canon1 + l.n_diag1) * sizeof(int));
     l.off_low1 = take((size_t)l.n_low1 * sizeof(int));
+    const bool tile = !filtered && tile_ok(N, L);
+    l.off_ttab = take(tile ? tile_table_entries(L) * 16 : 0);
+    l.off_tcoef = take(tile ? (size_t)kTileCoefCount * 8 : 0);
+    l.off_trows = take(tile ? (size_t)2 * kTileSteps * tile_blocks(L) * N * 16 : 0);
     const size_t fc = filtered ? filter_cap : 0;
     for (int b = 0; b < 2; ++b) {
         l.off_fkeys[b] = take(fc * 8);
@@ -554,6 +584,14 @@ struct quapi_ctx {
     std::vector<int> low1_h;
     double2 *plan3 = nullptr;
     void *coef3 = nullptr;
+    // The tile kernel: its tables, coefficients and two sets of rho rows; the
+    // rho of a pass is summed by extra blocks of the next pass, or by a launch
+    // of its own at the end of a call (tile_pending).
+    double2 *ttab = nullptr, *trows = nullptr;
+    void *tcoef = nullptr;
+    bool ttab_ready = false;
+    int trow_set = 0;
+    TileRho tile_pending{};
     // Filtered propagation (quapi_create_filtered): the kept entries as sorted
     // (key, value) pairs in two buffers of fcap entries, fkeys[cur] / fvals[cur]
     // the current tensor; fctr[0], fctr[1] their entry counts, fctr[2] (as int)
@@ -1437,6 +1475,103 @@ quapi_status enqueue_step3(quapi_ctx *c, int n, const bool *selk) {
     return QUAPI_OK;
 }
 
+// ------------------------------------------------------- four steps per pass
+bool tile_on(const quapi_ctx *c) { return !c->filtered && c->n_H == 0 && !c->fuse_pinned && tile_ok(c->N, c->L); }
+
+// The rho of the last pass that is still to be summed, as a launch of its own.
+quapi_status tile_finish(quapi_ctx *c) {
+    const hipError_t e = launch_tile_rho(c->tile_pending, c->stream);
+    c->tile_pending.n = 0;
+    if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "rho sum launch: %s", hipGetErrorString(e));
+    return QUAPI_OK;
+}
+
+// Steps n .. n+k-1 (n > L) of one group of four, whose groups start at the
+// steps n with n - L - 1 a multiple of 4: out[j] is where rho of step n+j goes
+// (NULL: not selected).
+quapi_status enqueue_tile(quapi_ctx *c, int n, int k, double2 *const *out) {
+    const int L = c->L, N = c->N;
+    const int s0 = (n - L - 1) % kTileSteps;
+    TileArgs a{};
+    a.d_mid = tile_mid_digits(L);
+    a.d_top = tile_top_digits(L);
+    a.t_w = c->ttab;
+    a.t_u = a.t_w + kTileSets * 16;
+    a.t_mid = a.t_u + kTileSets * 16;
+    a.t_top = a.t_mid + ((size_t)kTileSets << (2 * a.d_mid));
+    a.coef = c->tcoef;
+    if (!c->ttab_ready) {
+        TilePlanArgs pa{};
+        pa.bank = c->bank;
+        pa.eta = c->eta;
+        pa.s = (const double *)(c->ws + c->lay.off_s);
+        pa.L = L;
+        pa.d_mid = a.d_mid;
+        pa.d_top = a.d_top;
+        pa.t_w = (double2 *)a.t_w;
+        pa.t_u = (double2 *)a.t_u;
+        pa.t_mid = (double2 *)a.t_mid;
+        pa.t_top = (double2 *)a.t_top;
+        pa.coef = c->tcoef;
+        hipError_t e = launch_tile_tables(c->prec, pa, c->stream);
+        if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "tile tables launch: %s", hipGetErrorString(e));
+        c->ttab_ready = true;
+    }
+    const bool mirror = c->mirror != 0;
+    if (!mirror)
+        if (quapi_status st = ensure_full(c); st != QUAPI_OK) return st;
+    const size_t cap = c->lay.a_bytes / c->csize;
+    a.s0 = s0;
+    a.s1 = s0 + k;
+    a.m_count = ipow_ll(N, L - kTileSteps);
+    const long long tiles = tile_count(L, mirror);
+    if (k < 1 || a.s1 > kTileSteps || (size_t)a.m_count * 256 != cap || tiles > std::numeric_limits<int>::max() ||
+        1 + a.d_mid + a.d_top + 1 + kTileSteps != L)
+        return fail(c, QUAPI_ERR_DEVICE, "internal tile launch check failed at step %d", n);
+    a.n_tiles = (int)tiles;
+    a.n_work = (int)std::min<long long>(tiles, tile_blocks(L));
+    a.a_in = c->A[c->cur];
+    a.a_out = c->A[1 - c->cur];
+    // after j stages: the points d_j .. d_3, the digits m, then o_0 .. o_(j-1)
+    auto strides = [&](int j, long long *sd, long long *sm) {
+        for (int p = 0; p < kTileSteps; ++p) sd[p] = p < j ? ipow_ll(N, L - j + p) : ipow_ll(N, p - j);
+        *sm = ipow_ll(N, kTileSteps - j);
+    };
+    strides(a.s0, a.in_d, &a.in_m);
+    strides(a.s1, a.out_d, &a.out_m);
+    bool rho = false;
+    for (int j = 0; j < k; ++j) rho = rho || out[j];
+    if (rho) a.rows = c->trows + (size_t)c->trow_set * kTileSteps * tile_blocks(L) * N;
+    a.prev = c->tile_pending;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (c->timing) {
+        e0 = take_event(c);
+        e1 = take_event(c);
+        if (e0) (void)hipEventRecord(e0, c->stream);
+    }
+    const hipError_t e = launch_tile(c->prec, rho, mirror, a, c->stream);
+    if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "tile step launch: %s", hipGetErrorString(e));
+    if (c->timing && e0 && e1) {
+        (void)hipEventRecord(e1, c->stream);
+        c->recs.push_back({0, e0, e1, k, c->fuse});
+    }
+    c->tile_pending.n = 0;
+    if (rho) {
+        TileRho &r = c->tile_pending;
+        r.n_rows = a.n_work;
+        for (int j = 0; j < k; ++j)
+            if (out[j]) {
+                r.rows[r.n] = a.rows + (size_t)(s0 + j) * a.n_work * N;
+                r.out[r.n++] = out[j];
+            }
+        c->trow_set ^= 1;
+    }
+    c->cur = 1 - c->cur;
+    c->half_cur = mirror;
+    c->step = n + k - 1;
+    return QUAPI_OK;
+}
+
 // Capture full-window steps into an executable graph whose node arguments
 // never change (the step tables are the same for all n > L, and rho goes
 // through the sink); finalizes run on the same stream.
@@ -1648,12 +1783,14 @@ quapi_status propagate_impl(quapi_ctx *c, int n_steps, const int *sel, int n_sel
     if (n_out > 0 && !dev_out && !host_out) return fail(c, QUAPI_ERR_INVALID, "rho_out is NULL");
     if (small_on(c)) return propagate_small(c, n_steps, sel, n_sel, dev_out, host_out);
     const int N = c->N, L = c->L;
+    c->tile_pending.n = 0;               // an earlier call that failed may have left its own
     int si = 0;          // next selection entry
     int written = 0;     // outputs delivered so far
     int staged = 0;      // outputs in the staging buffer (blocking call)
     auto flush = [&]() -> quapi_status {
         if (!staged) return QUAPI_OK;
-        quapi_status js = join_side(c);
+        quapi_status js = tile_finish(c);
+        if (js == QUAPI_OK) js = join_side(c);
         if (js != QUAPI_OK) return js;
         HIP_TRY(c, hipMemcpyAsync(host_out + (size_t)2 * N * (written - staged), c->stage,
                                   (size_t)staged * N * 16, hipMemcpyDeviceToHost, c->stream));
@@ -1679,6 +1816,34 @@ quapi_status propagate_impl(quapi_ctx *c, int n_steps, const int *sel, int n_sel
     const int first = c->step + 1, last = c->step + n_steps;
     for (int n = first; n <= last; ++n) {
         const bool s0 = is_sel(n, si);
+        if (tile_on(c) && n > L) {
+            // up to four steps in one pass, groups fixed by the global step number
+            const int k = std::min(kTileSteps - (n - L - 1) % kTileSteps, last - n + 1);
+            bool selk[kTileSteps] = {};
+            int nsel = 0;
+            for (int j = 0; j < k; ++j) {
+                selk[j] = is_sel(n + j, si + nsel);
+                nsel += selk[j] ? 1 : 0;
+            }
+            if (!dev_out && staged + nsel > kRhoStage) {
+                st = flush();
+                if (st != QUAPI_OK) return st;
+            }
+            double2 *outs[kTileSteps] = {};
+            double2 *next = dev_out ? dev_out + (size_t)written * N : c->stage + (size_t)staged * N;
+            for (int j = 0; j < k; ++j)
+                if (selk[j]) {
+                    outs[j] = next;
+                    next += N;
+                }
+            st = enqueue_tile(c, n, k, outs);
+            if (st != QUAPI_OK) return st;
+            si += sel ? nsel : 0;
+            written += nsel;
+            if (!dev_out) staged += nsel;
+            n += k - 1;
+            continue;
+        }
         // Three full-window steps n, n+1, n+2 at groups fixed by the global
         // step number -- (L+1, L+2, L+3), (L+4, ..), ... -- as for pairs below.
         if (c->fuse == 3 && n > L && n + 2 <= last && (n - L - 1) % 3 == 0) {
@@ -1784,7 +1949,8 @@ quapi_status propagate_impl(quapi_ctx *c, int n_steps, const int *sel, int n_sel
             if (!dev_out) ++staged;
         }
     }
-    st = join_side(c);
+    st = tile_finish(c);
+    if (st == QUAPI_OK) st = join_side(c);
     if (st != QUAPI_OK) return st;
     if (!dev_out) {
         st = flush();
@@ -1934,6 +2100,9 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
     c->plan2 = (double2 *)(w + lay.off_plan2);
     c->plan3 = (double2 *)(w + lay.off_plan3);
     c->coef3 = w + lay.off_coef3;
+    c->ttab = (double2 *)(w + lay.off_ttab);
+    c->tcoef = w + lay.off_tcoef;
+    c->trows = (double2 *)(w + lay.off_trows);
     c->blk3 = (int *)(w + lay.off_blk3);
     c->low3 = (int *)(w + lay.off_low3);
     c->blk2 = (int *)(w + lay.off_blk2);
@@ -2540,9 +2709,18 @@ quapi_status quapi_get_timing(quapi_ctx *ctx, quapi_timing *out) {
             ctx->acc_ms[r.kind] += ms;
             ctx->acc_n[r.kind] += 1;
             ctx->acc_steps += r.steps;
-            if (r.kind == 0) {
-                ctx->acc_width_ms[r.width] += ms;
-                ctx->acc_width_n[r.width] += 1;
+            if (r.kind == 0 && r.steps > r.width && r.width > 0) {
+                // a pass over more steps than a group: counted as its groups and the rest
+                const int rest = r.steps % r.width;
+                ctx->acc_width_ms[r.width] += ms * (r.steps - rest) / r.steps;
+                ctx->acc_width_n[r.width] += r.steps / r.width;
+                if (rest) {
+                    ctx->acc_width_ms[rest] += ms * rest / r.steps;
+                    ctx->acc_width_n[rest] += 1;
+                }
+            } else if (r.kind == 0) {
+                ctx->acc_width_ms[r.width ? r.steps : 0] += ms;
+                ctx->acc_width_n[r.width ? r.steps : 0] += 1;
             }
         }
         ctx->pool.push_back(r.a);

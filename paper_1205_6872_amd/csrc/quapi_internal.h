@@ -298,6 +298,46 @@ hipError_t launch_step3_coef(const Coef3Args &a, hipStream_t st);
 size_t step3_lds_bytes(int prec, bool with_rho, int R, int Q);
 size_t step2_lds_bytes(int prec, bool with_rho, int R, int Q);
 
+// Four full-window steps per pass (N = 4, L >= kTileMinL; quapi_tile.hip).
+// A group of four steps is fixed by the global step number; stages s0 .. s1-1
+// of it run in one pass.  Digits of the tensor after step n-1: the points
+// d0 .. d3, then the outer digits m (w0, w1, the middle and the top digits).
+constexpr int kTileSteps = 4;
+constexpr int kTileSets = 4 * kTileSteps;            // factor tables: (stage, class, o in {1, 2})
+constexpr int kTileMinL = 8;
+constexpr int kTileCoefK = 48;                       // coefficients in the compute precision, then
+constexpr int kTileCoefCount = kTileCoefK + 16;      // 16 of K in FP64
+constexpr int kTileBlocks = 1024;                    // blocks of a pass (rho rows of a step)
+struct TilePlanArgs {
+    const double2 *bank, *eta;
+    const double *s;
+    int L, d_mid, d_top;
+    double2 *t_w, *t_u, *t_mid, *t_top;              // [set][16], [set][16], [set][4^d_mid], [set][4^d_top]
+    void *coef;                                      // kTileCoefCount reals (8 bytes each)
+};
+// rho of up to four steps from the rows of the pass that ran them.
+struct TileRho {
+    int n, n_rows;                                   // steps to sum; rows of each
+    const double2 *rows[kTileSteps];
+    double2 *out[kTileSteps];
+};
+struct TileArgs {
+    const void *a_in;
+    void *a_out;
+    const double2 *t_w, *t_u, *t_mid, *t_top;
+    const void *coef;
+    double2 *rows;                                   // [stage][n_work][4]
+    long long m_count;                               // N^(L-4)
+    // strides of the entry index in the digits d0 .. d3 (replaced by o0 .. o3
+    // as their stages run) and m, as read and as written
+    long long in_d[4], in_m, out_d[4], out_m;
+    int d_mid, d_top, n_tiles, n_work, s0, s1;
+    TileRho prev;                                    // summed by extra blocks of this launch
+};
+hipError_t launch_tile_tables(int prec, const TilePlanArgs &a, hipStream_t st);
+hipError_t launch_tile(int prec, bool rho, bool mirror, const TileArgs &a, hipStream_t st);
+hipError_t launch_tile_rho(const TileRho &r, hipStream_t st);
+
 // Filtered propagation (quapi_filter.hip): the kept tensor entries as sorted
 // (key, value) pairs.  Fixed grids; the entry count is read from device memory.
 constexpr int kFilterBlock = 256;

@@ -21,22 +21,7 @@
 namespace quapi {
 namespace {
 
-// ------------------------------------------------ compensated summation
-// Neumaier's variant of Kahan summation: s + c carries the running sum.
-__device__ __forceinline__ void neumaier(double &s, double &c, double x) {
-    const double t = s + x;
-    if (fabs(s) >= fabs(x)) c += (s - t) + x;
-    else c += (x - t) + s;
-    s = t;
-}
-// (s1, c1) += (s2, c2) with the rounding error of s1 + s2 kept (Knuth's two-sum).
-__device__ __forceinline__ void two_sum_combine(double &s1, double &c1, double s2, double c2) {
-    const double s = s1 + s2;
-    const double bp = s - s1;
-    const double e = (s1 - (s - bp)) + (s2 - bp);
-    s1 = s;
-    c1 = c1 + c2 + e;
-}
+// ------------------------------------------------ compensated block sums
 // Block-wide compensated reduction of (sum, compensation) pairs for a real
 // and an imaginary part, in a fixed tree order; the totals land in thread 0's
 // arguments.  All B threads of the block must call it.

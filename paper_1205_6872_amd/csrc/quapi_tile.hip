@@ -1,0 +1,757 @@
+// Four full-window propagation steps per pass over the tensor (M = 2, N = 4),
+// with the intermediate tensors kept in the registers of a block: the tile
+// kernel, its tables and their launchers.
+//
+// Method: Dattani 2012, Sec. II (exact path-sum equation and discretized
+// influence functional); the tensor-propagator step of the Introduction,
+// applied up to four times per pass.
+//
+// A block owns a tile: the 4^4 values of the four oldest points d0..d3 times
+// the 16 values of the next two digits w0, w1, 4096 entries, 16 per thread.  A
+// thread holds all values of two of the points in registers, so that a step
+// contracts within the thread: first (d0, d1), steps n and n+1, then, after one
+// exchange through 32 KB of LDS, (d2, d3), steps n+2 and n+3.
+//
+// Bounds and choices (M = 2, rho at every step, one GPU, per step, before ->
+// after, "before" three steps per pass in one thread's registers from L = 13 at
+// complex128 and complex64/FP32 and two otherwise, with two launches for the
+// rho of every step):
+//   L = 15  complex128 1.19 -> 0.91 ms, complex64/FP32 0.65 -> 0.56,
+//           complex64/FP64 0.92 -> 0.68.  One pass of the kept half moves
+//           17.2 GB at complex128; reads and stores of the same pattern alone
+//           take 3.47 ms of the 3.63 ms pass, so complex128 is HBM bound;
+//           FP32 arithmetic is bound by its instructions (about 440 vector
+//           instructions per stage and wave, a quarter of them the exact FP64
+//           sums of the rows that carry the trace).
+//   L = 13  complex64/FP64 84 -> 44 us; L = 12 complex128 53 -> 17 us; L = 10
+//           29 -> 4.5 us; L = 8 24 -> 2.8 us: bound by the launch and by the
+//           latency of one tile's chain; one launch per four steps, the rho of a
+//           pass summed by extra blocks of the next.
+//   16 consecutive entries per store (whole cache lines): with stores of 64 B
+//   from waves that run apart a pass takes 4.8 ms at L = 15; five points per
+//   tile would leave 64 B stores and takes 4.8 ms for the memory alone.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "quapi_device.h"
+#include "quapi_internal.h"
+
+namespace quapi {
+namespace {
+
+constexpr int kWaves = kBlock / 64;
+constexpr int kSets = kTileSets;         // (stage, class, o in {1, 2}) factor tables
+
+// The influence rows of the two off-diagonal points.  For M = 2 and the pair
+// o = 1 (s_0, s_1), D = s_0 - s_1 and a lag of coefficient eta,
+//   F(1, p) = e^{-i phi} { e^{-i theta}, e^{-g}, e^{g}, e^{i theta} },   p = 0 .. 3,
+// phi = D Im(eta) (s_0 + s_1), theta = D^2 Im(eta), g = D^2 Re(eta), and
+// F(2, p) the conjugate with p = 1, 2 swapped.  With the phase e^{-i phi} moved
+// into the factor tables a row takes four real coefficients:
+//   sum_p = cos(theta) (x0 + x3) -+ i sin(theta) (x0 - x3) + e^{-+g} x1 + e^{+-g} x2,
+// 8 real multiply-adds instead of 16, and x0 + x3 serves the diagonal rows too.
+//
+// Coefficients in the compute precision, read by scalar loads: cos, sin,
+// e^{-g}, e^{g} of the oldest point (lag L; interior, final class) and of the
+// group digit at lag L-1 (stages 0 and 2, "pair 0"); for the group digit e at
+// lag 1, with K (stages 1 and 3, "pair 1"), per e the complex factors of
+// o = 1, 2 (interior), then the final class; then per e K[0][e], K[3][e], in FP64 in every tier (at the
+// kTileCoefK-th double).
+constexpr int kTcOld = 0, kTcOldf = 4, kTcE = 8, kTcEf = 12, kTcLag1 = 16;
+
+__device__ __forceinline__ constexpr int mirror_d(int d) { return d == 1 ? 2 : d == 2 ? 1 : d; }
+
+// Bits of x -> base-4 digits 3 or 0.
+__device__ __forceinline__ int diagonal_digits_t(unsigned x) {
+    int out = 0;
+    for (int k = 0; x > 0; ++k, x >>= 1) out |= (int)(x & 1u) * 3 << (2 * k);
+    return out;
+}
+
+// The high-digit value of tile index idx over k digits.  Mirror mode runs the
+// values below their mirror, ordered by the place p of their highest
+// off-diagonal digit (digit p is 1, those above it diagonal, those below it
+// any: 2^(k-1-p) 4^p values), then the 2^k values that are their own mirror.
+__device__ __forceinline__ int tile_hi(int idx, int k, bool mirror, bool *self) {
+    *self = false;
+    if (!mirror) return idx;
+    for (int p = k - 1; p >= 0; --p) {
+        const int cnt = 1 << (k - 1 + p);
+        if (idx < cnt) {
+            const int low = idx & ((1 << (2 * p)) - 1);
+            return (diagonal_digits_t((unsigned)idx >> (2 * p)) << (2 * (p + 1))) | (1 << (2 * p)) | low;
+        }
+        idx -= cnt;
+    }
+    *self = true;
+    return diagonal_digits_t((unsigned)idx);
+}
+
+// ------------------------------------------------------------------ tables
+// set q = (s * 2 + cls) * 2 + (o - 1): t_w[q][w0 + 4 w1], t_u[q][u0 + 4 u1],
+// t_mid[q][v], t_top[q][v], all FP64; coef in the compute precision.
+__device__ int tile_tab(const BankLayout &B, int lag, int cls) {
+    if (lag == 1) return cls ? B.k_fin1() : B.k_lag1();
+    return cls ? B.fin(lag) : B.lag(lag);
+}
+template <typename T>
+__global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs a) {
+    const BankLayout B{a.L};
+    const int L = a.L;
+    const int n_mid = 1 << (2 * a.d_mid), n_top = 1 << (2 * a.d_top);
+    // F(mirror(o), mirror(p)) = conj(F(o, p)) bit for bit (the bank's K has it
+    // to rounding), so that an entry and its mirror come out exactly conjugate
+    // and a pass may take either: its results do not depend on which it read
+    auto tab = [&](int t, int row, int col) {
+        const int k = row * 4 + col, km = mirror_d(row) * 4 + mirror_d(col);
+        double2 v = a.bank[(size_t)t * 16 + (km < k ? km : k)];
+        if (km < k) v.y = -v.y;
+        if (km == k) v.y = 0.0;
+        return v;
+    };
+    const long long total = (long long)kSets * (32 + n_mid + n_top) + kTileCoefCount;
+    for (long long idx = (long long)blockIdx.x * kBlock + threadIdx.x; idx < total;
+         idx += (long long)gridDim.x * kBlock) {
+        if (idx >= (long long)kSets * (32 + n_mid + n_top)) {
+            const int k = (int)(idx - (long long)kSets * (32 + n_mid + n_top));
+            double v;
+            if (k < kTcLag1) {
+                const double2 eta = a.eta[1 + (k / 4 % 2 ? 2 * L : 0) + (k < kTcE ? L : L - 1)];
+                const double D = a.s[0] - a.s[1], th = D * D * eta.y, g = D * D * eta.x;
+                v = k % 4 == 0 ? cos(th) : k % 4 == 1 ? sin(th) : exp(k % 4 == 2 ? -g : g);
+            } else if (k < kTileCoefK) {
+                const int e = (k - kTcLag1) / 8, cls = k / 4 % 2, o = 1 + k / 2 % 2;
+                const double2 f = tab(tile_tab(B, 1, cls), o, e);
+                v = k % 2 ? f.y : f.x;
+            } else {
+                const double2 f = tab(B.k_lag1(), k / 2 % 2 * 3, (k - kTileCoefK) / 4);
+                v = k % 2 ? f.y : f.x;
+                if (sizeof(T) == 4) v = (float)v;           // exact: the diagonal rows of K are FP32 values
+                ((double *)a.coef)[k] = v;
+                continue;
+            }
+            ((T *)a.coef)[k] = (T)v;
+            continue;
+        }
+        int q, v, j0, nd;
+        double2 *out;
+        if (idx < kSets * 16) {
+            q = (int)(idx / 16); v = (int)(idx % 16); j0 = 0; nd = 2;
+            out = a.t_w + idx;
+        } else if (idx < kSets * 32) {
+            const int k = (int)idx - kSets * 16;
+            q = k / 16; v = k % 16; j0 = -1; nd = 2;
+            out = a.t_u + k;
+        } else if (idx < (long long)kSets * (32 + n_mid)) {
+            const int k = (int)(idx - kSets * 32);
+            q = k / n_mid; v = k % n_mid; j0 = 2; nd = a.d_mid;
+            out = a.t_mid + k;
+        } else {
+            const int k = (int)(idx - (long long)kSets * (32 + n_mid));
+            q = k / n_top; v = k % n_top; j0 = 2 + a.d_mid; nd = a.d_top;
+            out = a.t_top + k;
+        }
+        const int s = q / 4, cls = q / 2 % 2, o = 1 + q % 2;
+        double2 p = make_double2(1.0, 0.0);
+        if (j0 == 0) {
+            // t_w also carries the self factor and the phases e^{-+i phi} of the
+            // oldest point and (pair 0) of the group digit
+            const double ph = (a.s[0] - a.s[1]) * (a.s[0] + a.s[1]);
+            const double2 *eta = a.eta + 1 + (cls ? 2 * L : 0);
+            double sn, cs;
+            sincos(ph * (eta[L].y + (s % 2 == 0 ? eta[L - 1].y : 0.0)), &sn, &cs);
+            p = cmul(tab(cls ? B.self_end() : B.self_int(), o, 0), make_double2(cs, o == 1 ? -sn : sn));
+        }
+        for (int j = 0; j < nd; ++j, v >>= 2) {
+            // the lag from step n+s: outer digit j0 + j; for t_u the two points
+            // that are thread digits at stage s (d2, d3, then o0, o1)
+            const int lag = j0 >= 0 ? L - kTileSteps - (j0 + j) + s : s < 2 ? L + s - 2 - j : s - j;
+            p = cmul(p, tab(tile_tab(B, lag, cls), o, v & 3));
+        }
+        *out = p;
+    }
+}
+
+// ---------------------------------------------------------------- exchange
+// Thread layouts: A: registers (d0, d1), lane (d2, d3, w0), wave w1; B:
+// registers (d2, d3), lane (w0, w1, o0), wave o1, so that a wave stores 16
+// consecutive entries (whole cache lines) at a time.  Slot of an entry in the
+// block's LDS: low 5 bits d2 ^ w1 | (d3 ^ (w0_hi | d0_lo << 1)) << 2 | w0_lo << 4,
+// above them w1, w0_hi, d0, d1: the 8-byte accesses of 32 consecutive lanes
+// cover the 64 banks once in both layouts.
+struct XLane {
+    int wr, rd;
+    __device__ __forceinline__ XLane(int lane, int wave) {
+        const int d2 = lane & 3, d3 = (lane >> 2) & 3, w = lane >> 4;
+        wr = (d2 ^ wave) + ((d3 ^ (w >> 1)) << 2) + ((w & 1) << 4) + 32 * wave + 128 * (w >> 1);
+        const int w0 = lane & 3, w1 = (lane >> 2) & 3, o0 = lane >> 4;
+        rd = w1 + (((w0 >> 1) | (o0 & 1) << 1) << 2) + ((w0 & 1) << 4) + 32 * w1 + 128 * (w0 >> 1) + 256 * o0 +
+             1024 * wave;
+    }
+};
+// Orders this wave's LDS accesses (LDS runs a wave's accesses in order).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// 8 bytes per slot: a complex64 value, or one component of a complex128 value
+// at a time (a whole one would take twice the LDS, half the waves).
+template <typename C> struct XSlot;
+template <> struct XSlot<float2> {
+    static constexpr int kParts = 1;
+    using type = float2;
+    static __device__ __forceinline__ float2 get(float2 v, int) { return v; }
+    static __device__ __forceinline__ void set(float2 &v, float2 s, int) { v = s; }
+};
+template <> struct XSlot<double2> {
+    static constexpr int kParts = 2;
+    using type = double;
+    static __device__ __forceinline__ double get(double2 v, int part) { return part ? v.y : v.x; }
+    static __device__ __forceinline__ void set(double2 &v, double s, int part) { (part ? v.y : v.x) = s; }
+};
+// The slot of register r in layouts A and B.
+__device__ __forceinline__ int slot_a(const XLane &x, int r) { return (x.wr ^ ((r & 1) << 3)) + 256 * r; }
+__device__ __forceinline__ int slot_b(const XLane &x, int r) { return x.rd ^ r; }
+// between(): what the block does once every wave has left the buffer (and the
+// phase that reads it) of the tile before.
+template <typename C, typename F>
+__device__ __forceinline__ void exchange(C (&w)[16], void *buf, const XLane &x, F between) {
+    using X = XSlot<C>;
+    typename X::type *b = (typename X::type *)buf;
+#pragma unroll
+    for (int part = 0; part < X::kParts; ++part) {
+        __syncthreads();                   // the buffer's last readers are done
+        if (part == 0) between();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) b[slot_a(x, r)] = X::get(w[r], part);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) X::set(w[r], b[slot_b(x, r)], part);
+    }
+}
+// ------------------------------------------------------------- rho over blocks
+// rho of one step from its block rows (4 complex values each), compensated,
+// in a fixed order: a thread takes one of the 8 doubles of every 32nd row,
+// the 32 row lanes are combined in a wave and then over the waves.
+__device__ void tile_rho_sum(const double *__restrict__ rows, int n_rows, double *out, double2 *s_x) {
+    const int t = threadIdx.x, q = t & 7, lane = t & 63, wave = t >> 6;
+    double s = 0.0, c = 0.0;
+    int r = t >> 3;
+    constexpr int U = 4, kStep = kBlock / 8;
+    for (; r + (U - 1) * kStep < n_rows; r += U * kStep) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = rows[(size_t)(r + u * kStep) * 8 + q];
+#pragma unroll
+        for (int u = 0; u < U; ++u) neumaier(s, c, v[u]);
+    }
+    for (; r < n_rows; r += kStep) neumaier(s, c, rows[(size_t)r * 8 + q]);
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) {
+        const double s2 = __shfl_xor(s, off, 64), c2 = __shfl_xor(c, off, 64);
+        // the lower lane's pair first on both sides, so that both hold the same
+        double a = (lane & off) ? s2 : s, ac = (lane & off) ? c2 : c;
+        two_sum_combine(a, ac, (lane & off) ? s : s2, (lane & off) ? c : c2);
+        s = a;
+        c = ac;
+    }
+    if (lane < 8) s_x[wave * 8 + lane] = make_double2(s, c);
+    __syncthreads();
+    if (t < 8) {
+        double2 a = s_x[t];
+        for (int w = 1; w < kWaves; ++w) two_sum_combine(a.x, a.y, s_x[w * 8 + t].x, s_x[w * 8 + t].y);
+        out[t] = a.x + a.y;
+    }
+}
+
+__global__ void __launch_bounds__(kBlock) tile_rho_kernel(const TileRho r) {
+    __shared__ double2 s_x[kWaves * 8];
+    tile_rho_sum((const double *)r.rows[blockIdx.x], r.n_rows, (double *)r.out[blockIdx.x], s_x);
+}
+
+// --------------------------------------------------------------------- pass
+// D += E_q B over the wave, E_q the 4x4 matrix with ones in row q (4x4x4
+// FP64 MFMA, four blocks): adds the wave's values v, reduced 4 : 1, to the 16
+// lanes 16 q .. 16 q + 15 of acc.  Four such calls keep four running sums in
+// one register pair, where per-lane sums would take four pairs for every
+// stage (and shuffles of each at the end of every tile).
+__device__ __forceinline__ double row_add(double acc, double v, int q, int lane) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64((lane & 3) == q ? 1.0 : 0.0, v, acc, 0, 0, 0);
+}
+
+// The coefficient pointer through an opaque move: loads through it stay at
+// their use instead of being kept live in scalar registers.
+template <typename T>
+__device__ __forceinline__ const T *fresh_t(const T *p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// Wave-uniform read of one coefficient (see coef_ld).
+template <typename T>
+__device__ __forceinline__ T coef_s(const T *p, int k) {
+    return ((const __attribute__((address_space(4))) T *)p)[k];
+}
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+
+// The contraction of the oldest point for o = 1 (SIGN +) or o = 2 (SIGN -):
+// p = x0 + x3, q = x0 - x3, coefficients at k.  The terms of x1 and x2 are
+// taken in mirrored orders for the two points, so that the mirrored group
+// gives the exact conjugate.
+template <int SIGN, typename T, typename C>
+__device__ __forceinline__ C row12(const T *co, int k, C p, C q, C x1, C x2) {
+    const T c = coef_s(co, k), sn = SIGN > 0 ? coef_s(co, k + 1) : -coef_s(co, k + 1);
+    const T g1 = coef_s(co, k + 2), g2 = coef_s(co, k + 3);
+    const C a = SIGN > 0 ? x1 : x2, b = SIGN > 0 ? x2 : x1;
+    C r;
+    r.x = fma_t(g2, b.x, fma_t(g1, a.x, fma_t(sn, q.y, c * p.x)));
+    r.y = fma_t(g2, b.y, fma_t(g1, a.y, fma_t(-sn, q.x, c * p.y)));
+    return r;
+}
+
+// One step on the 16 values of a lane: digit PAIR of the register index
+// (stride 4^PAIR) is contracted, the groups are the other digit e.  c1, c2: the
+// thread's factors of the new points 1 and 2 (interior); prev: the previous
+// point when it is not e (PAIR 0), wave-uniform.  With RHO: tf1, tf2 the
+// final-point sums of the lane without the thread's factor, rd0 and rd3 the
+// terms of the diagonal points (REAL: their real parts only).
+template <typename T, bool RHO, bool REAL, int PAIR, typename CI>
+__device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::type (&w)[16],
+                                           const T *coef, typename Cx<T>::type c1,
+                                           typename Cx<T>::type c2, int prev, typename Cx<T>::type &tf1,
+                                           typename Cx<T>::type &tf2, double2 &rd0, double2 &rd3) {
+    using C = typename Cx<T>::type;
+    constexpr int SI = PAIR == 0 ? 1 : 4, SE = PAIR == 0 ? 4 : 1;
+    const T *co = fresh_t(coef);
+    double2 all = make_double2(0.0, 0.0);
+    if (RHO) {
+        tf1 = C{};
+        tf2 = C{};
+        rd0 = rd3 = make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        __builtin_amdgcn_sched_barrier(0);      // a group at a time: fewer live registers
+        const T *ce = PAIR == 0 ? co : fresh_t(coef);
+        const C x0 = conv<C>(in[SE * e]), x1 = conv<C>(in[SE * e + SI]);
+        const C x2 = conv<C>(in[SE * e + 2 * SI]), x3 = conv<C>(in[SE * e + 3 * SI]);
+        const C p = cadd(x0, x3);
+        C q;
+        q.x = x0.x - x3.x;
+        q.y = x0.y - x3.y;
+        // the diagonal points 0 and 3 carry no influence: K times the plain sum
+        // (K[0][e], K[3][e] are real for e = 0, 3)
+        TraceSum<C> sd;
+        if constexpr (sizeof(T) == 4) {
+            TraceSum<C> s2;
+            sd.init(x0);
+            sd.add(x3);
+            s2.init(x1);
+            s2.add(x2);
+            sd.s = cadd(sd.s, s2.s);
+        } else {
+            sd.init(cadd(p, cadd(x1, x2)));
+        }
+        const double *kd = (const double *)ce + kTileCoefK + 4 * (PAIR == 0 ? prev : e);
+        const double2 d0 = coef_ld(kd, 0), d3 = coef_ld(kd, 1), ds = sd.s;
+        if (PAIR == 1 && (e == 0 || e == 3)) {
+            w[SE * e] = from_d2<C>(make_double2(d0.x * ds.x, d0.x * ds.y));
+            w[SE * e + 3 * SI] = from_d2<C>(make_double2(d3.x * ds.x, d3.x * ds.y));
+        } else {
+            w[SE * e] = from_d2<C>(cmul(d0, ds));
+            w[SE * e + 3 * SI] = from_d2<C>(cmul(d3, ds));
+        }
+        if (RHO) {
+            if (PAIR == 0) {
+                all = cadd(all, ds);
+            } else if (REAL) {
+                rd0.x = fma(d0.x, ds.x, rd0.x);
+                rd3.x = fma(d3.x, ds.x, rd3.x);
+                if (e == 1 || e == 2) {
+                    rd0.x = fma(-d0.y, ds.y, rd0.x);
+                    rd3.x = fma(-d3.y, ds.y, rd3.x);
+                }
+            } else {
+                cmac(rd0, d0, ds);
+                cmac(rd3, d3, ds);
+            }
+        }
+        // e's own factor: for pair 0 the four-coefficient form of the row
+        auto factor_e = [&](int o, bool fin) {
+            C f;
+            if (PAIR == 0) {
+                const int k = fin ? kTcEf : kTcE;
+                f.x = coef_s(ce, e == 1 || e == 2 ? k + ((e == 1) == (o == 1) ? 2 : 3) : k);
+                f.y = (e == 0) == (o == 1) ? -coef_s(ce, k + 1) : coef_s(ce, k + 1);
+            } else {
+                const int k = kTcLag1 + 8 * e + 2 * (o - 1) + (fin ? 4 : 0);
+                f.x = coef_s(ce, k);
+                f.y = coef_s(ce, k + 1);
+            }
+            return f;
+        };
+        constexpr bool kRealE = PAIR == 0;            // factors of e = 1, 2 are real
+        auto with_e = [&](C c, int o) {
+            const C f = factor_e(o, false);
+            if (!(kRealE && (e == 1 || e == 2))) return cmul(c, f);
+            c.x *= f.x;
+            c.y *= f.x;
+            return c;
+        };
+        auto add_e = [&](C &sum, C v, int o) {        // sum += factor * v (final class)
+            const C f = factor_e(o, true);
+            if (kRealE && (e == 1 || e == 2)) {
+                sum.x = fma_t(v.x, f.x, sum.x);
+                sum.y = fma_t(v.y, f.x, sum.y);
+            } else {
+                cmac(sum, v, f);
+            }
+        };
+        const C s1 = row12<1>(co, kTcOld, p, q, x1, x2), s2 = row12<-1>(co, kTcOld, p, q, x1, x2);
+        w[SE * e + SI] = cmul(with_e(c1, 1), s1);
+        w[SE * e + 2 * SI] = cmul(with_e(c2, 2), s2);
+        if (RHO) {
+            add_e(tf1, row12<1>(co, kTcOldf, p, q, x1, x2), 1);
+            add_e(tf2, row12<-1>(co, kTcOldf, p, q, x1, x2), 2);
+        }
+    }
+    if (RHO && PAIR == 0) {
+        const double *kd = (const double *)co + kTileCoefK + 4 * prev;
+        rd0 = cmul(coef_ld(kd, 0), all);
+        rd3 = cmul(coef_ld(kd, 1), all);
+    }
+}
+
+// Stages s0 .. s1-1 of the group of four steps n .. n+3 (n > L, n - L - 1 a
+// multiple of 4).  The stage range only says which of the steps run and where
+// the entries are read and written: every entry and every rho sum is formed
+// by the same operations whatever the ranges a group is run in.
+// PART: kWhole all four stages; kFront some of stages 0 and 1 (no exchange);
+// kBack any other range (one kernel for all of them holds more registers than
+// there are: M = 2, L = 15, complex128, 3.70 -> 4.18 ms a whole pass).
+// AHEAD (FP64 arithmetic): a tile is read after the first stage of the tile
+// before it, which frees the registers; with the reads in flight under the
+// other stages and ahead of the stores two waves per SIMD do better than three
+// without them (L = 15, complex128, 3.90 -> 3.66 ms a pass, against 3.47 ms for
+// the reads and stores alone), but only where a block has several tiles.
+enum { kWhole, kFront, kBack };
+template <typename S, typename T, bool RHO, bool MIRROR, int PART, bool AHEAD>
+__global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileArgs a) {
+    constexpr bool WHOLE = PART == kWhole;
+    using C = typename Cx<T>::type;
+    using CS = typename Cx<S>::type;
+    __shared__ __align__(16) unsigned char s_buf[kWaves][1024 * 8];
+    __shared__ C s_u[kSets * 16];
+    __shared__ C s_w[kWaves][64];              // [w1][set][w0]
+    double2 *const s_red = (double2 *)s_buf;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    if ((int)blockIdx.x >= a.n_work) {
+        // the rho of the pass before (its rows were written by another launch)
+        const int k = (int)blockIdx.x - a.n_work;
+        tile_rho_sum((const double *)a.prev.rows[k], a.prev.n_rows, (double *)a.prev.out[k], s_red);
+        return;
+    }
+    const T *coef = (const T *)a.coef;
+    // layout A: lane (d2, d3, w0); layout B: lane (w0, o0, o1); w1 = wave
+    double acc[RHO ? kTileSteps : 1][MIRROR ? 1 : 2];
+#pragma unroll
+    for (int s = 0; s < (RHO ? kTileSteps : 1); ++s)
+#pragma unroll
+        for (int k = 0; k < (MIRROR ? 1 : 2); ++k) acc[s][k] = 0.0;
+    const int s0 = a.s0, s1 = a.s1;
+    const CS *__restrict__ ain = (const CS *)a.a_in;
+    CS *__restrict__ aout = (CS *)a.a_out;
+    const long long mc = a.m_count;
+
+    // The entries of a tile, with the tile's table values.
+    CS x[16];                              // as stored (converting waits for the read)
+    double2 top, mid;
+    const double2 tw = a.t_w[(lane >> 2) * 16 + (lane & 3) + 4 * wave];
+    auto read_tile = [&](int hi, bool self, int lane) {
+        const int set = lane >> 2, ua = lane & 15, wa = lane >> 4;
+        top = a.t_top[((size_t)set << (2 * a.d_top)) + (hi >> (2 * a.d_mid))];
+        mid = a.t_mid[((size_t)set << (2 * a.d_mid)) + (hi & ((1 << (2 * a.d_mid)) - 1))];
+        if constexpr (WHOLE) {
+            // a tile that is its own mirror: the entries above their mirror hold
+            // no valid value, their mirror's conjugate (of the same tile) does
+            const int b = (wa + 4 * wave) * 256 + 16 * ua, bm = MIRROR ? (int)mirror4(b) : b;
+            const CS *p = ain + (long long)hi * 4096 + (self ? min(b, bm) : b);
+            if (!self) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) x[r] = p[r];
+                // the reads of each branch stay whole and in it (merged over the
+                // branches they are split into components: 3.7 -> 4.6 ms a pass)
+                asm volatile("" ::: "memory");
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int rm = (int)mirror4(r);
+                    x[r] = p[b < bm ? r : b > bm ? rm : min(r, rm)];
+                }
+                asm volatile("" ::: "memory");
+            }
+        } else {
+            // part of a group: any entry, by its index (an entry above its
+            // mirror through the mirror)
+            const long long x0 = ((long long)hi * 16 + 4 * wave + wa) * a.in_m + (ua & 3) * a.in_d[2] +
+                                 (ua >> 2) * a.in_d[3];
+            const long long x0m = MIRROR ? mirror4(x0) : x0;
+            long long da = a.in_d[0], db = a.in_d[1];
+            asm volatile("" : "+s"(da), "+s"(db));     // their multiples are not kept over the tiles
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int rm = (int)mirror4(r);
+                const long long i = x0 + (r & 3) * da + (r >> 2) * db;
+                const long long im = MIRROR ? x0m + (rm & 3) * da + (rm >> 2) * db : i;
+                x[r] = ain[im < i ? im : i];
+                if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    // the conjugates of the entries that were read at their mirror
+    auto fix_tile = [&](int hi, bool self, int lane) {
+        const int ua = lane & 15, wa = lane >> 4;
+        if (WHOLE ? !self : !MIRROR) return;
+        const long long x0 = WHOLE ? (wa + 4 * wave) * 256 + 16 * ua
+                                   : ((long long)hi * 16 + 4 * wave + wa) * a.in_m + (ua & 3) * a.in_d[2] +
+                                         (ua >> 2) * a.in_d[3];
+        const long long x0m = mirror4(x0);
+        long long da = WHOLE ? 1 : a.in_d[0], db = WHOLE ? 4 : a.in_d[1];
+        if (!WHOLE) asm volatile("" : "+s"(da), "+s"(db));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int rm = (int)mirror4(r);
+            const long long i = x0 + (r & 3) * da + (r >> 2) * db;
+            const long long im = x0m + (rm & 3) * da + (rm >> 2) * db;
+            if (im < i) x[r].y = -x[r].y;
+            if (im == i) x[r].y = 0.0f;              // its own conjugate (another kernel's rounding aside)
+        }
+    };
+    const int k_hi = a.d_mid + a.d_top;
+    bool self, self_next = false;
+    int hi = tile_hi(blockIdx.x, k_hi, MIRROR, &self), hi_next = 0;
+    if (AHEAD) read_tile(hi, self, lane);
+    for (int idx = blockIdx.x; idx < a.n_tiles; idx += a.n_work, hi = hi_next, self = self_next) {
+        // opaque per tile: what the lane's position gives (LDS slots, offsets)
+        // is formed again for each tile rather than held in registers
+        int lane = t & 63;
+        asm volatile("" : "+v"(lane));
+        const XLane xl(lane, wave);
+        const int ua = lane & 15, wa = lane >> 4;
+        const int wb = lane & 15, ub = (lane >> 4) + 4 * wave;
+        C w[16];
+        if (!AHEAD) read_tile(hi, self, lane);
+        if (idx == (int)blockIdx.x) {
+            s_u[t] = from_d2<C>(a.t_u[t]);         // once, behind the first tile's loads
+            __syncthreads();
+        }
+        // lane set * 4 + w0 forms the factor of its set for the wave's w1.  The
+        // sets of stages 0 and 1 (lanes 0 .. 31) are read by this wave only;
+        // those of stages 2 and 3 by every wave, after the exchange's barriers
+        C tile_f;
+        {
+            tile_f = from_d2<C>(cmul(cmul(top, mid), tw));
+            wave_fence();
+            if (lane < 32) s_w[wave][lane] = tile_f;
+            wave_fence();
+        }
+        // the factor of set q over the thread's fixed digits, w0 + 4 w1 = wl
+        auto factor = [&](int q, int wl, int ul) {
+            return cmul(s_w[wl >> 2][q * 4 + (wl & 3)], s_u[q * 16 + ul]);
+        };
+        const int wl = wa + 4 * wave;
+        // one stage's rho terms into the running sums
+        auto add_rho = [&](int s, int wl, int ul, C tf1, C tf2, double2 v0, double2 v3) {
+            const double2 v1 = to_d2(cmul(factor(4 * s + 2, wl, ul), tf1));
+            const double2 v2 = to_d2(cmul(factor(4 * s + 3, wl, ul), tf2));
+            if constexpr (MIRROR) {
+                // a tile below its mirror also stands for the mirrored tile
+                // (conjugate, points 1 and 2 swapped); rho[2] = conj(rho[1])
+                const double two = self ? 1.0 : 2.0, one = self ? 0.0 : 1.0;
+                acc[s][0] = row_add(acc[s][0], two * v0.x, 0, lane);
+                acc[s][0] = row_add(acc[s][0], two * v3.x, 1, lane);
+                acc[s][0] = row_add(acc[s][0], fma(one, v2.x, v1.x), 2, lane);
+                acc[s][0] = row_add(acc[s][0], fma(-one, v2.y, v1.y), 3, lane);
+            } else {
+                acc[s][0] = row_add(acc[s][0], v0.x, 0, lane);
+                acc[s][0] = row_add(acc[s][0], v0.y, 1, lane);
+                acc[s][0] = row_add(acc[s][0], v1.x, 2, lane);
+                acc[s][0] = row_add(acc[s][0], v1.y, 3, lane);
+                acc[s][1] = row_add(acc[s][1], v2.x, 0, lane);
+                acc[s][1] = row_add(acc[s][1], v2.y, 1, lane);
+                acc[s][1] = row_add(acc[s][1], v3.x, 2, lane);
+                acc[s][1] = row_add(acc[s][1], v3.y, 3, lane);
+            }
+        };
+        C tf1, tf2;
+        double2 rd0, rd3;
+        // storage narrower than the arithmetic: the rounding of the stored
+        // pair groups, (n, n+1) and (n+2, n+3)
+        auto round_pair = [&]() {
+            if (sizeof(S) < sizeof(T)) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) w[r] = conv<C>(conv<CS>(w[r]));
+            }
+        };
+        fix_tile(hi, self, lane);
+        if (s0 <= 0) {
+            const int prev = hi >> (2 * (k_hi - 1));                   // point n-1
+            tile_stage<T, RHO, MIRROR, 0>(x, w, coef, factor(0, wl, ua), factor(1, wl, ua), prev, tf1, tf2, rd0,
+                                          rd3);
+            if (RHO) add_rho(0, wl, ua, tf1, tf2, rd0, rd3);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) w[r] = conv<C>(x[r]);
+        }
+        if (idx + a.n_work < a.n_tiles) {
+            hi_next = tile_hi(idx + a.n_work, k_hi, MIRROR, &self_next);
+            if (AHEAD) read_tile(hi_next, self_next, lane);
+        }
+        if (s0 <= 1 && s1 > 1) {
+            tile_stage<T, RHO, MIRROR, 1>(w, w, coef, factor(4, wl, ua), factor(5, wl, ua), 0, tf1, tf2, rd0, rd3);
+            if (RHO) add_rho(RHO ? 1 : 0, wl, ua, tf1, tf2, rd0, rd3);
+            round_pair();
+        }
+        // the 16 entries y0 + (r % 4) da + (r / 4) db of a part of a group (at the
+        // mirrored address, conjugated, when above their mirror; a tile that is
+        // its own mirror stores only those not above it)
+        auto store_part = [&](long long y0, long long da, long long db) {
+            asm volatile("" : "+s"(da), "+s"(db));     // their multiples are not kept over the tiles
+            const long long y0m = MIRROR ? mirror4(y0) : y0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int rm = (int)mirror4(r);
+                const long long y = y0 + (r & 3) * da + (r >> 2) * db;
+                const long long ym = MIRROR ? y0m + (rm & 3) * da + (rm >> 2) * db : y;
+                C v = w[r];
+                if (ym < y) v.y = -v.y;
+                if (!(ym < y && self)) aout[ym < y ? ym : y] = conv<CS>(v);
+                if (r % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if constexpr (PART == kFront) {
+            // the digits d2, d3, w0 that follow each other in memory are the lane's here
+            store_part(((long long)hi * 16 + 4 * wave + wa) * a.out_m + (ua & 3) * a.out_d[2] +
+                           (ua >> 2) * a.out_d[3],
+                       a.out_d[0], a.out_d[1]);
+        } else {
+        exchange(w, s_buf, xl, [&]() {
+            if (lane >= 32) s_w[wave][lane] = tile_f;
+        });
+        if (s0 <= 2 && s1 > 2) {
+            tile_stage<T, RHO, MIRROR, 0>(w, w, coef, factor(8, wb, ub), factor(9, wb, ub), wave, tf1, tf2, rd0, rd3);
+            if (RHO) add_rho(RHO ? 2 : 0, wb, ub, tf1, tf2, rd0, rd3);
+        }
+        if (s1 > 3) {
+            tile_stage<T, RHO, MIRROR, 1>(w, w, coef, factor(12, wb, ub), factor(13, wb, ub), 0, tf1, tf2, rd0, rd3);
+            if (RHO) add_rho(RHO ? 3 : 0, wb, ub, tf1, tf2, rd0, rd3);
+        }
+        const long long m = (long long)hi * 16 + wb;        // layout B's m
+        if (WHOLE) {
+            // an output above its mirror goes to the mirrored address as its
+            // conjugate (the entry the mirrored tile, which does not run, owns);
+            // a tile that is its own mirror forms those entries too, and stores
+            // only the ones not above their mirror
+            const int ubm = mirror_d(ub & 3) + 4 * mirror_d(ub >> 2);
+            CS *const pd = aout + m + mc * ub;
+            CS *const pm = aout + mirror4(m) + mc * ubm;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int rm = (int)mirror4(r);
+                const bool direct = !MIRROR || r < rm || (r == rm && ub <= ubm);
+                if (MIRROR && self && (!direct || (r == rm && ub == ubm && wb > (int)mirror4(wb)))) continue;
+                C v = w[r];
+                if (!direct) v.y = -v.y;
+                // the 16 plane offsets are formed per store, not all kept
+                long long plane = 16 * mc;
+                asm volatile("" : "+s"(plane));
+                CS *const p = (direct ? pd : pm) + plane * (direct ? r : rm);
+                *p = conv<CS>(v);
+            }
+        } else {
+            store_part(m * a.out_m + (ub & 3) * a.out_d[0] + (ub >> 2) * a.out_d[1], a.out_d[2], a.out_d[3]);
+        }
+        }
+    }
+    if constexpr (RHO) {
+        // rows of the block: [stage][block][4 complex]
+        __syncthreads();                   // s_red shares the exchange buffer
+#pragma unroll
+        for (int s = 0; s < kTileSteps; ++s) {
+#pragma unroll
+            for (int k = 0; k < (MIRROR ? 1 : 2); ++k) {
+                double v = acc[s][k];
+                for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+                if ((lane & 15) == 0) ((double *)s_red)[((s * 2 + k) * kWaves + wave) * 4 + (lane >> 4)] = v;
+            }
+        }
+        __syncthreads();
+        if (t < kTileSteps * 8) {
+            const int s = t / 8, q = t % 8;    // double q of the row: (rho[q / 2]).(q % 2)
+            auto sum = [&](int k, int row) {
+                double v = 0.0;
+                for (int w = 0; w < kWaves; ++w) v += ((const double *)s_red)[((s * 2 + k) * kWaves + w) * 4 + row];
+                return v;
+            };
+            double v;
+            if (MIRROR) v = q == 0 ? sum(0, 0) : q == 6 ? sum(0, 1) : q == 2 || q == 4 ? sum(0, 2)
+                          : q == 3 ? sum(0, 3) : q == 5 ? -sum(0, 3) : 0.0;
+            else v = sum(q / 4, q % 4);
+            ((double *)a.rows)[((size_t)s * a.n_work + blockIdx.x) * 8 + q] = v;
+        }
+    }
+}
+
+template <typename S, typename T, bool RHO, bool MIRROR, bool AHEAD>
+hipError_t launch_tile_w(const TileArgs &a, hipStream_t st) {
+    const dim3 g(a.n_work + a.prev.n), b(kBlock);
+    if (a.s1 - a.s0 == kTileSteps)
+        hipLaunchKernelGGL((tile_kernel<S, T, RHO, MIRROR, kWhole, AHEAD>), g, b, 0, st, a);
+    else if (a.s1 <= 2) hipLaunchKernelGGL((tile_kernel<S, T, RHO, MIRROR, kFront, AHEAD>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((tile_kernel<S, T, RHO, MIRROR, kBack, AHEAD>), g, b, 0, st, a);
+    return hipGetLastError();
+}
+template <typename S, typename T>
+hipError_t launch_tile_t(bool rho, bool mirror, const TileArgs &a, hipStream_t st) {
+    // Tiles are read ahead from eight per block (mirror mode: L = 13) on: with
+    // two or three a block finishes sooner three to a compute unit (L = 12,
+    // complex128, 60 steps: 1.06 ms ahead, 1.02 ms not).  FP32 arithmetic fits
+    // four waves per SIMD and is bound by its instructions either way.
+    if constexpr (sizeof(T) == 8) {
+        if (mirror && a.n_tiles >= 8 * a.n_work)
+            return rho ? launch_tile_w<S, T, true, true, true>(a, st) : launch_tile_w<S, T, false, true, true>(a, st);
+    }
+    if (rho)
+        return mirror ? launch_tile_w<S, T, true, true, false>(a, st) : launch_tile_w<S, T, true, false, false>(a, st);
+    return mirror ? launch_tile_w<S, T, false, true, false>(a, st) : launch_tile_w<S, T, false, false, false>(a, st);
+}
+
+}  // namespace
+
+hipError_t launch_tile(int prec, bool rho, bool mirror, const TileArgs &a, hipStream_t st) {
+    switch (prec) {
+    case kPrecC128: return launch_tile_t<double, double>(rho, mirror, a, st);
+    case kPrecC64: return launch_tile_t<float, float>(rho, mirror, a, st);
+    case kPrecC64F64: return launch_tile_t<float, double>(rho, mirror, a, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_tile_rho(const TileRho &r, hipStream_t st) {
+    if (r.n < 1) return hipSuccess;
+    hipLaunchKernelGGL(tile_rho_kernel, dim3(r.n), dim3(kBlock), 0, st, r);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_tables(int prec, const TilePlanArgs &a, hipStream_t st) {
+    const long long total =
+        (long long)kSets * (32 + (1LL << (2 * a.d_mid)) + (1LL << (2 * a.d_top))) + kTileCoefCount;
+    const dim3 g((unsigned)std::min<long long>(1024, (total + kBlock - 1) / kBlock)), b(kBlock);
+    if (prec == kPrecC64) hipLaunchKernelGGL(tile_tables_kernel<float>, g, b, 0, st, a);
+    else hipLaunchKernelGGL(tile_tables_kernel<double>, g, b, 0, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace quapi

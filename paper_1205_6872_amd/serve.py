@@ -72,6 +72,15 @@ def est_work_s(w) -> float:
     return max(2.0 * work_entries(w.N, w.L, w.n_steps) * cs / _NOMINAL_BYTES_PER_S, _MIN_STEP_S * w.n_steps)
 
 
+def _group_steps(w, ctx) -> int:
+    """Steps of a launch group past the growth phase: a chunk that ends inside
+    one takes an extra pass over the tensor (M = 2 from L = 8 on runs four
+    steps per pass, grouped from step L + 1), and one that ends inside a fused
+    group rounds differently from one call of all steps."""
+    f = ctx.fused_steps()
+    return 4 if f > 1 and w.L >= 8 else f
+
+
 @dataclass
 class RequestResult:
     index: int
@@ -144,7 +153,7 @@ class Server:
         rho_dev = torch.empty((rows, w.N, 2), dtype=torch.float64, device=self.device)
         ctx.propagate_async(0, [0], rho_dev.data_ptr())          # rho(t_0)
         return _Active(w=w, index=index, ctx=ctx, stream=stream, rho_dev=rho_dev, slot=slot,
-                       fp=Q.footprint(p), admit_s=now, fuse=ctx.fused_steps(), final_only=final_only,
+                       fp=Q.footprint(p), admit_s=now, fuse=_group_steps(w, ctx), final_only=final_only,
                        persistent=ctx.persistent() != 0)
 
     def _launch_batches(self, active) -> int:
