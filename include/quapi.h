@@ -102,8 +102,8 @@ typedef struct {
      * bare propagator of step k (interval (t_{k-1}, t_k]) is exp(-i H_t[k-1] dt)
      * for k <= n_H and uses H_t[n_H-1] after that.  NULL / n_H = 0: H for every
      * step.  A driven context computes every interval's propagator during
-     * quapi_create, rewrites the tables that carry K before every step, and
-     * runs one step per launch. */
+     * quapi_create and rewrites the tables that carry K before every launch,
+     * which runs one step, or up to four (M = 2, dk_max >= 8). */
     const double *H_t;
     int n_H;                  /* 0 <= n_H <= 1,000,000 */
 } quapi_params;
@@ -314,9 +314,9 @@ quapi_status quapi_restore(quapi_ctx *ctx, int step, const double *tensor, size_
 quapi_status quapi_tensor_size(const quapi_ctx *ctx, size_t *entries);
 
 /* Full-window steps of one group of this context (3, 2 or 1): the group size
- * of the determinism rule of quapi_propagate.  An undriven M = 2 context with
- * dk_max >= 8 that pins no width runs up to four steps in one launch, grouped
- * from step dk_max + 1; its results do not depend on the split into calls (at
+ * of the determinism rule of quapi_propagate.  An M = 2 context with dk_max >= 8
+ * that pins no width runs up to four steps in one launch, grouped from step
+ * dk_max + 1; its results do not depend on the split into calls (undriven at
  * QUAPI_C64_F64: into calls that end at whole groups).
  * Errors: QUAPI_ERR_INVALID for NULL arguments. */
 quapi_status quapi_fused_steps(const quapi_ctx *ctx, int *steps);

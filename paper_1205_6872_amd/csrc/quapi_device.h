@@ -108,6 +108,49 @@ __device__ __forceinline__ void two_sum_combine(double &s1, double &c1, double s
     c1 = c1 + c2 + e;
 }
 
+// Trace-exact FP32 representatives of the propagator's diagonal rows.  The
+// trace of rho is kept by the propagation because every influence factor of a
+// diagonal point o = (a, a) is 1 and, by unitarity of U, the K entries of the
+// diagonal rows sum to delta_cd over a for every column p = (c, d).  Rounding
+// each entry to FP32 on its own breaks that sum by a fixed amount that then
+// acts at every step (a linear trace drift).  Here, for each column and each
+// of the real and imaginary parts, the entries other than the largest one are
+// rounded to the FP32 spacing of the largest, and the largest is set to the
+// target minus their sum; all of them are then exact FP32 values whose sum is
+// exactly the target (up to the largest leaving its binade).  Change per entry:
+// at most half an FP32 spacing of the column's largest entry.
+__device__ inline void trace_exact_column(const double2 *U, int M, int c, int d, double2 *out) {
+    double2 v[kMaxM];
+    for (int q = 0; q < M; ++q) {
+        const double2 u2 = U[q * M + d];
+        v[q] = cmul(U[q * M + c], make_double2(u2.x, -u2.y));
+    }
+    for (int part = 0; part < 2; ++part) {
+        const double target = (part == 0 && c == d) ? 1.0 : 0.0;
+        int big = 0;
+        for (int q = 1; q < M; ++q)
+            if (fabs(part ? v[q].y : v[q].x) > fabs(part ? v[big].y : v[big].x)) big = q;
+        const double vb = fabs(part ? v[big].y : v[big].x);
+        double w[kMaxM];
+        if (vb == 0.0) {
+            for (int q = 0; q < M; ++q) w[q] = 0.0;
+        } else {
+            const double grid = ldexp(1.0, ilogb(vb) - 23);   // FP32 spacing in the binade of vb
+            double rest = 0.0;
+            for (int q = 0; q < M; ++q) {
+                if (q == big) continue;
+                w[q] = rint((part ? v[q].y : v[q].x) / grid) * grid;
+                rest += w[q];
+            }
+            w[big] = target - rest;
+        }
+        for (int q = 0; q < M; ++q) {
+            if (part) out[q].y = w[q];
+            else out[q].x = w[q];
+        }
+    }
+}
+
 // ------------------------------------------------------------------- LDS
 // Carve `bytes` (16-byte aligned) out of a dynamic LDS block at offset `off`.
 __host__ __device__ inline unsigned lds_take(unsigned &off, unsigned bytes) {

@@ -131,7 +131,7 @@ int fusion_width(int N, int L, int prec) {
 }
 
 // The four-step tile kernel (quapi_tile.hip) runs every full-window step past
-// n = L of a dense, undriven M = 2 context from L = kTileMinL that pins no
+// n = L of a dense M = 2 context from L = kTileMinL that pins no
 // launch width.  Below, at N^L <= 2^14, the persistent path does better (L = 7:
 // 11 us per step, one launch); a tile needs the digits d0 .. d3, w0, w1 and at
 // least one more.
@@ -1476,7 +1476,7 @@ quapi_status enqueue_step3(quapi_ctx *c, int n, const bool *selk) {
 }
 
 // ------------------------------------------------------- four steps per pass
-bool tile_on(const quapi_ctx *c) { return !c->filtered && c->n_H == 0 && !c->fuse_pinned && tile_ok(c->N, c->L); }
+bool tile_on(const quapi_ctx *c) { return !c->filtered && !c->fuse_pinned && tile_ok(c->N, c->L); }
 
 // The rho of the last pass that is still to be summed, as a launch of its own.
 quapi_status tile_finish(quapi_ctx *c) {
@@ -1517,6 +1517,22 @@ quapi_status enqueue_tile(quapi_ctx *c, int n, int k, double2 *const *out) {
         if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "tile tables launch: %s", hipGetErrorString(e));
         c->ttab_ready = true;
     }
+    if (c->n_H > 0) {
+        TileDriveArgs da{};
+        da.bank = c->bank;
+        da.U_t = c->Ut_d;
+        da.L = L;
+        da.n = n - s0;
+        da.n_H = c->n_H;
+        da.d_last = a.d_top > 0 ? a.d_top : a.d_mid;
+        da.k_trace_exact = c->prec == kPrecC64;
+        da.t_u = (double2 *)a.t_u;
+        da.t_last = (double2 *)(a.d_top > 0 ? a.t_top : a.t_mid);
+        da.coef = c->tcoef;
+        const hipError_t e = launch_tile_drive(c->prec, da, c->stream);
+        if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "driven tables launch: %s", hipGetErrorString(e));
+    }
+    a.round_each = c->n_H > 0;
     const bool mirror = c->mirror != 0;
     if (!mirror)
         if (quapi_status st = ensure_full(c); st != QUAPI_OK) return st;

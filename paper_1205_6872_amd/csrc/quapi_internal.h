@@ -305,8 +305,8 @@ size_t step2_lds_bytes(int prec, bool with_rho, int R, int Q);
 constexpr int kTileSteps = 4;
 constexpr int kTileSets = 4 * kTileSteps;            // factor tables: (stage, class, o in {1, 2})
 constexpr int kTileMinL = 8;
-constexpr int kTileCoefK = 48;                       // coefficients in the compute precision, then
-constexpr int kTileCoefCount = kTileCoefK + 16;      // 16 of K in FP64
+constexpr int kTileCoefK = 80;                       // coefficients in the compute precision, then
+constexpr int kTileCoefCount = kTileCoefK + 64;      // 16 of K per stage in FP64
 constexpr int kTileBlocks = 1024;                    // blocks of a pass (rho rows of a step)
 struct TilePlanArgs {
     const double2 *bank, *eta;
@@ -332,8 +332,17 @@ struct TileArgs {
     // as their stages run) and m, as read and as written
     long long in_d[4], in_m, out_d[4], out_m;
     int d_mid, d_top, n_tiles, n_work, s0, s1;
+    int round_each;                                  // round to the storage type after every step
     TileRho prev;                                    // summed by extra blocks of this launch
 };
+// A driven system: what carries the propagators of steps n .. n+3.
+struct TileDriveArgs {
+    const double2 *bank, *U_t;                       // U_t[k]: exp(-i H_t[k] dt), k < n_H
+    int L, n, n_H, d_last, k_trace_exact;
+    double2 *t_u, *t_last;                           // t_last: sets 0 .. 3 of t_top (t_mid where d_top = 0)
+    void *coef;
+};
+hipError_t launch_tile_drive(int prec, const TileDriveArgs &a, hipStream_t st);
 hipError_t launch_tile_tables(int prec, const TilePlanArgs &a, hipStream_t st);
 hipError_t launch_tile(int prec, bool rho, bool mirror, const TileArgs &a, hipStream_t st);
 hipError_t launch_tile_rho(const TileRho &r, hipStream_t st);

@@ -27,6 +27,9 @@
 //           29 -> 4.5 us; L = 8 24 -> 2.8 us: bound by the launch and by the
 //           latency of one tile's chain; one launch per four steps, the rho of a
 //           pass summed by extra blocks of the next.
+//   A driven system (complex128, L = 11, rho at the last step, 64 steps): 2281 ->
+//           383 us, a launch of tables and a pass per four steps where each step
+//           took three launches (tables, factor products, step).
 //   16 consecutive entries per store (whole cache lines): with stores of 64 B
 //   from waves that run apart a pass takes 4.8 ms at L = 15; five points per
 //   tile would leave 64 B stores and takes 4.8 ms for the memory alone.
@@ -55,10 +58,13 @@ constexpr int kSets = kTileSets;         // (stage, class, o in {1, 2}) factor t
 // Coefficients in the compute precision, read by scalar loads: cos, sin,
 // e^{-g}, e^{g} of the oldest point (lag L; interior, final class) and of the
 // group digit at lag L-1 (stages 0 and 2, "pair 0"); for the group digit e at
-// lag 1, with K (stages 1 and 3, "pair 1"), per e the complex factors of
-// o = 1, 2 (interior), then the final class; then per e K[0][e], K[3][e], in FP64 in every tier (at the
-// kTileCoefK-th double).
+// lag 1, with K (stages 1 and 3, "pair 1"), per stage and e the complex factors
+// of o = 1, 2 (interior), then the final class; then per stage and e K[0][e],
+// K[3][e], in FP64 in every tier (from the kTileCoefK-th double).  The stages
+// differ in K for a driven system only.
 constexpr int kTcOld = 0, kTcOldf = 4, kTcE = 8, kTcEf = 12, kTcLag1 = 16;
+__device__ __forceinline__ constexpr int tc_lag1(int stage) { return kTcLag1 + 32 * (stage >> 1); }
+__device__ __forceinline__ constexpr int tc_k(int stage) { return kTileCoefK + 16 * stage; }
 
 __device__ __forceinline__ constexpr int mirror_d(int d) { return d == 1 ? 2 : d == 2 ? 1 : d; }
 
@@ -121,11 +127,11 @@ __global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs 
                 const double D = a.s[0] - a.s[1], th = D * D * eta.y, g = D * D * eta.x;
                 v = k % 4 == 0 ? cos(th) : k % 4 == 1 ? sin(th) : exp(k % 4 == 2 ? -g : g);
             } else if (k < kTileCoefK) {
-                const int e = (k - kTcLag1) / 8, cls = k / 4 % 2, o = 1 + k / 2 % 2;
+                const int e = (k - kTcLag1) / 8 % 4, cls = k / 4 % 2, o = 1 + k / 2 % 2;
                 const double2 f = tab(tile_tab(B, 1, cls), o, e);
                 v = k % 2 ? f.y : f.x;
             } else {
-                const double2 f = tab(B.k_lag1(), k / 2 % 2 * 3, (k - kTileCoefK) / 4);
+                const double2 f = tab(B.k_lag1(), k / 2 % 2 * 3, (k - kTileCoefK) / 4 % 4);
                 v = k % 2 ? f.y : f.x;
                 if (sizeof(T) == 4) v = (float)v;           // exact: the diagonal rows of K are FP32 values
                 ((double *)a.coef)[k] = v;
@@ -170,6 +176,70 @@ __global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs 
             p = cmul(p, tab(tile_tab(B, lag, cls), o, v & 3));
         }
         *out = p;
+    }
+}
+
+// The parts of the tables that carry the propagator, for the group of four
+// steps that starts at step n of a driven system: K of step n+s from its U, in
+// the coefficients (stages 1 and 3 at lag 1, the diagonal rows of every stage),
+// in t_u (stage 2: lag 1 is the thread digit o1) and, for stage 0, in the table
+// t_last of the highest outer digits (lag 1 is the highest).
+template <typename T>
+__global__ void __launch_bounds__(kBlock) tile_drive_kernel(const TileDriveArgs a) {
+    const BankLayout B{a.L};
+    const int n_last = 1 << (2 * a.d_last);
+    const int total = 2 * 32 + 4 * 16 + 4 * 16 + 4 * n_last;
+    // K[o][p] of stage s times the influence factor at lag 1 of class cls (-1:
+    // K alone), exactly conjugate under the mirror as in tile_tables_kernel
+    auto kf = [&](int s, int cls, int o, int p) {
+        const int k = o * 4 + p, km = mirror_d(o) * 4 + mirror_d(p);
+        const int oo = km < k ? mirror_d(o) : o, pp = km < k ? mirror_d(p) : p;
+        const double2 *U = a.U_t + 4 * (size_t)min(a.n + s - 1, a.n_H - 1);
+        double2 v;
+        if (a.k_trace_exact && oo % 3 == 0) {
+            double2 col[kMaxM];
+            trace_exact_column(U, 2, pp / 2, pp % 2, col);
+            v = col[oo / 3];
+        } else {
+            const double2 u2 = U[oo % 2 * 2 + pp % 2];
+            v = cmul(U[oo / 2 * 2 + pp / 2], make_double2(u2.x, -u2.y));
+        }
+        if (cls >= 0) v = cmul(v, a.bank[(size_t)(cls ? B.fin(1) : B.lag(1)) * 16 + oo * 4 + pp]);
+        if (km < k) v.y = -v.y;
+        if (km == k) v.y = 0.0;
+        return v;
+    };
+    auto tab = [&](int t, int o, int p) {
+        const int k = o * 4 + p, km = mirror_d(o) * 4 + mirror_d(p);
+        double2 v = a.bank[(size_t)t * 16 + (km < k ? km : k)];
+        if (km < k) v.y = -v.y;
+        if (km == k) v.y = 0.0;
+        return v;
+    };
+    for (int idx = blockIdx.x * kBlock + threadIdx.x; idx < total; idx += gridDim.x * kBlock) {
+        if (idx < 64) {
+            const int st = 1 + idx / 32 * 2, k = idx % 32, e = k / 8, cls = k / 4 % 2, o = 1 + k / 2 % 2;
+            const double2 f = kf(st, cls, o, e);
+            ((T *)a.coef)[tc_lag1(st) + k] = (T)(k % 2 ? f.y : f.x);
+        } else if (idx < 128) {
+            const int k = idx - 64, st = k / 16;
+            const double2 f = kf(st, -1, k / 2 % 2 * 3, k / 4 % 4);
+            double v = k % 2 ? f.y : f.x;
+            if (sizeof(T) == 4) v = (float)v;
+            ((double *)a.coef)[tc_k(0) + k] = v;
+        } else if (idx < 192) {
+            const int k = idx - 128, q = 8 + k / 16, v = k % 16, cls = q / 2 % 2, o = 1 + q % 2;
+            a.t_u[q * 16 + v] = cmul(tab(cls ? B.fin(2) : B.lag(2), o, v & 3), kf(2, cls, o, v >> 2));
+        } else {
+            const int k = idx - 192, q = k / n_last, cls = q / 2, o = 1 + q % 2;
+            int v = k % n_last;
+            double2 p = make_double2(1.0, 0.0);
+            for (int j = 0; j < a.d_last - 1; ++j, v >>= 2) {
+                const int lag = a.d_last - j;
+                p = cmul(p, tab(cls ? B.fin(lag) : B.lag(lag), o, v & 3));
+            }
+            a.t_last[k] = cmul(p, kf(0, cls, o, v));
+        }
     }
 }
 
@@ -311,18 +381,19 @@ __device__ __forceinline__ C row12(const T *co, int k, C p, C q, C x1, C x2) {
     return r;
 }
 
-// One step on the 16 values of a lane: digit PAIR of the register index
+// One step (stage) on the 16 values of a lane: digit PAIR of the register index
 // (stride 4^PAIR) is contracted, the groups are the other digit e.  c1, c2: the
 // thread's factors of the new points 1 and 2 (interior); prev: the previous
 // point when it is not e (PAIR 0), wave-uniform.  With RHO: tf1, tf2 the
 // final-point sums of the lane without the thread's factor, rd0 and rd3 the
 // terms of the diagonal points (REAL: their real parts only).
-template <typename T, bool RHO, bool REAL, int PAIR, typename CI>
+template <typename T, bool RHO, bool REAL, int STAGE, typename CI>
 __device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::type (&w)[16],
                                            const T *coef, typename Cx<T>::type c1,
                                            typename Cx<T>::type c2, int prev, typename Cx<T>::type &tf1,
                                            typename Cx<T>::type &tf2, double2 &rd0, double2 &rd3) {
     using C = typename Cx<T>::type;
+    constexpr int PAIR = STAGE % 2;
     constexpr int SI = PAIR == 0 ? 1 : 4, SE = PAIR == 0 ? 4 : 1;
     const T *co = fresh_t(coef);
     double2 all = make_double2(0.0, 0.0);
@@ -354,7 +425,7 @@ __device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::t
         } else {
             sd.init(cadd(p, cadd(x1, x2)));
         }
-        const double *kd = (const double *)ce + kTileCoefK + 4 * (PAIR == 0 ? prev : e);
+        const double *kd = (const double *)ce + tc_k(STAGE) + 4 * (PAIR == 0 ? prev : e);
         const double2 d0 = coef_ld(kd, 0), d3 = coef_ld(kd, 1), ds = sd.s;
         if (PAIR == 1 && (e == 0 || e == 3)) {
             w[SE * e] = from_d2<C>(make_double2(d0.x * ds.x, d0.x * ds.y));
@@ -386,7 +457,7 @@ __device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::t
                 f.x = coef_s(ce, e == 1 || e == 2 ? k + ((e == 1) == (o == 1) ? 2 : 3) : k);
                 f.y = (e == 0) == (o == 1) ? -coef_s(ce, k + 1) : coef_s(ce, k + 1);
             } else {
-                const int k = kTcLag1 + 8 * e + 2 * (o - 1) + (fin ? 4 : 0);
+                const int k = tc_lag1(STAGE) + 8 * e + 2 * (o - 1) + (fin ? 4 : 0);
                 f.x = coef_s(ce, k);
                 f.y = coef_s(ce, k + 1);
             }
@@ -418,7 +489,7 @@ __device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::t
         }
     }
     if (RHO && PAIR == 0) {
-        const double *kd = (const double *)co + kTileCoefK + 4 * prev;
+        const double *kd = (const double *)co + tc_k(STAGE) + 4 * prev;
         rd0 = cmul(coef_ld(kd, 0), all);
         rd3 = cmul(coef_ld(kd, 1), all);
     }
@@ -587,10 +658,11 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         };
         C tf1, tf2;
         double2 rd0, rd3;
-        // storage narrower than the arithmetic: the rounding of the stored
-        // pair groups, (n, n+1) and (n+2, n+3)
-        auto round_pair = [&]() {
-            if (sizeof(S) < sizeof(T)) {
+        // storage narrower than the arithmetic: the values are rounded to it where
+        // a call may end without changing the result, after the pairs (n, n+1)
+        // and (n+2, n+3), or for a driven system after every step
+        auto round_to_storage = [&](bool on) {
+            if (sizeof(S) < sizeof(T) && on) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) w[r] = conv<C>(conv<CS>(w[r]));
             }
@@ -601,6 +673,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             tile_stage<T, RHO, MIRROR, 0>(x, w, coef, factor(0, wl, ua), factor(1, wl, ua), prev, tf1, tf2, rd0,
                                           rd3);
             if (RHO) add_rho(0, wl, ua, tf1, tf2, rd0, rd3);
+            round_to_storage(a.round_each);
         } else {
 #pragma unroll
             for (int r = 0; r < 16; ++r) w[r] = conv<C>(x[r]);
@@ -612,7 +685,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         if (s0 <= 1 && s1 > 1) {
             tile_stage<T, RHO, MIRROR, 1>(w, w, coef, factor(4, wl, ua), factor(5, wl, ua), 0, tf1, tf2, rd0, rd3);
             if (RHO) add_rho(RHO ? 1 : 0, wl, ua, tf1, tf2, rd0, rd3);
-            round_pair();
+            round_to_storage(true);
         }
         // the 16 entries y0 + (r % 4) da + (r / 4) db of a part of a group (at the
         // mirrored address, conjugated, when above their mirror; a tile that is
@@ -641,11 +714,12 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             if (lane >= 32) s_w[wave][lane] = tile_f;
         });
         if (s0 <= 2 && s1 > 2) {
-            tile_stage<T, RHO, MIRROR, 0>(w, w, coef, factor(8, wb, ub), factor(9, wb, ub), wave, tf1, tf2, rd0, rd3);
+            tile_stage<T, RHO, MIRROR, 2>(w, w, coef, factor(8, wb, ub), factor(9, wb, ub), wave, tf1, tf2, rd0, rd3);
             if (RHO) add_rho(RHO ? 2 : 0, wb, ub, tf1, tf2, rd0, rd3);
+            round_to_storage(a.round_each);
         }
         if (s1 > 3) {
-            tile_stage<T, RHO, MIRROR, 1>(w, w, coef, factor(12, wb, ub), factor(13, wb, ub), 0, tf1, tf2, rd0, rd3);
+            tile_stage<T, RHO, MIRROR, 3>(w, w, coef, factor(12, wb, ub), factor(13, wb, ub), 0, tf1, tf2, rd0, rd3);
             if (RHO) add_rho(RHO ? 3 : 0, wb, ub, tf1, tf2, rd0, rd3);
         }
         const long long m = (long long)hi * 16 + wb;        // layout B's m
@@ -751,6 +825,14 @@ hipError_t launch_tile_tables(int prec, const TilePlanArgs &a, hipStream_t st) {
     const dim3 g((unsigned)std::min<long long>(1024, (total + kBlock - 1) / kBlock)), b(kBlock);
     if (prec == kPrecC64) hipLaunchKernelGGL(tile_tables_kernel<float>, g, b, 0, st, a);
     else hipLaunchKernelGGL(tile_tables_kernel<double>, g, b, 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_drive(int prec, const TileDriveArgs &a, hipStream_t st) {
+    const int total = 2 * 32 + 8 * 16 + (4 << (2 * a.d_last));
+    const dim3 g((total + kBlock - 1) / kBlock), b(kBlock);
+    if (prec == kPrecC64) hipLaunchKernelGGL(tile_drive_kernel<float>, g, b, 0, st, a);
+    else hipLaunchKernelGGL(tile_drive_kernel<double>, g, b, 0, st, a);
     return hipGetLastError();
 }
 

@@ -99,3 +99,29 @@ def test_tile_passes_against_oracle_and_splits(L, hermitian, dtype):
         with Q.create(Q.params_from(w, dtype=dtype)) as c:
             c.set_fused_steps(1)
             assert np.abs(c.propagate(n) - one).max() <= {"c128": 1e-13, "c64": 1e-5, "c64f64": 1e-6}[dtype]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["c128", "c64", "c64f64"])
+@pytest.mark.parametrize("L", [8, 11])            # the newest outer digit in the middle table; in the top one
+def test_driven_tile_passes_against_oracle_and_splits(L, dtype):
+    rng = np.random.default_rng(L + 20)
+    n = L + 11
+    H_t = np.stack([0.7 * W.random_hermitian(rng, 2) for _ in range(L + 6)])     # held past step L + 6
+    rho0 = np.array([[0.7, 0.2 - 0.1j], [0.2 + 0.1j, 0.3]])
+    w = W.spin_boson_l7().with_(L=L, H=H_t[0].copy(), H_t=H_t, xi=0.3, rho0=rho0)
+    print(f"case driven L={L} {dtype}", flush=True)
+    one, tens = _run(w, dtype, [n])
+    o = oracle_run(w, n)[1:]
+    assert np.abs(one - o).max() <= TOL[dtype] * (np.abs(o).max() if dtype == "c128" else 1.0)
+    # one step per group: any split gives the same bits at every tier
+    for parts in ([L, 1, 3, 1, 1, 5], [L + 3, 8], [1] * n):
+        rho, t = _run(w, dtype, parts)
+        assert np.array_equal(rho, one) and np.array_equal(t, tens), parts
+    last, t = _run(w, dtype, [n], sel=[n])
+    assert np.array_equal(last, one[[n - 1]]) and np.array_equal(t, tens)
+    if dtype != "c64":      # one Hamiltonian at every step is the static system (FP32 rounds its pairs otherwise)
+        ws = w.with_(H_t=None)
+        wd = w.with_(H_t=np.stack([w.H] * 3))
+        d = np.abs(_run(ws, dtype, [n])[0] - _run(wd, dtype, [n])[0]).max()
+        assert d == 0.0 if dtype == "c128" else d <= 1e-6
