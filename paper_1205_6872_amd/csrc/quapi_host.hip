@@ -315,7 +315,7 @@ std::string validate(const quapi_params *p, int max_log2 = kDenseMaxLog2) {
 // ------------------------------------------------------------------ layout
 struct Layout {
     size_t a_bytes;                  // one tensor buffer
-    size_t off_a0, off_a1, off_bank, off_bankf, off_g, off_eta, off_U, off_s, off_H, off_Ht, off_Ut, off_rho0;
+    size_t off_a0, off_a1, off_bank, off_bankf, off_g, off_gpart, off_eta, off_U, off_s, off_H, off_Ht, off_Ut, off_rho0;
     size_t off_pa, off_ph, off_pseg, off_tw, off_tJ, off_glx, off_glw, off_partials, off_stage;
     size_t off_plan, off_plan2, off_coef, off_plan3, off_coef3, off_blk3, off_low3, off_blk2, off_low2, off_blk1,
         off_low1, off_pairs, off_sink, off_ttab, off_tcoef, off_trows;
@@ -358,6 +358,10 @@ int mirror_parts(int passes, int n_diag) {
 bool single_mirror_ok(int N, int L, const DigitSplit &main_split) {
     return L >= 2 && (N == 4 || N == 9 || (N == 16 && main_split.R == 16));
 }
+
+// Blocks that share the quadrature nodes of one G(t_j): about four nodes per
+// thread, at most 64.
+int quad_parts(int n_panels) { return std::max(1, std::min(64, n_panels * kGL / (4 * kBlock))); }
 
 // filter_cap > 0: a filtered context holding up to filter_cap kept entries
 // (no dense tensors, no dense-step plans, mirror or fused-step buffers).
@@ -450,6 +454,7 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_bank = take((size_t)l.n_tables * N * N * 16);
     l.off_bankf = take(p.dtype == QUAPI_C64 ? (size_t)l.n_tables * N * N * 8 : 0);
     l.off_g = take((size_t)(2 * L + 3) * 16);
+    l.off_gpart = take((size_t)(2 * L + 3) * quad_parts(n_panels) * 2 * 16);
     l.off_eta = take((size_t)(4 * L + 2) * 16);
     l.off_U = take((size_t)M * M * 16);
     l.off_s = take((size_t)M * 8);
@@ -2267,13 +2272,16 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
     qa.n_tab = p->bath.kind == QUAPI_BATH_TABLE ? p->bath.n_tab : 0;
     qa.glx = (const double *)(w + lay.off_glx);
     qa.glw = (const double *)(w + lay.off_glw);
-    e = launch_g_quad(qa, 2 * L + 3, c->g, c->stream);
+    const int parts = quad_parts(lay.n_panels);
+    e = launch_g_quad(qa, 2 * L + 3, parts, (double2 *)(w + lay.off_gpart), c->stream);
     TablesArgs ta{};
     ta.M = M;
     ta.L = L;
     ta.dt = p->dt;
     ta.s = (const double *)(w + lay.off_s);
     ta.g = c->g;
+    ta.g_part = (const double2 *)(w + lay.off_gpart);
+    ta.g_parts = parts;
     ta.U = c->U;
     ta.eta = c->eta;
     ta.bank = c->bank;

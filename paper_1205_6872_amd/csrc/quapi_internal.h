@@ -228,7 +228,9 @@ struct TablesArgs {
     int M, L;
     double dt;
     const double *s;
-    const double2 *g;           // G(j dt/2), j = 0..2L+2
+    double2 *g;                 // G(j dt/2), j = 0..2L+2: out on setup (from its parts), in with k_only
+    const double2 *g_part;      // compensated pairs (re, im) of the g_parts parts of each G
+    int g_parts;
     double2 *U;                 // out: M x M
     double2 *eta;               // out: 4L+2 classes
     double2 *bank;              // out: BankLayout{L}.count() tables
@@ -239,7 +241,7 @@ struct TablesArgs {
 };
 
 // Kernel launchers (quapi_kernels.hip).  They return the launch status.
-hipError_t launch_g_quad(const QuadArgs &a, int n_t, double2 *g, hipStream_t st);
+hipError_t launch_g_quad(const QuadArgs &a, int n_t, int parts, double2 *part_out, hipStream_t st);
 hipError_t launch_tables(const TablesArgs &a, hipStream_t st);
 // U_k = exp(-i H_t[k] dt) for k < n_H (M x M each), a thread each.
 hipError_t launch_u_stack(const double2 *H_t, int n_H, int M, double dt, double2 *U_t, hipStream_t st);

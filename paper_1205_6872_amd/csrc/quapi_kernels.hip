@@ -47,10 +47,6 @@ __device__ void block_reduce_pairs(double &sr, double &cr, double &si, double &c
     ci = s_v[3][0];
     __syncthreads();
 }
-__device__ double2 block_sum_compensated(double sr, double cr, double si, double ci) {
-    block_reduce_pairs<kBlock>(sr, cr, si, ci);
-    return make_double2(sr + cr, si + ci);
-}
 
 // --------------------------------------------------- lineshape quadrature
 // sin(u) - u without cancellation: Taylor series for |u| < 1 (terms through
@@ -72,15 +68,20 @@ __device__ double sin_minus_id(double u) {
 }
 
 // G(t_j) = (1/pi) Int_0^inf J(w)/w^2 [coth(w/2kT)(1 - cos wt) + i (sin wt - wt)] dw,
-// t_j = j dt/2, by composite Gauss-Legendre over host-planned panels.  One
-// block per t_j; compensated sums, fixed reduction order.
-__global__ void __launch_bounds__(kBlock) g_quad_kernel(const QuadArgs a, double2 *g) {
-    const int j = blockIdx.x;
+// t_j = j dt/2, by composite Gauss-Legendre over host-planned panels.  Block
+// (j, part) sums the part's share of the nodes at t_j into the compensated pairs
+// part_out[j * parts + part] (re, im); tables_kernel adds the parts in order.
+// Bound by the FP64 transcendentals of the nodes: with one block per t_j the
+// 4000-segment table of the paper's quantum dot at L = 5 took 437 us on 13
+// compute units.
+__global__ void __launch_bounds__(kBlock) g_quad_kernel(const QuadArgs a, double2 *part_out) {
+    const int j = blockIdx.x, part = blockIdx.y, parts = gridDim.y;
     const double t = j * a.half_dt;
     double sr = 0.0, cr = 0.0, si = 0.0, ci = 0.0;
     if (j > 0) {
         const int total = a.n_panels * kGL;
-        for (int idx = threadIdx.x; idx < total; idx += kBlock) {
+        const int per = (total + parts - 1) / parts, end = min(total, (part + 1) * per);
+        for (int idx = part * per + threadIdx.x; idx < end; idx += kBlock) {
             const int p = idx / kGL, q = idx % kGL;
             const double half_h = 0.5 * a.ph[p];
             const double w = a.pa[p] + half_h * (1.0 + a.glx[q]);
@@ -107,8 +108,11 @@ __global__ void __launch_bounds__(kBlock) g_quad_kernel(const QuadArgs a, double
             neumaier(si, ci, f * im);
         }
     }
-    const double2 r = block_sum_compensated(sr, cr, si, ci);
-    if (threadIdx.x == 0) g[j] = r;
+    block_reduce_pairs<kBlock>(sr, cr, si, ci);
+    if (threadIdx.x == 0) {
+        part_out[2 * (j * parts + part)] = make_double2(sr, cr);
+        part_out[2 * (j * parts + part) + 1] = make_double2(si, ci);
+    }
 }
 
 // ------------------------------------------------------------ setup tables
@@ -126,14 +130,20 @@ __device__ double2 influence(const double *s, int M, int o, int p, double2 eta) 
 }
 
 // U = exp(-i H dt) by scaling and squaring of the Taylor series (degree 20 on
-// a matrix of 1-norm <= 1/4, then repeated squaring).  One thread; M <= 4.
-__device__ void expm_minus_i_h_dt(const double2 *H, int M, double dt, double2 *U) {
-    double2 A[kMaxM * kMaxM], T[kMaxM * kMaxM], term[kMaxM * kMaxM], tmp[kMaxM * kMaxM];
-    const int MM = M * M;
+// a matrix of 1-norm <= 1/4, then repeated squaring).  One thread; M a
+// template argument, so that the matrices stay in registers (as arrays of a
+// run-time size they were scratch memory: M = 2 29-37 us, M = 4 217 us).
+template <int M>
+__device__ void expm_minus_i_h_dt(const double2 *H, double dt, double2 *U) {
+    constexpr int MM = M * M;
+    double2 A[MM], T[MM], term[MM], tmp[MM];
     double norm = 0.0;
+#pragma unroll
     for (int i = 0; i < MM; ++i) A[i] = make_double2(H[i].y * dt, -H[i].x * dt);  // -i H dt
+#pragma unroll
     for (int c = 0; c < M; ++c) {
         double col = 0.0;
+#pragma unroll
         for (int r = 0; r < M; ++r) col += hypot(A[r * M + c].x, A[r * M + c].y);
         norm = fmax(norm, col);
     }
@@ -143,38 +153,53 @@ __device__ void expm_minus_i_h_dt(const double2 *H, int M, double dt, double2 *U
         ++sq;
     }
     const double scale = ldexp(1.0, -sq);
+#pragma unroll
     for (int i = 0; i < MM; ++i) {
         A[i].x *= scale;
         A[i].y *= scale;
         T[i] = term[i] = make_double2((i / M) == (i % M) ? 1.0 : 0.0, 0.0);
     }
+#pragma unroll 1
     for (int k = 1; k <= 20; ++k) {
         const double inv = 1.0 / k;
+#pragma unroll
         for (int r = 0; r < M; ++r)
+#pragma unroll
             for (int c = 0; c < M; ++c) {
                 double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
                 for (int x = 0; x < M; ++x) cmac(acc, term[r * M + x], A[x * M + c]);
                 tmp[r * M + c] = make_double2(acc.x * inv, acc.y * inv);
             }
+#pragma unroll
         for (int i = 0; i < MM; ++i) {
             term[i] = tmp[i];
             T[i].x += term[i].x;
             T[i].y += term[i].y;
         }
     }
+#pragma unroll 1
     for (int k = 0; k < sq; ++k) {
+#pragma unroll
         for (int r = 0; r < M; ++r)
+#pragma unroll
             for (int c = 0; c < M; ++c) {
                 double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
                 for (int x = 0; x < M; ++x) cmac(acc, T[r * M + x], T[x * M + c]);
                 tmp[r * M + c] = acc;
             }
+#pragma unroll
         for (int i = 0; i < MM; ++i) T[i] = tmp[i];
     }
+#pragma unroll
     for (int i = 0; i < MM; ++i) U[i] = T[i];
 }
 
+// Every block forms the eta classes (from the parts of G on setup) and its
+// share of the bank; block 0 writes G, the classes and U.
 __global__ void __launch_bounds__(kBlock) tables_kernel(const TablesArgs a) {
+    __shared__ double2 sG[2 * kMaxL + 3];
     __shared__ double2 sU[kMaxM * kMaxM];
     __shared__ double2 sEta[4 * kMaxL + 2];
     __shared__ double sS[kMaxM];
@@ -186,6 +211,30 @@ __global__ void __launch_bounds__(kBlock) tables_kernel(const TablesArgs a) {
     // eta classes from g_j = G(j dt/2) (second differences of G over the
     // intervals [0, dt/2], [k dt - dt/2, k dt + dt/2] and [n dt - dt/2, n dt])
     const double2 *g = a.g;
+    if (!a.k_only) {
+        // eight lanes per G(t_j), each every eighth part, then combined in order
+        for (int j = t >> 3; j < 2 * L + 3; j += kBlock / 8) {
+            const double2 *q = a.g_part + 2 * (size_t)j * a.g_parts;
+            double2 re = make_double2(0.0, 0.0), im = re;
+            for (int k = t & 7; k < a.g_parts; k += 8) {
+                two_sum_combine(re.x, re.y, q[2 * k].x, q[2 * k].y);
+                two_sum_combine(im.x, im.y, q[2 * k + 1].x, q[2 * k + 1].y);
+            }
+            for (int off = 4; off > 0; off >>= 1) {
+                const double2 r2 = make_double2(__shfl_down(re.x, off, 8), __shfl_down(re.y, off, 8));
+                const double2 i2 = make_double2(__shfl_down(im.x, off, 8), __shfl_down(im.y, off, 8));
+                two_sum_combine(re.x, re.y, r2.x, r2.y);
+                two_sum_combine(im.x, im.y, i2.x, i2.y);
+            }
+            if ((t & 7) == 0) {
+                sG[j] = make_double2(re.x + re.y, im.x + im.y);
+                if (blockIdx.x == 0) a.g[j] = sG[j];
+            }
+        }
+        __syncthreads();
+        g = sG;
+    }
+    const bool first = blockIdx.x == 0;
     for (int c = t; c < 4 * L + 2; c += kBlock) {
         double2 v;
         if (c == 0) {
@@ -206,10 +255,10 @@ __global__ void __launch_bounds__(kBlock) tables_kernel(const TablesArgs a) {
             }
         }
         sEta[c] = v;
-        if (!a.k_only) a.eta[c] = v;
+        if (first && !a.k_only) a.eta[c] = v;
     }
     __syncthreads();
-    if (t < M * M && !a.k_only) a.U[t] = sU[t];
+    if (first && t < M * M && !a.k_only) a.U[t] = sU[t];
     if (a.k_trace_exact && t < N) {
         double2 col[kMaxM];
         trace_exact_column(sU, M, t / M, t % M, col);
@@ -229,7 +278,7 @@ __global__ void __launch_bounds__(kBlock) tables_kernel(const TablesArgs a) {
         return tb == B.K() || tb == B.k_lag1() || tb == B.k_init1() || tb == B.k_fin1() ||
                tb == B.k_fin_init1() || (L == 1 && tb >= B.old_main() && tb <= B.oldf_first());
     };
-    for (int idx = t; idx < n_tab * NN; idx += kBlock) {
+    for (int idx = blockIdx.x * kBlock + t; idx < n_tab * NN; idx += gridDim.x * kBlock) {
         const int tb = idx / NN, o = (idx / N) % N, p = idx % N;
         if (a.k_only && !carries_k(tb)) continue;
         const int oa = o / M, ob = o % M, pc = p / M, pd = p % M;
@@ -1144,26 +1193,37 @@ size_t step_lds_bytes(int N, int prec, bool with_rho, bool grow, int R, int Q) {
     return step_lds_layout(N, prec == kPrecC64 ? 8 : 16, with_rho, grow ? 1 : N, R, Q, N <= 4).total;
 }
 
-hipError_t launch_g_quad(const QuadArgs &a, int n_t, double2 *g, hipStream_t st) {
-    hipLaunchKernelGGL(g_quad_kernel, dim3(n_t), dim3(kBlock), 0, st, a, g);
+hipError_t launch_g_quad(const QuadArgs &a, int n_t, int parts, double2 *part_out, hipStream_t st) {
+    hipLaunchKernelGGL(g_quad_kernel, dim3(n_t, parts), dim3(kBlock), 0, st, a, part_out);
     return hipGetLastError();
 }
 
 // U = exp(-i H dt) for each of n_H Hamiltonians (one for a static system,
 // one per time interval for a driven one), a thread each.
-__global__ void __launch_bounds__(64) u_stack_kernel(const double2 *H_t, int n_H, int M, double dt, double2 *U_t) {
+template <int M>
+__global__ void __launch_bounds__(64) u_stack_kernel(const double2 *H_t, int n_H, double dt, double2 *U_t) {
     const int k = blockIdx.x * 64 + threadIdx.x;
-    if (k < n_H) expm_minus_i_h_dt(H_t + (size_t)k * M * M, M, dt, U_t + (size_t)k * M * M);
+    if (k < n_H) expm_minus_i_h_dt<M>(H_t + (size_t)k * M * M, dt, U_t + (size_t)k * M * M);
 }
 
 hipError_t launch_u_stack(const double2 *H_t, int n_H, int M, double dt, double2 *U_t, hipStream_t st) {
     if (n_H <= 0) return hipSuccess;
-    hipLaunchKernelGGL(u_stack_kernel, dim3((n_H + 63) / 64), dim3(64), 0, st, H_t, n_H, M, dt, U_t);
+    const dim3 g((n_H + 63) / 64), b(64);
+    switch (M) {
+    case 1: hipLaunchKernelGGL(u_stack_kernel<1>, g, b, 0, st, H_t, n_H, dt, U_t); break;
+    case 2: hipLaunchKernelGGL(u_stack_kernel<2>, g, b, 0, st, H_t, n_H, dt, U_t); break;
+    case 3: hipLaunchKernelGGL(u_stack_kernel<3>, g, b, 0, st, H_t, n_H, dt, U_t); break;
+    case 4: hipLaunchKernelGGL(u_stack_kernel<4>, g, b, 0, st, H_t, n_H, dt, U_t); break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_tables(const TablesArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL(tables_kernel, dim3(1), dim3(kBlock), 0, st, a);
+    // an entry or two per thread (one block took 42 us for the 35 tables of
+    // 16 x 16 at M = 4, L = 6)
+    const int total = BankLayout{a.L}.count() * a.M * a.M * a.M * a.M;
+    hipLaunchKernelGGL(tables_kernel, dim3(std::min(64, (total + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, a);
     return hipGetLastError();
 }
 
