@@ -976,9 +976,8 @@ bool single_mirror_on(const quapi_ctx *c) {
 }
 
 // Launch a full-window single step with the arguments of prepare_step: one
-// launch, or in mirror mode the launches over the high-digit values below
-// their mirror (mode 1) and equal to it (modes 2, 3).  *rows: the rho
-// partial rows written.
+// launch over every block, or in mirror mode over the kept half.  *rows: the
+// rho partial rows written.
 hipError_t launch_full_step(quapi_ctx *c, bool rho, StepArgs a, int grid, int *rows) {
     if (!single_mirror_on(c)) {
         a.mode = 0;
@@ -986,39 +985,16 @@ hipError_t launch_full_step(quapi_ctx *c, bool rho, StepArgs a, int grid, int *r
         return launch_step(c->N, c->prec, rho, false, a, grid, c->stream);
     }
     const Layout &l = c->lay;
-    hipError_t e = hipSuccess;
-    const bool listed = c->N == 9;      // the diagonal values' items in the tail of mode 1
-    if (l.n_canon1 > 0 || (listed && l.n_diag1 > 0)) {
-        a.mode = 1;
-        a.blk_hi = c->blk1;
-        a.n_canon = l.n_canon1;
-        a.n_blk = l.n_canon1 + (listed ? l.n_diag1 * l.parts1 : 0);
-        a.low_list = c->low1;
-        a.n_low = l.n_low1;
-        a.parts = listed ? l.parts1 : 1;
-        a.q_span = l.span1;
-        a.part_base = 0;
-        e = launch_step(c->N, c->prec, rho, false, a, grid, c->stream);
-    }
-    if (e == hipSuccess && l.n_diag1 > 0 && !listed) {
-        a.mode = 2;
-        a.blk_hi = c->blk1 + l.n_canon1;
-        a.n_blk = l.n_diag1 * l.parts1;
-        a.parts = l.parts1;
-        a.q_span = l.span1;
-        a.part_base = l.n_canon1;
-        e = launch_step(c->N, c->prec, rho, false, a, grid, c->stream);
-    }
-    if (e == hipSuccess && l.n_diag1 > 0) {
-        a.mode = 3;
-        a.blk_hi = c->blk1 + l.n_canon1;
-        a.n_blk = l.n_diag1;
-        a.parts = 1;
-        a.part_base = l.n_canon1 + l.n_diag1 * l.parts1;
-        e = launch_step(c->N, c->prec, rho, false, a, grid, c->stream);
-    }
-    *rows = l.n_canon1 + l.n_diag1 * (l.parts1 + 1);
-    return e;
+    a.mode = 1;
+    a.blk_hi = c->blk1;
+    a.low_list = c->low1;
+    a.n_low = l.n_low1;
+    a.n_canon = l.n_canon1;
+    a.n_diag = l.n_diag1;
+    a.parts = l.parts1;
+    a.q_span = l.span1;
+    a.n_blk = *rows = l.n_canon1 + l.n_diag1 * (l.parts1 + 1);
+    return launch_step(c->N, c->prec, rho, false, a, grid, c->stream);
 }
 
 quapi_status enqueue_step(quapi_ctx *c, int n, bool rho) {

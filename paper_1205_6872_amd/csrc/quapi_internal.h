@@ -64,18 +64,16 @@ struct StepArgs {
     int old_tab, oldf_tab;      // bank indices of the oldest-point tables
     int16_t tab[kMaxL];         // bank index of the interior table for digit j
     int16_t tabf[kMaxL];        // bank index of the final-point table for digit j
-    // Mirror mode of the N = 4, 9 and 16 single steps (as for the three-step
-    // kernel): mode 1 the high-digit values blk_hi[..] below their mirror
-    // (n_canon of them), mode 2 those equal to it in `parts` blocks of q_span
-    // sweep rows (items below their mirror), mode 3 the same values, the items
-    // that are their own mirror; rho partials at row part_base + block.  At
-    // N = 9 the mode-1 launch also runs, after its n_canon blocks, `parts`
-    // blocks per value equal to its mirror over q_span items of low_list (the
-    // n_low indices qm * R + r below their mirror), and mode 2 does not run.
-    // Mode 0: every block.
+    // Mirror mode of the N = 4, 9 and 16 single steps (mode 1: on, one launch of
+    // n_blk blocks): a block per high-digit value blk_hi[..] below its mirror
+    // (n_canon of them), then `parts` blocks per value equal to it (n_diag of
+    // them, listed after) for its items below their mirror -- q_span sweep rows
+    // each, or at N = 9 q_span items of low_list (the n_low indices qm * R + r
+    // below their mirror) -- then a block per such value for the items that are
+    // their own mirror.  rho partials at row block.  Mode 0: every block.
     const int *blk_hi;
     const int *low_list;
-    int n_blk, n_canon, parts, q_span, part_base, mode, n_low;
+    int n_blk, n_canon, n_diag, parts, q_span, mode, n_low;
     // N = 16 full-window steps (L >= 2) with the new points grouped by their
     // oldest-point rows (cls_on): the row of o is F_self(o) times the
     // influence row of the oldest point, which depends on o = (a, b) only
@@ -250,14 +248,14 @@ hipError_t launch_init_tensor(int N, int prec, const double2 *rho0, const double
 hipError_t launch_step(int N, int prec, bool with_rho, bool grow, const StepArgs &a, int grid,
                        hipStream_t st);
 // Where finalized rho values go: rho of the k-th finalize after a reset is
-// written to base + k*N.  Device-resident, so graph replays need no new arguments.
+// written to base + k*N (k counted per point).  Device-resident, so graph replays need no new arguments.
 struct RhoSink {
     double2 *base;
-    unsigned long long count;
+    unsigned long long count[kMaxN];         // per point o
 };
 
-// Sums the block partials of rho into the sink's next slot: two launches on
-// st, using pairs (kRhoSlices * N * 2 complex) as scratch.
+// Sums the block partials of rho into the sink's next slot: one launch on st, or
+// for many rows two, using pairs (kRhoSlices * N * 2 complex) as scratch.
 constexpr int kRhoSlices = 256;
 hipError_t launch_rho_finalize(int N, const double2 *partials, int n_blocks, double2 *pairs, RhoSink *sink,
                                hipStream_t st);

@@ -405,8 +405,8 @@ struct MirrorDigits {
         return out;
     }
 };
-template <int N, typename S, typename T, bool RHO, bool GROW, int MODE = 0>
-__global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
+template <int N, typename S, typename T, bool RHO, bool GROW, int MODE>
+__device__ __forceinline__ void step_body(const StepArgs &a, const int bid) {
     static_assert(MODE == 0 || ((N == 4 || N == 9) && !GROW), "mirror mode: full-window N = 4, 9 steps");
     using MD = MirrorDigits<N == 9 ? 9 : 4>;
     using C = typename Cx<T>::type;
@@ -436,12 +436,13 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
     // N = 9, mode 1: blocks below n_canon run the canonical high-digit values,
     // the rest the listed items of the values equal to their mirror
     constexpr bool kListed = N == 9 && MODE == 1;
-    const bool listed = kListed && (int)blockIdx.x >= a.n_canon;
-    const int lblk = listed ? (int)blockIdx.x - a.n_canon : 0;
-    const long long blk = MODE == 0   ? (long long)blockIdx.x
+    const bool listed = kListed && bid >= a.n_canon;
+    const int lblk = listed ? bid - a.n_canon : 0;
+    const long long blk = MODE == 0   ? (long long)bid
                           : listed    ? (long long)a.blk_hi[a.n_canon + lblk / a.parts]
-                          : MODE == 2 ? (long long)a.blk_hi[blockIdx.x / a.parts]
-                                      : (long long)a.blk_hi[blockIdx.x];     // high digits
+                          : MODE == 1 ? (long long)a.blk_hi[bid]
+                          : MODE == 2 ? (long long)a.blk_hi[a.n_canon + bid / a.parts]
+                                      : (long long)a.blk_hi[a.n_canon + bid];     // high digits
     const double2 one = make_double2(1.0, 0.0);
     const bool planned = a.t_lo != nullptr;
     const int j_hi = a.d_lo + a.d_mid;
@@ -531,7 +532,7 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
         // listed block (N = 9) walks its part of the list of the items below
         // their mirror (qm * R + r, the same for every diagonal high value),
         // one item per active thread
-        const int part = listed ? lblk % a.parts : MODE == 2 ? (int)(blockIdx.x % a.parts) : 0;
+        const int part = listed ? lblk % a.parts : MODE == 2 ? bid % a.parts : 0;
         const bool thread_runs = MODE != 3 || MD::diagonal_only(r);
         int n_diag_rows = 1;
         if (MODE == 3)
@@ -647,122 +648,149 @@ __global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
                     s.y -= s_red[w * N + tb].y;
                 }
             }
-            a.partials[((size_t)a.part_base + (MODE == 0 ? blk : (long long)blockIdx.x)) * N + t] = s;
+            a.partials[(size_t)blockIdx.x * N + t] = s;
         }
     }
+}
+
+template <int N, typename S, typename T, bool RHO, bool GROW>
+__global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
+    step_body<N, S, T, RHO, GROW, 0>(a, (int)blockIdx.x);
+}
+// Mirror mode in one launch: the blocks of mode 1 (at N = 9 with their listed
+// tail, which is then all of the diagonal values' items below their mirror),
+// those of mode 2 (N = 4), then those of mode 3.
+template <int N, typename S, typename T, bool RHO>
+__global__ void __launch_bounds__(kBlock) step_mirror_kernel(const StepArgs a) {
+    const int n2 = a.n_diag * a.parts, b = (int)blockIdx.x - a.n_canon;
+    if (b < (N == 9 ? n2 : 0)) step_body<N, S, T, RHO, false, 1>(a, (int)blockIdx.x);
+    else if (N != 9 && b < n2) step_body<N, S, T, RHO, false, 2>(a, b);
+    else step_body<N, S, T, RHO, false, 3>(a, b - n2);
 }
 
 // rho(t_n)[o] = sum over the step's block partials, compensated, in a fixed
-// order, in two launches on the side stream (each launch boundary makes the
-// previous writes visible without device-scope fences):
-//   rho_slice_kernel   kSlices blocks; block b sums rows [b*rows/kSlices,
-//                      (b+1)*rows/kSlices) -- thread t takes rows t, t+kBlock, ...
-//                      with Neumaier sums, then a fixed two-sum tree -- and
-//                      writes a (sum, compensation) pair per o;
-//   rho_final_kernel   one block combines the kSlices pairs in a fixed tree and
-//                      writes rho to sink->base + sink->count * N, then advances
-//                      sink->count (so a captured graph can replay it unchanged).
+// order (each launch boundary makes the previous writes visible without
+// device-scope fences), to sink->base + sink->count[o] * N + o; block o advances
+// its own count, so a captured graph can replay the launch unchanged.
+//   up to kDirectRows rows  rho_direct_kernel: one launch, a block per o;
+//   more                    rho_slice_kernel: kSlices blocks, block b a
+//                           contiguous share of the rows, a (sum, compensation)
+//                           pair per o; then rho_final_kernel, a block per o.
+// Bound by latency (a row set is 0.1 - 1 MB): threads run Neumaier sums, the
+// lanes of a wave are combined by shuffles in pairs, then the waves.  One block
+// that took the points one after the other, each through a tree of barriers,
+// ran 36 us at N = 16 and 8 us at N = 4, now 5.
 constexpr int kSlices = kRhoSlices;
+constexpr int kDirectRows = 8192;        // 32 rows per thread
+
+// The block's (sum, compensation) pairs (re in r, im in i) combined in a fixed
+// order; the total lands in thread 0.
+__device__ __forceinline__ void block_combine_pairs(double2 &r, double2 &i) {
+    __shared__ double2 s_p[2][kBlock / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double2 r2 = make_double2(__shfl_down(r.x, off, 64), __shfl_down(r.y, off, 64));
+        const double2 i2 = make_double2(__shfl_down(i.x, off, 64), __shfl_down(i.y, off, 64));
+        two_sum_combine(r.x, r.y, r2.x, r2.y);
+        two_sum_combine(i.x, i.y, i2.x, i2.y);
+    }
+    if (lane == 0) {
+        s_p[0][wave] = r;
+        s_p[1][wave] = i;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kBlock / 64; ++w) {
+            two_sum_combine(r.x, r.y, s_p[0][w].x, s_p[0][w].y);
+            two_sum_combine(i.x, i.y, s_p[1][w].x, s_p[1][w].y);
+        }
+}
+__device__ __forceinline__ void sink_put(RhoSink *sink, int N, int o, double2 r, double2 i) {
+    const unsigned long long k = sink->count[o];
+    sink->base[k * N + o] = make_double2(r.x + r.y, i.x + i.y);
+    sink->count[o] = k + 1;
+}
+
+__global__ void __launch_bounds__(kBlock) rho_direct_kernel(const double2 *__restrict__ partials, int rows,
+                                                            RhoSink *sink) {
+    const int o = blockIdx.x, N = gridDim.x;
+    double2 r = make_double2(0.0, 0.0), i = r;
+    constexpr int U = 8;                  // rows in flight per thread
+    int k = threadIdx.x;
+    for (; k + (U - 1) * kBlock < rows; k += U * kBlock) {
+        double2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = partials[(size_t)(k + u * kBlock) * N + o];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            neumaier(r.x, r.y, v[u].x);
+            neumaier(i.x, i.y, v[u].y);
+        }
+    }
+    for (; k < rows; k += kBlock) {
+        const double2 v = partials[(size_t)k * N + o];
+        neumaier(r.x, r.y, v.x);
+        neumaier(i.x, i.y, v.y);
+    }
+    block_combine_pairs(r, i);
+    if (threadIdx.x == 0) sink_put(sink, N, o, r, i);
+}
+
+// One point o per thread and kBlock / N row lanes: a row's N values are read by
+// N neighbouring threads; the lanes of a point are then combined in lane order.
 template <int N>
 __global__ void __launch_bounds__(kBlock) rho_slice_kernel(const double2 *__restrict__ partials, int rows,
                                                             double2 *__restrict__ pairs) {
-    const int t = threadIdx.x;
-    const int b = blockIdx.x;
+    const int t = threadIdx.x, b = blockIdx.x;
     const long long r0 = (long long)rows * b / kSlices, r1 = (long long)rows * (b + 1) / kSlices;
-    if constexpr (N >= 9) {
-        // one point o per thread and kBlock / N row lanes: a row's N values
-        // are read by N neighbouring threads, and each thread keeps one pair
-        // of compensated sums; the lanes of a point are then combined in
-        // lane order by one thread
-        constexpr int RL = kBlock / N;
-        __shared__ double s_p[4][kBlock];
-        const int o = t % N, lane_r = t / N;
-        double sr = 0.0, cr = 0.0, si = 0.0, ci = 0.0;
-        if (lane_r < RL) {
-            for (long long r = r0 + lane_r; r < r1; r += RL) {
-                const double2 v = partials[(size_t)r * N + o];
-                neumaier(sr, cr, v.x);
-                neumaier(si, ci, v.y);
-            }
+    constexpr int RL = kBlock / N;
+    __shared__ double2 s_p[2][kBlock];
+    const int o = t % N, lane_r = t / N;
+    double2 r = make_double2(0.0, 0.0), i = r;
+    if (lane_r < RL)
+        for (long long k = r0 + lane_r; k < r1; k += RL) {
+            const double2 v = partials[(size_t)k * N + o];
+            neumaier(r.x, r.y, v.x);
+            neumaier(i.x, i.y, v.y);
         }
-        s_p[0][t] = sr;
-        s_p[1][t] = cr;
-        s_p[2][t] = si;
-        s_p[3][t] = ci;
+    s_p[0][t] = r;
+    s_p[1][t] = i;
+    __syncthreads();
+    // halve the row lanes while they are even, then add the odd rest in order
+    int n = RL;
+    for (; n % 2 == 0; n /= 2) {
+        if (t < n / 2 * N) {
+            const int u = t + n / 2 * N;
+            two_sum_combine(s_p[0][t].x, s_p[0][t].y, s_p[0][u].x, s_p[0][u].y);
+            two_sum_combine(s_p[1][t].x, s_p[1][t].y, s_p[1][u].x, s_p[1][u].y);
+        }
         __syncthreads();
-        if (t < N) {
-            for (int k = 1; k < RL; ++k) {
-                const int u = k * N + t;
-                two_sum_combine(sr, cr, s_p[0][u], s_p[1][u]);
-                two_sum_combine(si, ci, s_p[2][u], s_p[3][u]);
-            }
-            pairs[((size_t)b * N + t) * 2] = make_double2(sr, si);
-            pairs[((size_t)b * N + t) * 2 + 1] = make_double2(cr, ci);
-        }
-        return;
     }
-    constexpr int U = N >= 16 ? 1 : 16 / N;   // rows in flight per thread
-    double sr[N], cr[N], si[N], ci[N];
-#pragma unroll
-    for (int o = 0; o < N; ++o) sr[o] = cr[o] = si[o] = ci[o] = 0.0;
-    long long r = r0 + t;
-    for (; r + (long long)(U - 1) * kBlock < r1; r += (long long)U * kBlock) {
-        double2 v[U][N];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int o = 0; o < N; ++o) v[u][o] = partials[(size_t)(r + (long long)u * kBlock) * N + o];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int o = 0; o < N; ++o) {
-                neumaier(sr[o], cr[o], v[u][o].x);
-                neumaier(si[o], ci[o], v[u][o].y);
-            }
-    }
-    for (; r < r1; r += kBlock) {
-#pragma unroll
-        for (int o = 0; o < N; ++o) {
-            const double2 v = partials[(size_t)r * N + o];
-            neumaier(sr[o], cr[o], v.x);
-            neumaier(si[o], ci[o], v.y);
+    if (t < N) {
+        r = s_p[0][t];
+        i = s_p[1][t];
+        for (int k = 1; k < n; ++k) {
+            const int u = k * N + t;
+            two_sum_combine(r.x, r.y, s_p[0][u].x, s_p[0][u].y);
+            two_sum_combine(i.x, i.y, s_p[1][u].x, s_p[1][u].y);
         }
-    }
-#pragma unroll
-    for (int o = 0; o < N; ++o) {
-        double a0 = sr[o], a1 = cr[o], a2 = si[o], a3 = ci[o];
-        block_reduce_pairs<kBlock>(a0, a1, a2, a3);
-        if (t == 0) {
-            pairs[((size_t)b * N + o) * 2] = make_double2(a0, a2);
-            pairs[((size_t)b * N + o) * 2 + 1] = make_double2(a1, a3);
-        }
+        pairs[((size_t)b * N + t) * 2] = r;
+        pairs[((size_t)b * N + t) * 2 + 1] = i;
     }
 }
 
-template <int N>
 __global__ void __launch_bounds__(kSlices) rho_final_kernel(const double2 *__restrict__ pairs, RhoSink *sink) {
-    const int t = threadIdx.x;
-    double2 *out = nullptr;
-    unsigned long long count = 0;
-    if (t == 0) {
-        count = sink->count;
-        out = sink->base + count * N;
-    }
-#pragma unroll
-    for (int o = 0; o < N; ++o) {
-        const double2 sv = pairs[((size_t)t * N + o) * 2], cv = pairs[((size_t)t * N + o) * 2 + 1];
-        double a0 = sv.x, a1 = cv.x, a2 = sv.y, a3 = cv.y;
-        block_reduce_pairs<kSlices>(a0, a1, a2, a3);
-        if (t == 0) out[o] = make_double2(a0 + a1, a2 + a3);
-    }
-    if (t == 0) sink->count = count + 1;
+    static_assert(kSlices == kBlock, "a thread per slice");
+    const int o = blockIdx.x, N = gridDim.x;
+    double2 r = pairs[((size_t)threadIdx.x * N + o) * 2], i = pairs[((size_t)threadIdx.x * N + o) * 2 + 1];
+    block_combine_pairs(r, i);
+    if (threadIdx.x == 0) sink_put(sink, N, o, r, i);
 }
 
 __global__ void set_sink_kernel(RhoSink *sink, double2 *base) {
-    if (threadIdx.x == 0) {
-        sink->base = base;
-        sink->count = 0;
-    }
+    if (threadIdx.x == 0) sink->base = base;
+    if (threadIdx.x < kMaxN) sink->count[threadIdx.x] = 0;
 }
 
 // Factor products of the full-window digit split: t_lo[o][v] over digits
@@ -884,7 +912,7 @@ template <> struct Mfma16<double> {
 };
 
 template <typename S, typename T, bool RHO, int MODE, bool CLS>
-__global__ void __launch_bounds__(kBlock, (RHO && MODE <= 1) ? 3 : 1) step16_mfma_kernel(const StepArgs a) {
+__device__ __forceinline__ void step16_body(const StepArgs &a, const int bid, const int row) {
     constexpr int N = 16, NB = CLS ? (RHO ? 2 : 1) : (RHO ? 4 : 2);
     // A-fragment blocks held in registers; the rest are read from LDS per use
     constexpr int kRegBlocks = !RHO ? NB : !CLS ? 0 : sizeof(T) == 8 ? 1 : NB;
@@ -901,9 +929,10 @@ __global__ void __launch_bounds__(kBlock, (RHO && MODE <= 1) ? 3 : 1) step16_mfm
     T *s_afr = (T *)(smem + lay.afr);
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int j = lane & 15, g = lane >> 4;
-    const long long blk = MODE == 0   ? (long long)blockIdx.x
-                          : MODE == 2 ? (long long)a.blk_hi[blockIdx.x / a.parts]
-                                      : (long long)a.blk_hi[blockIdx.x];     // high digits
+    const long long blk = MODE == 0   ? (long long)bid
+                          : MODE == 1 ? (long long)a.blk_hi[bid]
+                          : MODE == 2 ? (long long)a.blk_hi[a.n_canon + bid / a.parts]
+                                      : (long long)a.blk_hi[a.n_canon + bid];     // high digits
 
     for (int idx = t; idx < N * Q; idx += kBlock) {
         const int o = idx / Q;
@@ -971,7 +1000,7 @@ __global__ void __launch_bounds__(kBlock, (RHO && MODE <= 1) ? 3 : 1) step16_mfm
     // sweep rows: all (mode 0, 1), a part of them (mode 2), or those whose
     // digits are all diagonal (mode 3)
     const int dm = (31 - __clz(Q)) >> 2;
-    const int part = MODE == 2 ? (int)(blockIdx.x % a.parts) : 0;
+    const int part = MODE == 2 ? (bid % a.parts) : 0;
     const int i0 = (MODE == 2 ? part * a.q_span : 0) + wave;
     const int i1 = MODE == 3 ? (1 << (2 * dm)) : MODE == 2 ? min(Q, (part + 1) * a.q_span) : Q;
     // the item of sweep index it: its index m, its mirror, and whether it runs
@@ -1119,9 +1148,29 @@ __global__ void __launch_bounds__(kBlock, (RHO && MODE <= 1) ? 3 : 1) step16_mfm
                 s.x += sb.x;
                 s.y -= sb.y;
             }
-            a.partials[((size_t)a.part_base + blockIdx.x) * N + t] = s;
+            a.partials[(size_t)row * N + t] = s;
         }
     }
+}
+
+// Mode 0, or mode 1 alone.
+template <typename S, typename T, bool RHO, bool CLS, int MODE>
+__global__ void __launch_bounds__(kBlock, RHO ? 3 : 1) step16_mfma_kernel(const StepArgs a) {
+    step16_body<S, T, RHO, MODE, CLS>(a, (int)blockIdx.x, (int)blockIdx.x);
+}
+// Mirror mode in one launch (ALL): the blocks of mode 1, then those of mode 2,
+// then those of mode 3; as three launches the last two, too few blocks to fill
+// the GPU, took 12 of 43 us at M = 4, L = 6, complex64 (51.6 -> 42.3 us per
+// step).  With FP64 arithmetic the three together need registers that cost the
+// mode-1 blocks waves (L = 6, complex128 without rho 66 -> 72 us), so those keep
+// a launch of their own and only the other two share one.
+template <typename S, typename T, bool RHO, bool CLS, bool ALL>
+__global__ void __launch_bounds__(kBlock, ALL ? (RHO ? 3 : 4) : 1) step16_mirror_kernel(const StepArgs a) {
+    const int row = (int)blockIdx.x + (ALL ? 0 : a.n_canon);
+    const int n2 = a.n_diag * a.parts, b = row - a.n_canon;
+    if (ALL && b < 0) step16_body<S, T, RHO, 1, CLS>(a, row, row);
+    else if (b < n2) step16_body<S, T, RHO, 2, CLS>(a, b, row);
+    else step16_body<S, T, RHO, 3, CLS>(a, b - n2, row);
 }
 
 template <typename S, typename T, bool RHO, bool CLS>
@@ -1129,12 +1178,15 @@ hipError_t launch_step16_c(const StepArgs &a, int grid, hipStream_t st) {
     using C = typename Cx<T>::type;
     const Step16Lds lay = step16_lds_layout((int)sizeof(C), RHO, a.Q, RHO && (!CLS || sizeof(T) == 8));
     const dim3 b(kBlock);
-    switch (a.mode) {
-    case 0: hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, 0, CLS>), dim3(grid), b, lay.total, st, a); break;
-    case 1: hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, 1, CLS>), dim3(a.n_blk), b, lay.total, st, a); break;
-    case 2: hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, 2, CLS>), dim3(a.n_blk), b, lay.total, st, a); break;
-    case 3: hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, 3, CLS>), dim3(a.n_blk), b, lay.total, st, a); break;
-    default: return hipErrorInvalidValue;
+    if (a.mode == 0) {
+        hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, CLS, 0>), dim3(grid), b, lay.total, st, a);
+    } else if constexpr (sizeof(T) == 4) {
+        hipLaunchKernelGGL((step16_mirror_kernel<S, T, RHO, CLS, true>), dim3(a.n_blk), b, lay.total, st, a);
+    } else {
+        if (a.n_canon > 0)
+            hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, CLS, 1>), dim3(a.n_canon), b, lay.total, st, a);
+        hipLaunchKernelGGL((step16_mirror_kernel<S, T, RHO, CLS, false>), dim3(a.n_blk - a.n_canon), b, lay.total, st,
+                           a);
     }
     return hipGetLastError();
 }
@@ -1154,12 +1206,9 @@ hipError_t launch_step_t(const StepArgs &a, int grid, hipStream_t st) {
     const StepLds lay = step_lds_layout(N, (int)sizeof(C), RHO, GROW ? 1 : N, a.R, a.Q, N <= 4);
     const dim3 b(kBlock);
     if constexpr ((N == 4 || N == 9) && !GROW) {
-        switch (a.mode) {
-        case 0: break;
-        case 1: hipLaunchKernelGGL((step_kernel<N, S, T, RHO, GROW, 1>), dim3(a.n_blk), b, lay.total, st, a); return hipGetLastError();
-        case 2: hipLaunchKernelGGL((step_kernel<N, S, T, RHO, GROW, 2>), dim3(a.n_blk), b, lay.total, st, a); return hipGetLastError();
-        case 3: hipLaunchKernelGGL((step_kernel<N, S, T, RHO, GROW, 3>), dim3(a.n_blk), b, lay.total, st, a); return hipGetLastError();
-        default: return hipErrorInvalidValue;
+        if (a.mode != 0) {
+            hipLaunchKernelGGL((step_mirror_kernel<N, S, T, RHO>), dim3(a.n_blk), b, lay.total, st, a);
+            return hipGetLastError();
         }
     } else {
         if (a.mode != 0) return hipErrorInvalidValue;
@@ -1266,19 +1315,20 @@ hipError_t launch_set_sink(RhoSink *sink, double2 *base, hipStream_t st) {
 
 hipError_t launch_rho_finalize(int N, const double2 *partials, int n_blocks, double2 *pairs, RhoSink *sink,
                                hipStream_t st) {
+    if (N < 1 || N > kMaxN) return hipErrorInvalidValue;
+    if (n_blocks <= kDirectRows) {
+        hipLaunchKernelGGL(rho_direct_kernel, dim3(N), dim3(kBlock), 0, st, partials, n_blocks, sink);
+        return hipGetLastError();
+    }
+    const dim3 g(kSlices), b(kBlock);
     switch (N) {
-#define QUAPI_FIN(NV)                                                                                  \
-    case NV:                                                                                           \
-        hipLaunchKernelGGL(rho_slice_kernel<NV>, dim3(kSlices), dim3(kBlock), 0, st, partials, n_blocks, pairs); \
-        hipLaunchKernelGGL(rho_final_kernel<NV>, dim3(1), dim3(kSlices), 0, st, pairs, sink);          \
-        break;
-        QUAPI_FIN(1)
-        QUAPI_FIN(4)
-        QUAPI_FIN(9)
-        QUAPI_FIN(16)
-#undef QUAPI_FIN
+    case 1: hipLaunchKernelGGL(rho_slice_kernel<1>, g, b, 0, st, partials, n_blocks, pairs); break;
+    case 4: hipLaunchKernelGGL(rho_slice_kernel<4>, g, b, 0, st, partials, n_blocks, pairs); break;
+    case 9: hipLaunchKernelGGL(rho_slice_kernel<9>, g, b, 0, st, partials, n_blocks, pairs); break;
+    case 16: hipLaunchKernelGGL(rho_slice_kernel<16>, g, b, 0, st, partials, n_blocks, pairs); break;
     default: return hipErrorInvalidValue;
     }
+    hipLaunchKernelGGL(rho_final_kernel, dim3(N), dim3(kSlices), 0, st, pairs, sink);
     return hipGetLastError();
 }
 
