@@ -237,11 +237,12 @@ quapi_status quapi_propagate_static(const quapi_params *p, int n_steps, const in
 
 /* The persistent path.  A context whose tensor has at most 2^14 entries
  * (N^L; M = 2 up to dk_max = 7, M = 3 up to 4, M = 4 up to 3) runs every
- * step of a call in one launch, one workgroup per context: the tensor stays
+ * step of a call in a launch or two, one workgroup per context: the tensor stays
  * in LDS when both of its buffers fit there (M = 2 up to dk_max = 6),
  * otherwise in the context's two buffers in HBM, which stay in the L2 cache
  * at these sizes; a step costs a workgroup barrier instead of kernel
- * launches.  Not for driven contexts, contexts whose launch width is pinned
+ * launches.  For M = 2, dk_max = 5 .. 7, the steps past dk_max run in a second
+ * launch with the tensor in the workgroup's registers.  Not for driven contexts, contexts whose launch width is pinned
  * (quapi_set_fused_steps != 0) or mirror mode 2.  Results do not depend on
  * how a run is split into calls or batched.
  *   quapi_persistent:  *mode = 0 (multi-block kernels), 1 (persistent, tensor

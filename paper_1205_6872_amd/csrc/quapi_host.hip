@@ -494,7 +494,8 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_low1 = take((size_t)l.n_low1 * sizeof(int));
     const bool tile = !filtered && tile_ok(N, L);
     l.off_ttab = take(tile ? tile_table_entries(L) * 16 : 0);
-    l.off_tcoef = take(tile ? (size_t)kTileCoefCount * 8 : 0);
+    const bool reg = !filtered && N == 4 && L >= kRegMinL && L <= kRegMaxL;
+    l.off_tcoef = take(tile || reg ? (size_t)kTileCoefCount * 8 : 0);
     l.off_trows = take(tile ? (size_t)2 * kTileSteps * tile_blocks(L) * N * 16 : 0);
     const size_t fc = filtered ? filter_cap : 0;
     for (int b = 0; b < 2; ++b) {
@@ -570,6 +571,8 @@ struct quapi_ctx {
     // persistent path (small tensors, quapi_small.hip): 0 off, 1 tensor in
     // LDS, 2 tensor in the context's global buffers
     int small = 0;
+    // its full-window steps run with the tensor in registers (M = 2, L = 5 .. 7)
+    bool reg = false, reg_coef_ready = false;
     // Mirror mode of the full-window kernels: they read and write only the
     // entries not above their mirror; half_cur says A[cur] holds only those.
     bool mirror_ok = false;       // M = 2, 3, 4, L >= 2, rho0 exactly Hermitian
@@ -1661,6 +1664,25 @@ bool small_on(const quapi_ctx *c) {
     return c->small != 0 && c->n_H == 0 && !c->fuse_pinned && c->mirror != 2;
 }
 
+// The coefficients of the register kernel, once per context.
+quapi_status reg_prepare(quapi_ctx *c) {
+    if (!c->reg || c->reg_coef_ready) return QUAPI_OK;
+    TilePlanArgs pa{};
+    pa.bank = c->bank;
+    pa.eta = c->eta;
+    pa.s = (const double *)(c->ws + c->lay.off_s);
+    pa.L = c->L;
+    pa.coef_only = 1;
+    pa.coef = c->tcoef;
+    const hipError_t e = launch_tile_tables(c->prec, pa, c->stream);
+    if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "coefficient kernel launch: %s", hipGetErrorString(e));
+    c->reg_coef_ready = true;
+    return QUAPI_OK;
+}
+
+// Steps of a run of k that the register kernel does not take: up to n = L.
+int reg_head(const quapi_ctx *c, int k) { return c->reg ? std::min(k, std::max(0, c->L - c->step)) : k; }
+
 SmallCtxArgs small_args(const quapi_ctx *c, int n_steps, int rho_mode, double2 *rho_out) {
     SmallCtxArgs s{};
     s.bank = c->bank;
@@ -1671,7 +1693,22 @@ SmallCtxArgs small_args(const quapi_ctx *c, int n_steps, int rho_mode, double2 *
     s.step0 = c->step;
     s.n_steps = n_steps;
     s.rho_mode = rho_mode;
+    s.eta = c->eta;
+    s.s = (const double *)(c->ws + c->lay.off_s);
+    s.coef = c->tcoef;
     return s;
+}
+
+// A run of k steps in two launches: the first head steps, which leave the
+// tensor in A[cur] (head even) or in the other buffer, and the rest.
+void split_small(const SmallCtxArgs &all, int head, SmallCtxArgs *first, SmallCtxArgs *rest) {
+    *first = *rest = all;
+    first->n_steps = head;
+    if (all.rho_mode == 2 && head < all.n_steps) first->rho_mode = 0;
+    rest->n_steps = all.n_steps - head;
+    rest->step0 += head;
+    if (head & 1) std::swap(rest->a0, rest->a1);
+    if (all.rho_mode == 1) rest->rho_out += (size_t)head * 4;
 }
 
 // After a persistent launch of n steps: the tensor is in A[cur] after an
@@ -1699,6 +1736,7 @@ quapi_status propagate_small(quapi_ctx *c, int n_steps, const int *sel, int n_se
     }
     quapi_status st = join_side(c);
     if (st == QUAPI_OK) st = ensure_full(c);
+    if (st == QUAPI_OK) st = reg_prepare(c);
     if (st != QUAPI_OK) return st;
     auto flush = [&]() -> quapi_status {
         if (!staged) return QUAPI_OK;
@@ -1731,15 +1769,17 @@ quapi_status propagate_small(quapi_ctx *c, int n_steps, const int *sel, int n_se
             if (mode == 1) k = std::min(k, kRhoStage - staged);
         }
         double2 *out = dev_out ? dev_out + (size_t)written * N : c->stage + (size_t)staged * N;
-        SmallBatchArgs b;
-        b.c[0] = small_args(c, k, mode, out);
+        SmallBatchArgs b, br;
+        const int head = reg_head(c, k);
+        split_small(small_args(c, k, mode, out), head, &b.c[0], &br.c[0]);
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (c->timing) {
             e0 = take_event(c);
             e1 = take_event(c);
             if (e0) (void)hipEventRecord(e0, c->stream);
         }
-        hipError_t e = launch_small(N, c->prec, c->small == 1, b, 1, c->L, c->stream);
+        hipError_t e = head > 0 ? launch_small(N, c->prec, c->small == 1, b, 1, c->L, c->stream) : hipSuccess;
+        if (e == hipSuccess && head < k) e = launch_small_reg(c->prec, c->L, br, 1, c->stream);
         if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "persistent step launch: %s", hipGetErrorString(e));
         if (c->timing && e0 && e1) {
             (void)hipEventRecord(e1, c->stream);
@@ -2184,6 +2224,8 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
         if (ent <= (size_t)kSmallMaxEntries && !filtered) {
             c->small = small_lds_bytes(N, c->prec, L, true) <= (size_t)lds_max ? 1
                        : small_lds_bytes(N, c->prec, L, false) <= (size_t)lds_max ? 2 : 0;
+            c->reg = N == 4 && L >= kRegMinL && L <= kRegMaxL &&
+                     small_reg_lds_bytes(L, c->prec) <= (size_t)lds_max;
         }
     }
     c->pa_h = std::move(pa);
@@ -2514,6 +2556,7 @@ quapi_status quapi_propagate_batch(quapi_ctx *const *ctxs, int n_ctx, const int 
         quapi_ctx *c = ctxs[k];
         quapi_status st = join_side(c);
         if (st == QUAPI_OK) st = ensure_full(c);
+        if (st == QUAPI_OK) st = reg_prepare(c);
         if (st != QUAPI_OK) return st;
         if (k > 0) {
             HIP_TRY(c, hipEventRecord(c->ev_fork, c->stream));
@@ -2533,13 +2576,35 @@ quapi_status quapi_propagate_batch(quapi_ctx *const *ctxs, int n_ctx, const int 
         };
         for (int k = 0; k < n_ctx; ++k) {
             quapi_ctx *c = ctxs[k];
-            if (c->small != mode || n_steps[k] == 0) continue;
-            b.c[nb++] = small_args(c, n_steps[k], rho_mode[k], (double2 *)rho_out_dev[k]);
+            const int head = reg_head(c, n_steps[k]);
+            if (c->small != mode || head == 0) continue;
+            SmallCtxArgs rest;
+            split_small(small_args(c, n_steps[k], rho_mode[k], (double2 *)rho_out_dev[k]), head, &b.c[nb++], &rest);
             L_max = std::max(L_max, c->L);
             if (nb == kMaxSmallBatch)
                 if (quapi_status st = launch(); st != QUAPI_OK) return st;
         }
         if (quapi_status st = launch(); st != QUAPI_OK) return st;
+    }
+    // the steps past n = L of the M = 2 contexts whose tensor fits registers, a
+    // launch per memory length
+    for (int L = kRegMaxL; L >= kRegMinL; --L) {
+        SmallBatchArgs b;
+        int nb = 0;
+        for (int k = 0; k <= n_ctx; ++k) {
+            if (nb == kMaxSmallBatch || (k == n_ctx && nb > 0)) {
+                hipError_t e = launch_small_reg(c0->prec, L, b, nb, bs);
+                if (e != hipSuccess)
+                    return fail(c0, QUAPI_ERR_DEVICE, "persistent batch launch: %s", hipGetErrorString(e));
+                nb = 0;
+            }
+            if (k == n_ctx) break;
+            quapi_ctx *c = ctxs[k];
+            const int head = reg_head(c, n_steps[k]);
+            if (!c->reg || c->L != L || head == n_steps[k]) continue;
+            SmallCtxArgs first;
+            split_small(small_args(c, n_steps[k], rho_mode[k], (double2 *)rho_out_dev[k]), head, &first, &b.c[nb++]);
+        }
     }
     for (int k = 0; k < n_ctx; ++k) small_advance(ctxs[k], n_steps[k]);
     // later work on every other context's stream waits for the launches

@@ -279,6 +279,9 @@ struct SmallCtxArgs {
     const double2 *bank;
     void *a0, *a1;              // the context's two tensor buffers
     double2 *rho_out;           // rho of the selected steps, N complex each, in step order
+    const double2 *eta;         // the register kernel: eta classes, coordinates, coefficients
+    const double *s;
+    const void *coef;
     int L;
     int step0;                  // global step reached before the launch
     int n_steps;
@@ -292,6 +295,11 @@ size_t small_lds_bytes(int N, int prec, int L, bool in_lds);
 // n_ctx blocks, block k running b.c[k]; L_max sizes the dynamic LDS.
 hipError_t launch_small(int N, int prec, bool in_lds, const SmallBatchArgs &b, int n_ctx, int L_max,
                         hipStream_t st);
+// The full-window steps past n = L of M = 2, L = 5 .. 7 with the tensor in a
+// block's registers (step0 >= L for every context, all of one L).
+constexpr int kRegMinL = 5, kRegMaxL = 7;
+size_t small_reg_lds_bytes(int L, int prec);
+hipError_t launch_small_reg(int prec, int L, const SmallBatchArgs &b, int n_ctx, hipStream_t st);
 // Fill every entry above its mirror (N = 4, 9 or 16) with the conjugate of the mirror.
 hipError_t launch_mirror_complete(int N, int prec, void *a, long long entries, hipStream_t st);
 hipError_t launch_step3_coef(const Coef3Args &a, hipStream_t st);
@@ -312,6 +320,7 @@ struct TilePlanArgs {
     const double2 *bank, *eta;
     const double *s;
     int L, d_mid, d_top;
+    int coef_only;                                   // the coefficients only (the persistent kernel's)
     double2 *t_w, *t_u, *t_mid, *t_top;              // [set][16], [set][16], [set][4^d_mid], [set][4^d_top]
     void *coef;                                      // kTileCoefCount reals (8 bytes each)
 };

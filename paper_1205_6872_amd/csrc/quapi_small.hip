@@ -15,8 +15,10 @@
 // stay in the L2 cache at these sizes.
 #include <hip/hip_runtime.h>
 
-#include "quapi_device.h"
+#include <type_traits>
+
 #include "quapi_internal.h"
+#include "quapi_step4.h"
 
 namespace quapi {
 namespace {
@@ -277,6 +279,215 @@ __global__ void __launch_bounds__(SmallBlock<N>::threads) small_kernel(const Sma
     }
 }
 
+// ------------------------------------------------ the window in registers
+// Full-window steps n > L of an M = 2 context with L = 5, 6 or 7, all steps of a
+// call in one launch: the tensor stays in the registers of one block, 16 entries
+// per thread (4^(L-2) threads), the two oldest points in a thread's registers.
+// Two steps contract those; one exchange through LDS then moves the next two
+// oldest points into the registers.  A thread's digits stand for the same ages
+// at every pair of steps, so its factors never change.  Pairs are fixed by the
+// global step number, (L+1, L+2), (L+3, L+4), ...: a call may begin or end inside
+// one, and every entry and every rho is formed by the same operations.
+//
+// Bound by the instructions of one compute unit, about 320 per stage and wave, and
+// the exchange.  Before, the tensor went through LDS, or at L = 7 through HBM
+// buffers (512 KB a step through one compute unit's L2 port), one item at a time.
+// One context, rho at every step / at the last, us per step, before -> now:
+//   L = 7  complex128 10.7 / 6.4 -> 4.2 / 2.8   complex64 7.8 / 4.3 -> 3.8 / 2.3
+//   L = 6              4.0 / 2.1 -> 1.5 / 1.0              3.0 / 1.4 -> 1.5 / 0.9
+//   L = 5              2.0 / 1.0 -> 1.3 / 0.8              1.9 / 0.9 -> 1.4 / 0.8
+// At L = 4 (16 columns, a quarter of a wave) a step would gain nothing.
+constexpr int kRegSets = 8;              // (stage, class, o in {1, 2})
+// A thread stands for U of the 4^(L-2) columns of 16 entries.  U = 2 at L = 7: 1024
+// threads leave 128 registers each, of which FP64 values alone take 64 (spilled:
+// 17.3 us per step).
+template <int L, int CSIZE> struct SmallReg {
+    static constexpr int cols = 1 << (2 * (L - 2)), U = L == 7 ? 2 : 1;
+    static constexpr int threads = cols / U, waves = threads / 64;
+    static constexpr int hi = 1 << (2 * (L - 4));            // values of the column's digits above the lowest two
+    static constexpr unsigned buf = cols * 16 * 8;           // exchange: 8 bytes per slot
+    static constexpr unsigned lds = buf + kRegSets * (16 + hi) * CSIZE + 2 * 2 * waves * 8 * 8;
+};
+// The slot of entry y (canonical index) is y ^ reg_bits(y): consecutive lanes'
+// 8-byte accesses cover the banks both at y = c + columns r (written) and at
+// y = r + 16 c (read).
+__device__ __forceinline__ constexpr int reg_bits(int y) { return (y >> 5) & 15; }
+
+template <int L, typename S, typename T>
+__global__ void __launch_bounds__((SmallReg<L, 2 * sizeof(T)>::threads)) small_reg_kernel(const SmallBatchArgs args) {
+    using C = typename Cx<T>::type;
+    using CS = typename Cx<S>::type;
+    using X = XSlot<C>;
+    using R = SmallReg<L, 2 * sizeof(T)>;
+    constexpr int TH = R::threads, U = R::U;
+    extern __shared__ __align__(16) unsigned char smem[];
+    typename X::type *s_x = (typename X::type *)smem;
+    C *s_lo = (C *)(smem + R::buf);                          // [set][16]
+    C *s_hi = s_lo + kRegSets * 16;                          // [set][hi]
+    double *s_red = (double *)(s_hi + kRegSets * R::hi);     // [pair parity][stage][wave][8]
+    const SmallCtxArgs &a = args.c[blockIdx.x];
+    int t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const BankLayout B{L};
+    const T *coef = (const T *)a.coef;
+    // factors over the thread's digits d2 .. d_(L-1), the lowest two (with the
+    // prefix) and the others, formed in FP64 and rounded once
+    for (int idx = t; idx < kRegSets * (16 + R::hi); idx += TH) {
+        const bool lo = idx < kRegSets * 16;
+        const int k = lo ? idx : idx - kRegSets * 16, q = lo ? k / 16 : k / R::hi;
+        const int st = q / 4, cls = q / 2 % 2, o = 1 + q % 2;
+        int v = lo ? k % 16 : k % R::hi;
+        double2 p = lo ? prefix4(a.bank, a.eta, a.s, L, o, cls, st) : make_double2(1.0, 0.0);
+        for (int j = lo ? 0 : 2; j < (lo ? 2 : L - 2); ++j, v >>= 2)
+            p = cmul(p, tab4(a.bank, tile_tab(B, L - 2 - j + st, cls), o, v & 3));
+        (lo ? s_lo : s_hi)[k] = from_d2<C>(p);
+    }
+    // the previous point of a pair's first step is the highest digit of the column
+    auto prev_k = [&](int c, double2 &k0, double2 &k3) {
+        const int prev = c >> (2 * (L - 3));
+        if (L >= 6) {
+            coef_k(coef, 0, __builtin_amdgcn_readfirstlane(prev), k0, k3);
+        } else {
+            const double2 *kd = (const double2 *)((const double *)coef + tc_k(0) + 4 * prev);
+            k0 = kd[0];
+            k3 = kd[1];
+        }
+    };
+    auto factor = [&](int q, int c) { return cmul(s_lo[q * 16 + (c & 15)], s_hi[q * R::hi + (c >> 4)]); };
+    int stage = (a.step0 - L) & 1;                           // of the next step
+    // the index of register r's entry: after a pair (or before the first), and
+    // after its first step (registers: new point, second oldest)
+    auto index = [&](int c, int r) { return stage ? (r >> 2) + 4 * c + (r & 3) * (R::cols * 4) : r + 16 * c; };
+    C w[U][16];
+    {
+        const CS *src = (const CS *)a.a0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) w[u][r] = conv<C>(src[index(t + TH * u, r)]);
+    }
+    __syncthreads();                                         // every entry is read, the factors are there
+    int n_out = 0, par = 0, pend = 0;                        // pend: steps whose wave sums wait in s_red
+    double2 *out = a.rho_out;
+    auto flush = [&]() {                                     // after a barrier that follows the wave sums
+        if (t < 8)
+            for (int st = 0; st < 2; ++st)
+                if (pend >> st & 1) {
+                    const double *p = s_red + (par * 2 + st) * R::waves * 8 + t;
+                    double v = 0.0;
+                    for (int k = 0; k < R::waves; ++k) v += p[k * 8];
+                    ((double *)(out + (size_t)n_out * 4))[t] = v;
+                    ++n_out;
+                }
+        if (t >= 8) n_out += (pend & 1) + (pend >> 1);
+        pend = 0;
+        par ^= 1;
+    };
+    // the wave's sums of one step: rows v0.x, v0.y, v1.x, v1.y (s0) and v2, v3 (s1)
+    auto add_rho = [&](int st, int c, C tf1, C tf2, double2 v0, double2 v3, double &s0, double &s1) {
+        const double2 v1 = to_d2(cmul(factor(4 * st + 2, c), tf1)), v2 = to_d2(cmul(factor(4 * st + 3, c), tf2));
+        s0 = row_add(s0, v0.x, 0, lane);
+        s0 = row_add(s0, v0.y, 1, lane);
+        s0 = row_add(s0, v1.x, 2, lane);
+        s0 = row_add(s0, v1.y, 3, lane);
+        s1 = row_add(s1, v2.x, 0, lane);
+        s1 = row_add(s1, v2.y, 1, lane);
+        s1 = row_add(s1, v3.x, 2, lane);
+        s1 = row_add(s1, v3.y, 3, lane);
+    };
+    auto put_rho = [&](int st, double s0, double s1) {
+        for (int off = 8; off > 0; off >>= 1) {
+            s0 += __shfl_xor(s0, off, 64);
+            s1 += __shfl_xor(s1, off, 64);
+        }
+        if ((lane & 15) == 0) {
+            double *p = s_red + ((par * 2 + st) * R::waves + wave) * 8;
+            p[lane >> 4] = s0;
+            p[4 + (lane >> 4)] = s1;
+        }
+        pend |= 1 << st;
+    };
+    // one step; STAGE 0 or 1 of the pair
+    auto step = [&](auto stage_c, bool sel) {
+        constexpr int ST = decltype(stage_c)::value;
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = t + TH * u;
+            C tf1, tf2;
+            double2 rd0, rd3, k0{}, k3{};
+            __builtin_amdgcn_sched_barrier(0);
+            if (ST == 0) prev_k(c, k0, k3);
+            if (sel) {
+                tile_stage<T, true, false, ST>(w[u], w[u], coef, factor(4 * ST, c), factor(4 * ST + 1, c), k0, k3, tf1,
+                                               tf2, rd0, rd3);
+                add_rho(ST, c, tf1, tf2, rd0, rd3, s0, s1);
+            } else {
+                tile_stage<T, false, false, ST>(w[u], w[u], coef, factor(4 * ST, c), factor(4 * ST + 1, c), k0, k3,
+                                                tf1, tf2, rd0, rd3);
+            }
+            if (sizeof(S) < sizeof(T)) {                     // a call may end after any step
+#pragma unroll
+                for (int r = 0; r < 16; ++r) w[u][r] = conv<C>(conv<CS>(w[u][r]));
+            }
+        }
+        if (sel) put_rho(ST, s0, s1);
+    };
+    auto selected = [&](int k) { return a.rho_mode == 1 || (a.rho_mode == 2 && k == a.n_steps - 1); };
+    for (int k = 0; k < a.n_steps; ++k) {                    // a pair, or the part of it in this call
+        // opaque per pair: the LDS slots and factors of a thread are formed or read
+        // again at each, not kept in registers over the run
+        asm volatile("" : "+v"(t));
+        if (stage == 0) {
+            step(std::integral_constant<int, 0>{}, selected(k));
+            stage = 1;
+            if (++k >= a.n_steps) break;
+        }
+        step(std::integral_constant<int, 1>{}, selected(k));
+        stage = 0;
+        // the next two oldest points into the registers: written at
+        // y = column + columns (new points), read at y = r + 16 column
+#pragma unroll
+        for (int part = 0; part < X::kParts; ++part) {
+            __syncthreads();
+            if (part == 0) flush();
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    s_x[(t ^ (reg_bits((t & 511) + R::cols * r))) + TH * u + R::cols * r] = X::get(w[u][r], part);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) X::set(w[u][r], s_x[16 * t + 16 * TH * u + (r ^ ((t >> 1) & 15))], part);
+        }
+    }
+    __syncthreads();
+    flush();
+    CS *dst = (CS *)((a.n_steps & 1) ? a.a1 : a.a0);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dst[index(t + TH * u, r)] = conv<CS>(w[u][r]);
+}
+
+template <int L, typename S, typename T>
+hipError_t launch_small_reg_t(const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
+    using R = SmallReg<L, 2 * sizeof(T)>;
+    hipLaunchKernelGGL((small_reg_kernel<L, S, T>), dim3(n_ctx), dim3(R::threads), R::lds, st, b);
+    return hipGetLastError();
+}
+template <int L>
+hipError_t launch_small_reg_l(int prec, const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
+    switch (prec) {
+    case kPrecC128: return launch_small_reg_t<L, double, double>(b, n_ctx, st);
+    case kPrecC64: return launch_small_reg_t<L, float, float>(b, n_ctx, st);
+    case kPrecC64F64: return launch_small_reg_t<L, float, double>(b, n_ctx, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 template <int N, typename S, typename T>
 hipError_t launch_small_t(bool in_lds, const SmallBatchArgs &b, int n_ctx, int L_max, hipStream_t st) {
     const SmallLds lay = small_lds_layout(N, (int)sizeof(typename Cx<S>::type), (int)sizeof(typename Cx<T>::type),
@@ -305,6 +516,21 @@ size_t small_lds_bytes(int N, int prec, int L, bool in_lds) {
     const int cs = prec == kPrecC128 ? 16 : 8;
     const int cc = prec == kPrecC64 ? 8 : 16;
     return small_lds_layout(N, cs, cc, L, in_lds).total;
+}
+
+size_t small_reg_lds_bytes(int L, int prec) {
+    if (prec == kPrecC64) return L == 5 ? SmallReg<5, 8>::lds : L == 6 ? SmallReg<6, 8>::lds : SmallReg<7, 8>::lds;
+    return L == 5 ? SmallReg<5, 16>::lds : L == 6 ? SmallReg<6, 16>::lds : SmallReg<7, 16>::lds;
+}
+
+hipError_t launch_small_reg(int prec, int L, const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
+    if (n_ctx < 1 || n_ctx > kMaxSmallBatch) return hipErrorInvalidValue;
+    switch (L) {
+    case 5: return launch_small_reg_l<5>(prec, b, n_ctx, st);
+    case 6: return launch_small_reg_l<6>(prec, b, n_ctx, st);
+    case 7: return launch_small_reg_l<7>(prec, b, n_ctx, st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_small(int N, int prec, bool in_lds, const SmallBatchArgs &b, int n_ctx, int L_max,

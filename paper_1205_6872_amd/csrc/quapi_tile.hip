@@ -37,36 +37,14 @@
 
 #include <algorithm>
 
-#include "quapi_device.h"
 #include "quapi_internal.h"
+#include "quapi_step4.h"
 
 namespace quapi {
 namespace {
 
 constexpr int kWaves = kBlock / 64;
 constexpr int kSets = kTileSets;         // (stage, class, o in {1, 2}) factor tables
-
-// The influence rows of the two off-diagonal points.  For M = 2 and the pair
-// o = 1 (s_0, s_1), D = s_0 - s_1 and a lag of coefficient eta,
-//   F(1, p) = e^{-i phi} { e^{-i theta}, e^{-g}, e^{g}, e^{i theta} },   p = 0 .. 3,
-// phi = D Im(eta) (s_0 + s_1), theta = D^2 Im(eta), g = D^2 Re(eta), and
-// F(2, p) the conjugate with p = 1, 2 swapped.  With the phase e^{-i phi} moved
-// into the factor tables a row takes four real coefficients:
-//   sum_p = cos(theta) (x0 + x3) -+ i sin(theta) (x0 - x3) + e^{-+g} x1 + e^{+-g} x2,
-// 8 real multiply-adds instead of 16, and x0 + x3 serves the diagonal rows too.
-//
-// Coefficients in the compute precision, read by scalar loads: cos, sin,
-// e^{-g}, e^{g} of the oldest point (lag L; interior, final class) and of the
-// group digit at lag L-1 (stages 0 and 2, "pair 0"); for the group digit e at
-// lag 1, with K (stages 1 and 3, "pair 1"), per stage and e the complex factors
-// of o = 1, 2 (interior), then the final class; then per stage and e K[0][e],
-// K[3][e], in FP64 in every tier (from the kTileCoefK-th double).  The stages
-// differ in K for a driven system only.
-constexpr int kTcOld = 0, kTcOldf = 4, kTcE = 8, kTcEf = 12, kTcLag1 = 16;
-__device__ __forceinline__ constexpr int tc_lag1(int stage) { return kTcLag1 + 32 * (stage >> 1); }
-__device__ __forceinline__ constexpr int tc_k(int stage) { return kTileCoefK + 16 * stage; }
-
-__device__ __forceinline__ constexpr int mirror_d(int d) { return d == 1 ? 2 : d == 2 ? 1 : d; }
 
 // Bits of x -> base-4 digits 3 or 0.
 __device__ __forceinline__ int diagonal_digits_t(unsigned x) {
@@ -97,30 +75,20 @@ __device__ __forceinline__ int tile_hi(int idx, int k, bool mirror, bool *self) 
 // ------------------------------------------------------------------ tables
 // set q = (s * 2 + cls) * 2 + (o - 1): t_w[q][w0 + 4 w1], t_u[q][u0 + 4 u1],
 // t_mid[q][v], t_top[q][v], all FP64; coef in the compute precision.
-__device__ int tile_tab(const BankLayout &B, int lag, int cls) {
-    if (lag == 1) return cls ? B.k_fin1() : B.k_lag1();
-    return cls ? B.fin(lag) : B.lag(lag);
-}
 template <typename T>
 __global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs a) {
     const BankLayout B{a.L};
     const int L = a.L;
     const int n_mid = 1 << (2 * a.d_mid), n_top = 1 << (2 * a.d_top);
-    // F(mirror(o), mirror(p)) = conj(F(o, p)) bit for bit (the bank's K has it
-    // to rounding), so that an entry and its mirror come out exactly conjugate
-    // and a pass may take either: its results do not depend on which it read
-    auto tab = [&](int t, int row, int col) {
-        const int k = row * 4 + col, km = mirror_d(row) * 4 + mirror_d(col);
-        double2 v = a.bank[(size_t)t * 16 + (km < k ? km : k)];
-        if (km < k) v.y = -v.y;
-        if (km == k) v.y = 0.0;
-        return v;
-    };
-    const long long total = (long long)kSets * (32 + n_mid + n_top) + kTileCoefCount;
+    // exactly conjugate under the mirror: a pass may read an entry or its mirror,
+    // and its results do not depend on which it read
+    auto tab = [&](int t, int row, int col) { return tab4(a.bank, t, row, col); };
+    const long long n_tab = a.coef_only ? 0 : (long long)kSets * (32 + n_mid + n_top);
+    const long long total = n_tab + kTileCoefCount;
     for (long long idx = (long long)blockIdx.x * kBlock + threadIdx.x; idx < total;
          idx += (long long)gridDim.x * kBlock) {
-        if (idx >= (long long)kSets * (32 + n_mid + n_top)) {
-            const int k = (int)(idx - (long long)kSets * (32 + n_mid + n_top));
+        if (idx >= n_tab) {
+            const int k = (int)(idx - n_tab);
             double v;
             if (k < kTcLag1) {
                 const double2 eta = a.eta[1 + (k / 4 % 2 ? 2 * L : 0) + (k < kTcE ? L : L - 1)];
@@ -161,13 +129,7 @@ __global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs 
         const int s = q / 4, cls = q / 2 % 2, o = 1 + q % 2;
         double2 p = make_double2(1.0, 0.0);
         if (j0 == 0) {
-            // t_w also carries the self factor and the phases e^{-+i phi} of the
-            // oldest point and (pair 0) of the group digit
-            const double ph = (a.s[0] - a.s[1]) * (a.s[0] + a.s[1]);
-            const double2 *eta = a.eta + 1 + (cls ? 2 * L : 0);
-            double sn, cs;
-            sincos(ph * (eta[L].y + (s % 2 == 0 ? eta[L - 1].y : 0.0)), &sn, &cs);
-            p = cmul(tab(cls ? B.self_end() : B.self_int(), o, 0), make_double2(cs, o == 1 ? -sn : sn));
+            p = prefix4(a.bank, a.eta, a.s, L, o, cls, s % 2);       // t_w also carries these
         }
         for (int j = 0; j < nd; ++j, v >>= 2) {
             // the lag from step n+s: outer digit j0 + j; for t_u the two points
@@ -209,13 +171,7 @@ __global__ void __launch_bounds__(kBlock) tile_drive_kernel(const TileDriveArgs 
         if (km == k) v.y = 0.0;
         return v;
     };
-    auto tab = [&](int t, int o, int p) {
-        const int k = o * 4 + p, km = mirror_d(o) * 4 + mirror_d(p);
-        double2 v = a.bank[(size_t)t * 16 + (km < k ? km : k)];
-        if (km < k) v.y = -v.y;
-        if (km == k) v.y = 0.0;
-        return v;
-    };
+    auto tab = [&](int t, int o, int p) { return tab4(a.bank, t, o, p); };
     for (int idx = blockIdx.x * kBlock + threadIdx.x; idx < total; idx += gridDim.x * kBlock) {
         if (idx < 64) {
             const int st = 1 + idx / 32 * 2, k = idx % 32, e = k / 8, cls = k / 4 % 2, o = 1 + k / 2 % 2;
@@ -265,21 +221,6 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
-// 8 bytes per slot: a complex64 value, or one component of a complex128 value
-// at a time (a whole one would take twice the LDS, half the waves).
-template <typename C> struct XSlot;
-template <> struct XSlot<float2> {
-    static constexpr int kParts = 1;
-    using type = float2;
-    static __device__ __forceinline__ float2 get(float2 v, int) { return v; }
-    static __device__ __forceinline__ void set(float2 &v, float2 s, int) { v = s; }
-};
-template <> struct XSlot<double2> {
-    static constexpr int kParts = 2;
-    using type = double;
-    static __device__ __forceinline__ double get(double2 v, int part) { return part ? v.y : v.x; }
-    static __device__ __forceinline__ void set(double2 &v, double s, int part) { (part ? v.y : v.x) = s; }
-};
 // The slot of register r in layouts A and B.
 __device__ __forceinline__ int slot_a(const XLane &x, int r) { return (x.wr ^ ((r & 1) << 3)) + 256 * r; }
 __device__ __forceinline__ int slot_b(const XLane &x, int r) { return x.rd ^ r; }
@@ -341,160 +282,6 @@ __global__ void __launch_bounds__(kBlock) tile_rho_kernel(const TileRho r) {
 }
 
 // --------------------------------------------------------------------- pass
-// D += E_q B over the wave, E_q the 4x4 matrix with ones in row q (4x4x4
-// FP64 MFMA, four blocks): adds the wave's values v, reduced 4 : 1, to the 16
-// lanes 16 q .. 16 q + 15 of acc.  Four such calls keep four running sums in
-// one register pair, where per-lane sums would take four pairs for every
-// stage (and shuffles of each at the end of every tile).
-__device__ __forceinline__ double row_add(double acc, double v, int q, int lane) {
-    return __builtin_amdgcn_mfma_f64_4x4x4f64((lane & 3) == q ? 1.0 : 0.0, v, acc, 0, 0, 0);
-}
-
-// The coefficient pointer through an opaque move: loads through it stay at
-// their use instead of being kept live in scalar registers.
-template <typename T>
-__device__ __forceinline__ const T *fresh_t(const T *p) {
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
-// Wave-uniform read of one coefficient (see coef_ld).
-template <typename T>
-__device__ __forceinline__ T coef_s(const T *p, int k) {
-    return ((const __attribute__((address_space(4))) T *)p)[k];
-}
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
-
-// The contraction of the oldest point for o = 1 (SIGN +) or o = 2 (SIGN -):
-// p = x0 + x3, q = x0 - x3, coefficients at k.  The terms of x1 and x2 are
-// taken in mirrored orders for the two points, so that the mirrored group
-// gives the exact conjugate.
-template <int SIGN, typename T, typename C>
-__device__ __forceinline__ C row12(const T *co, int k, C p, C q, C x1, C x2) {
-    const T c = coef_s(co, k), sn = SIGN > 0 ? coef_s(co, k + 1) : -coef_s(co, k + 1);
-    const T g1 = coef_s(co, k + 2), g2 = coef_s(co, k + 3);
-    const C a = SIGN > 0 ? x1 : x2, b = SIGN > 0 ? x2 : x1;
-    C r;
-    r.x = fma_t(g2, b.x, fma_t(g1, a.x, fma_t(sn, q.y, c * p.x)));
-    r.y = fma_t(g2, b.y, fma_t(g1, a.y, fma_t(-sn, q.x, c * p.y)));
-    return r;
-}
-
-// One step (stage) on the 16 values of a lane: digit PAIR of the register index
-// (stride 4^PAIR) is contracted, the groups are the other digit e.  c1, c2: the
-// thread's factors of the new points 1 and 2 (interior); prev: the previous
-// point when it is not e (PAIR 0), wave-uniform.  With RHO: tf1, tf2 the
-// final-point sums of the lane without the thread's factor, rd0 and rd3 the
-// terms of the diagonal points (REAL: their real parts only).
-template <typename T, bool RHO, bool REAL, int STAGE, typename CI>
-__device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::type (&w)[16],
-                                           const T *coef, typename Cx<T>::type c1,
-                                           typename Cx<T>::type c2, int prev, typename Cx<T>::type &tf1,
-                                           typename Cx<T>::type &tf2, double2 &rd0, double2 &rd3) {
-    using C = typename Cx<T>::type;
-    constexpr int PAIR = STAGE % 2;
-    constexpr int SI = PAIR == 0 ? 1 : 4, SE = PAIR == 0 ? 4 : 1;
-    const T *co = fresh_t(coef);
-    double2 all = make_double2(0.0, 0.0);
-    if (RHO) {
-        tf1 = C{};
-        tf2 = C{};
-        rd0 = rd3 = make_double2(0.0, 0.0);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        __builtin_amdgcn_sched_barrier(0);      // a group at a time: fewer live registers
-        const T *ce = PAIR == 0 ? co : fresh_t(coef);
-        const C x0 = conv<C>(in[SE * e]), x1 = conv<C>(in[SE * e + SI]);
-        const C x2 = conv<C>(in[SE * e + 2 * SI]), x3 = conv<C>(in[SE * e + 3 * SI]);
-        const C p = cadd(x0, x3);
-        C q;
-        q.x = x0.x - x3.x;
-        q.y = x0.y - x3.y;
-        // the diagonal points 0 and 3 carry no influence: K times the plain sum
-        // (K[0][e], K[3][e] are real for e = 0, 3)
-        TraceSum<C> sd;
-        if constexpr (sizeof(T) == 4) {
-            TraceSum<C> s2;
-            sd.init(x0);
-            sd.add(x3);
-            s2.init(x1);
-            s2.add(x2);
-            sd.s = cadd(sd.s, s2.s);
-        } else {
-            sd.init(cadd(p, cadd(x1, x2)));
-        }
-        const double *kd = (const double *)ce + tc_k(STAGE) + 4 * (PAIR == 0 ? prev : e);
-        const double2 d0 = coef_ld(kd, 0), d3 = coef_ld(kd, 1), ds = sd.s;
-        if (PAIR == 1 && (e == 0 || e == 3)) {
-            w[SE * e] = from_d2<C>(make_double2(d0.x * ds.x, d0.x * ds.y));
-            w[SE * e + 3 * SI] = from_d2<C>(make_double2(d3.x * ds.x, d3.x * ds.y));
-        } else {
-            w[SE * e] = from_d2<C>(cmul(d0, ds));
-            w[SE * e + 3 * SI] = from_d2<C>(cmul(d3, ds));
-        }
-        if (RHO) {
-            if (PAIR == 0) {
-                all = cadd(all, ds);
-            } else if (REAL) {
-                rd0.x = fma(d0.x, ds.x, rd0.x);
-                rd3.x = fma(d3.x, ds.x, rd3.x);
-                if (e == 1 || e == 2) {
-                    rd0.x = fma(-d0.y, ds.y, rd0.x);
-                    rd3.x = fma(-d3.y, ds.y, rd3.x);
-                }
-            } else {
-                cmac(rd0, d0, ds);
-                cmac(rd3, d3, ds);
-            }
-        }
-        // e's own factor: for pair 0 the four-coefficient form of the row
-        auto factor_e = [&](int o, bool fin) {
-            C f;
-            if (PAIR == 0) {
-                const int k = fin ? kTcEf : kTcE;
-                f.x = coef_s(ce, e == 1 || e == 2 ? k + ((e == 1) == (o == 1) ? 2 : 3) : k);
-                f.y = (e == 0) == (o == 1) ? -coef_s(ce, k + 1) : coef_s(ce, k + 1);
-            } else {
-                const int k = tc_lag1(STAGE) + 8 * e + 2 * (o - 1) + (fin ? 4 : 0);
-                f.x = coef_s(ce, k);
-                f.y = coef_s(ce, k + 1);
-            }
-            return f;
-        };
-        constexpr bool kRealE = PAIR == 0;            // factors of e = 1, 2 are real
-        auto with_e = [&](C c, int o) {
-            const C f = factor_e(o, false);
-            if (!(kRealE && (e == 1 || e == 2))) return cmul(c, f);
-            c.x *= f.x;
-            c.y *= f.x;
-            return c;
-        };
-        auto add_e = [&](C &sum, C v, int o) {        // sum += factor * v (final class)
-            const C f = factor_e(o, true);
-            if (kRealE && (e == 1 || e == 2)) {
-                sum.x = fma_t(v.x, f.x, sum.x);
-                sum.y = fma_t(v.y, f.x, sum.y);
-            } else {
-                cmac(sum, v, f);
-            }
-        };
-        const C s1 = row12<1>(co, kTcOld, p, q, x1, x2), s2 = row12<-1>(co, kTcOld, p, q, x1, x2);
-        w[SE * e + SI] = cmul(with_e(c1, 1), s1);
-        w[SE * e + 2 * SI] = cmul(with_e(c2, 2), s2);
-        if (RHO) {
-            add_e(tf1, row12<1>(co, kTcOldf, p, q, x1, x2), 1);
-            add_e(tf2, row12<-1>(co, kTcOldf, p, q, x1, x2), 2);
-        }
-    }
-    if (RHO && PAIR == 0) {
-        const double *kd = (const double *)co + tc_k(STAGE) + 4 * prev;
-        rd0 = cmul(coef_ld(kd, 0), all);
-        rd3 = cmul(coef_ld(kd, 1), all);
-    }
-}
-
 // Stages s0 .. s1-1 of the group of four steps n .. n+3 (n > L, n - L - 1 a
 // multiple of 4).  The stage range only says which of the steps run and where
 // the entries are read and written: every entry and every rho sum is formed
@@ -670,7 +457,9 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         fix_tile(hi, self, lane);
         if (s0 <= 0) {
             const int prev = hi >> (2 * (k_hi - 1));                   // point n-1
-            tile_stage<T, RHO, MIRROR, 0>(x, w, coef, factor(0, wl, ua), factor(1, wl, ua), prev, tf1, tf2, rd0,
+            double2 k0, k3;
+            coef_k(coef, 0, prev, k0, k3);
+            tile_stage<T, RHO, MIRROR, 0>(x, w, coef, factor(0, wl, ua), factor(1, wl, ua), k0, k3, tf1, tf2, rd0,
                                           rd3);
             if (RHO) add_rho(0, wl, ua, tf1, tf2, rd0, rd3);
             round_to_storage(a.round_each);
@@ -683,7 +472,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             if (AHEAD) read_tile(hi_next, self_next, lane);
         }
         if (s0 <= 1 && s1 > 1) {
-            tile_stage<T, RHO, MIRROR, 1>(w, w, coef, factor(4, wl, ua), factor(5, wl, ua), 0, tf1, tf2, rd0, rd3);
+            tile_stage<T, RHO, MIRROR, 1>(w, w, coef, factor(4, wl, ua), factor(5, wl, ua), double2{}, double2{}, tf1, tf2, rd0, rd3);
             if (RHO) add_rho(RHO ? 1 : 0, wl, ua, tf1, tf2, rd0, rd3);
             round_to_storage(true);
         }
@@ -714,12 +503,14 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             if (lane >= 32) s_w[wave][lane] = tile_f;
         });
         if (s0 <= 2 && s1 > 2) {
-            tile_stage<T, RHO, MIRROR, 2>(w, w, coef, factor(8, wb, ub), factor(9, wb, ub), wave, tf1, tf2, rd0, rd3);
+            double2 k0, k3;
+            coef_k(coef, 2, wave, k0, k3);
+            tile_stage<T, RHO, MIRROR, 2>(w, w, coef, factor(8, wb, ub), factor(9, wb, ub), k0, k3, tf1, tf2, rd0, rd3);
             if (RHO) add_rho(RHO ? 2 : 0, wb, ub, tf1, tf2, rd0, rd3);
             round_to_storage(a.round_each);
         }
         if (s1 > 3) {
-            tile_stage<T, RHO, MIRROR, 3>(w, w, coef, factor(12, wb, ub), factor(13, wb, ub), 0, tf1, tf2, rd0, rd3);
+            tile_stage<T, RHO, MIRROR, 3>(w, w, coef, factor(12, wb, ub), factor(13, wb, ub), double2{}, double2{}, tf1, tf2, rd0, rd3);
             if (RHO) add_rho(RHO ? 3 : 0, wb, ub, tf1, tf2, rd0, rd3);
         }
         const long long m = (long long)hi * 16 + wb;        // layout B's m
@@ -821,7 +612,7 @@ hipError_t launch_tile_rho(const TileRho &r, hipStream_t st) {
 
 hipError_t launch_tile_tables(int prec, const TilePlanArgs &a, hipStream_t st) {
     const long long total =
-        (long long)kSets * (32 + (1LL << (2 * a.d_mid)) + (1LL << (2 * a.d_top))) + kTileCoefCount;
+        (a.coef_only ? 0 : (long long)kSets * (32 + (1LL << (2 * a.d_mid)) + (1LL << (2 * a.d_top)))) + kTileCoefCount;
     const dim3 g((unsigned)std::min<long long>(1024, (total + kBlock - 1) / kBlock)), b(kBlock);
     if (prec == kPrecC64) hipLaunchKernelGGL(tile_tables_kernel<float>, g, b, 0, st, a);
     else hipLaunchKernelGGL(tile_tables_kernel<double>, g, b, 0, st, a);

@@ -209,3 +209,52 @@ def test_batch_refusals():
     finally:
         for x in (a, b, c, d, big):
             x.destroy()
+
+
+@pytest.mark.parametrize("dtype,tol", [("c128", None), ("c64", 1e-5), ("c64f64", 1e-6)])
+@pytest.mark.parametrize("hermitian", [True, False])
+@pytest.mark.parametrize("L", [5, 6, 7])
+def test_window_in_registers_against_oracle_splits_and_batch(L, hermitian, dtype, tol):
+    # the full-window steps past n = L keep the tensor in a block's registers,
+    # two steps per exchange: calls that end inside a pair, runs without rho, a
+    # batch of mixed memory lengths and step counts
+    rho0 = np.array([[0.7, 0.2 - 0.1j], [0.2 + 0.1j if hermitian else 0.4j, 0.3]])
+    w = W.spin_boson_l7().with_(L=L, H=W.random_hermitian(np.random.default_rng(L), 2), xi=0.3, rho0=rho0)
+    n = L + 13
+    print(f"case L={L} hermitian={hermitian} {dtype}", flush=True)
+
+    def run(parts, **kw):
+        with Q.create(Q.params_from(w, dtype=dtype)) as c:
+            assert c.persistent() in (1, 2)
+            rho = [c.propagate(k, **kw) for k in parts]
+            return np.concatenate(rho), c.read_tensor(0, c.tensor_size())
+    one, tens = run([n])
+    o = orun.oracle_run(w, n)[1:]
+    if tol is None:
+        assert np.abs(one - o).max() <= 1e-12 * np.abs(o).max()
+    else:
+        assert np.abs(one - o).max() <= tol
+    for parts in ([L, 1, 3, 2, 7], [L + 1, 12], [L - 2, 15], [1] * n):
+        rho, t = run(parts)
+        assert np.array_equal(rho, one) and np.array_equal(t, tens), parts
+    last, t = run([n], sel=[L + 4, n])
+    assert np.array_equal(last, one[[L + 3, n - 1]]) and np.array_equal(t, tens)
+    with Q.create(Q.params_from(w, dtype=dtype)) as c:          # the step-by-step kernels, to rounding
+        c.set_fused_steps(1)
+        assert np.abs(c.propagate(n) - one).max() <= {"c128": 1e-13, "c64": 1e-5, "c64f64": 1e-6}[dtype]
+    import torch
+    ws = [w.with_(L=k) for k in (4, L, 7, L)]
+    steps = [n, n, 20, L + 2]
+    ctxs = [Q.create(Q.params_from(x, dtype=dtype)) for x in ws]
+    try:
+        outs = [torch.zeros((k, 4, 2), dtype=torch.float64, device="cuda:0") for k in steps]
+        torch.cuda.synchronize()
+        Q.propagate_batch(ctxs, steps, [1] * 4, [b.data_ptr() for b in outs])
+        torch.cuda.synchronize()
+        for x, k, b in zip(ws, steps, outs):
+            with Q.create(Q.params_from(x, dtype=dtype)) as c:
+                want = c.propagate(k)
+            assert np.array_equal(b.cpu().numpy().view(np.complex128).reshape(k, 2, 2), want), (x.L, k)
+    finally:
+        for c in ctxs:
+            c.destroy()
