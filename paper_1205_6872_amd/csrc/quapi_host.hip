@@ -322,6 +322,7 @@ struct Layout {
     // filtered contexts: keys and values of the two tensors, flags, segment
     // starts, scan partials, counters, rho partials, factor-level tables
     size_t off_fkeys[2], off_fvals[2], off_fmask, off_fbofs, off_fctr, off_fpart, off_fplan;
+    size_t up_bytes;                 // bytes of the host's inputs, from off_s on
     size_t fplan_entries;            // entries of one factor-level table set
     size_t total;
     int n_panels, n_tables, partial_blocks;
@@ -457,10 +458,11 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_gpart = take((size_t)(2 * L + 3) * quad_parts(n_panels) * 2 * 16);
     l.off_eta = take((size_t)(4 * L + 2) * 16);
     l.off_U = take((size_t)M * M * 16);
+    l.off_Ut = take((size_t)std::max(p.n_H, 0) * M * M * 16);
+    // what the host uploads, in one piece: up_bytes from off_s on
     l.off_s = take((size_t)M * 8);
     l.off_H = take((size_t)M * M * 16);
     l.off_Ht = take((size_t)std::max(p.n_H, 0) * M * M * 16);
-    l.off_Ut = take((size_t)std::max(p.n_H, 0) * M * M * 16);
     l.off_rho0 = take((size_t)N * 16);
     l.off_pa = take((size_t)n_panels * 8);
     l.off_ph = take((size_t)n_panels * 8);
@@ -470,6 +472,13 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_tJ = take((size_t)nt * 8);
     l.off_glx = take(kGL * 8);
     l.off_glw = take(kGL * 8);
+    l.off_blk3 = take(triple ? (size_t)(l.n_canon3 + l.n_diag3) * sizeof(int) : 0);
+    l.off_low3 = take(triple ? (size_t)l.n_low3 * sizeof(int) : 0);
+    l.off_blk2 = take((size_t)(l.n_canon2 + l.n_diag2) * sizeof(int));
+    l.off_low2 = take((size_t)l.n_low2 * sizeof(int));
+    l.off_blk1 = take((size_t)(l.n_canon1 + l.n_diag1) * sizeof(int));
+    l.off_low1 = take((size_t)l.n_low1 * sizeof(int));
+    l.up_bytes = off - l.off_s;
     l.off_partials = take((size_t)kSlots * l.partial_blocks * N * 16);
     l.off_stage = take((size_t)kRhoStage * N * 16);
     l.off_pairs = take((size_t)kRhoSlices * N * 2 * 16);
@@ -486,12 +495,6 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     const DigitSplit &s3 = l.split3;
     l.off_plan3 = take(triple ? (size_t)6 * N * (s3.R + s3.Q + s3.grid) * 16 : 0);
     l.off_coef3 = take(triple ? (size_t)kC3Count * 16 : 0);
-    l.off_blk3 = take(triple ? (size_t)(l.n_canon3 + l.n_diag3) * sizeof(int) : 0);
-    l.off_low3 = take(triple ? (size_t)l.n_low3 * sizeof(int) : 0);
-    l.off_blk2 = take((size_t)(l.n_canon2 + l.n_diag2) * sizeof(int));
-    l.off_low2 = take((size_t)l.n_low2 * sizeof(int));
-    l.off_blk1 = take((size_t)(l.n_canon1 + l.n_diag1) * sizeof(int));
-    l.off_low1 = take((size_t)l.n_low1 * sizeof(int));
     const bool tile = !filtered && tile_ok(N, L);
     l.off_ttab = take(tile ? tile_table_entries(L) * 16 : 0);
     const bool reg = !filtered && N == 4 && L >= kRegMinL && L <= kRegMaxL;
@@ -539,6 +542,7 @@ struct quapi_ctx {
     // the small mirror-mode launches of a three-step group (modes 2, 3) run
     // on a third stream, concurrently with mode 1, joined before the next work
     hipStream_t aux = nullptr;
+    bool side_ready = false;      // both and their events exist (ensure_side)
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     bool fin_pending[kSlots] = {};
     int next_slot = 0;
@@ -555,7 +559,6 @@ struct quapi_ctx {
     int n_H = 0;                  // driven: per-interval Hamiltonians on the device
     const double2 *Ht_d = nullptr;
     double2 *Ut_d = nullptr;      // driven: U_k = exp(-i H_t[k] dt), computed at create
-    std::vector<double> Ht_h;
     TablesArgs drive_ta{};        // the setup tables call, reused per step with k_only
     float2 *bank_f = nullptr;     // the bank rounded to complex64 (FP32 arithmetic only)
     RhoSink *sink = nullptr;
@@ -579,17 +582,11 @@ struct quapi_ctx {
     int mirror = 0;               // 0 off, 1 where it pays, 2 at every size (quapi_set_mirror)
     bool half_cur = false;
     int *blk3 = nullptr;          // high-digit values: n_canon3 below their mirror, then n_diag3 equal
-    std::vector<int> blk3_h;
     int *low3 = nullptr;          // mode 2's list of the items qm * R + r below their mirror
-    std::vector<int> low3_h;
     int *blk2 = nullptr;          // the same for the two-step kernel (n_canon2, n_diag2)
-    std::vector<int> blk2_h;
     int *low2 = nullptr;          // its list of the items below their mirror
-    std::vector<int> low2_h;
     int *blk1 = nullptr;          // the same for the single step (n_canon1, n_diag1)
-    std::vector<int> blk1_h;
     int *low1 = nullptr;          // N = 9: its list of the items below their mirror
-    std::vector<int> low1_h;
     double2 *plan3 = nullptr;
     void *coef3 = nullptr;
     // The tile kernel: its tables, coefficients and two sets of rho rows; the
@@ -616,14 +613,13 @@ struct quapi_ctx {
     size_t fplan_entries = 0;
     int fplan_for = -1;           // the step set fplan holds: 0 the full window, n growth step n
     std::vector<double> rho0_h;
-    // host copies of uploaded inputs (kept alive until the uploads complete)
-    std::vector<double> s_h, H_h, pa_h, ph_h, tw_h, tJ_h, glx_h, glw_h;
+    std::vector<double> s_h;
+    std::vector<char> up_h;       // the uploaded inputs (kept alive until the upload completes)
     // N = 16: the new points grouped by the classes of their oldest-point
     // rows for the MFMA step (Cls16), when such a grouping exists
     bool cls_ok = false;
     unsigned long long cls_out = 0;
     unsigned cls_rep = 0, cls_selb = 0;
-    std::vector<int> pseg_h;
     std::string err;
     std::atomic<int> busy{0};
     // timing
@@ -913,6 +909,23 @@ quapi_status wait_slot(quapi_ctx *c, int s) {
         HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_fin[s], 0));
         c->fin_pending[s] = false;
     }
+    return QUAPI_OK;
+}
+
+// The side and aux streams and their events: at create, except for contexts on
+// the persistent path, which need them only once a setter takes them off it.
+quapi_status ensure_side(quapi_ctx *c) {
+    if (c->one_stream || c->side_ready) return QUAPI_OK;
+    auto event = [](hipEvent_t *e) { return *e ? hipSuccess : hipEventCreateWithFlags(e, hipEventDisableTiming); };
+    if (!c->side) HIP_TRY(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+    if (!c->aux) HIP_TRY(c, hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking));
+    HIP_TRY(c, event(&c->ev_fork));
+    HIP_TRY(c, event(&c->ev_join));
+    for (int k = 0; k < kSlots; ++k) {
+        HIP_TRY(c, event(&c->ev_step[k]));
+        HIP_TRY(c, event(&c->ev_fin[k]));
+    }
+    c->side_ready = true;
     return QUAPI_OK;
 }
 
@@ -2090,18 +2103,6 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
         }
         c->own_stream = true;
     }
-    bool side_ok = one_stream ||
-                   (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) == hipSuccess &&
-                    hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) == hipSuccess &&
-                    hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess &&
-                    hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) == hipSuccess);
-    for (int k = 0; k < kSlots && side_ok && !one_stream; ++k)
-        side_ok = hipEventCreateWithFlags(&c->ev_step[k], hipEventDisableTiming) == hipSuccess &&
-                  hipEventCreateWithFlags(&c->ev_fin[k], hipEventDisableTiming) == hipSuccess;
-    if (!side_ok) {
-        release(c);
-        return fail(nullptr, QUAPI_ERR_DEVICE, "side stream / event creation failed");
-    }
     if (workspace) {
         c->ws = (char *)workspace;
     } else {
@@ -2175,9 +2176,8 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
     // L = 1: the oldest-point tables carry K, whose rows are not shared
     if (N == 16 && L >= 2 && !filtered && !cls16_disabled())
         c->cls_ok = pack_classes16(c->s_h, &c->cls_out, &c->cls_rep, &c->cls_selb);
-    c->H_h.assign(p->H, p->H + 2 * M * M);
-    if (p->n_H > 0) c->Ht_h.assign(p->H_t, p->H_t + (size_t)2 * M * M * p->n_H);
     c->rho0_h.assign(p->rho0, p->rho0 + 2 * N);
+    std::vector<int> blk3, low3, blk2, low2, blk1, low1;
     {
         // the path sum maps to its conjugate under the mirror only if rho0 does
         bool herm = true;
@@ -2188,25 +2188,25 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
         if (triple_ok(N, L) && !filtered) {
             for (int pass = 0; pass < 2; ++pass)
                 for (int h = 0; h < lay.split3.grid; ++h)
-                    if (pass == 0 ? h < mirror4(h) : h == mirror4(h)) c->blk3_h.push_back(h);
+                    if (pass == 0 ? h < mirror4(h) : h == mirror4(h)) blk3.push_back(h);
             for (int low = 0; low < lay.split3.R * lay.split3.Q; ++low)
-                if (mirror4(low) > low) c->low3_h.push_back(low);
+                if (mirror4(low) > low) low3.push_back(low);
             c->mirror_ok = herm;
         }
         if (fused_ok(N, L) && !filtered) {
             for (int pass = 0; pass < 2; ++pass)
                 for (int h = 0; h < lay.split2.grid; ++h)
-                    if (pass == 0 ? h < mirror4(h) : h == mirror4(h)) c->blk2_h.push_back(h);
+                    if (pass == 0 ? h < mirror4(h) : h == mirror4(h)) blk2.push_back(h);
             for (int low = 0; low < lay.split2.R * lay.split2.Q; ++low)
-                if (mirror4(low) > low) c->low2_h.push_back(low);
+                if (mirror4(low) > low) low2.push_back(low);
         }
         if (single_mirror_ok(N, L, lay.main_split) && !filtered) {
             for (int pass = 0; pass < 2; ++pass)
                 for (int h = 0; h < lay.main_split.grid; ++h)
-                    if (pass == 0 ? h < mirror_n(N, h) : h == mirror_n(N, h)) c->blk1_h.push_back(h);
+                    if (pass == 0 ? h < mirror_n(N, h) : h == mirror_n(N, h)) blk1.push_back(h);
             if (N == 9)
                 for (int low = 0; low < lay.main_split.R * lay.main_split.Q; ++low)
-                    if (mirror9(low) > low) c->low1_h.push_back(low);
+                    if (mirror9(low) > low) low1.push_back(low);
             c->mirror_ok = herm;
         }
         c->mirror = c->mirror_ok ? 1 : 0;
@@ -2228,42 +2228,51 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
                      small_reg_lds_bytes(L, c->prec) <= (size_t)lds_max;
         }
     }
-    c->pa_h = std::move(pa);
-    c->ph_h = std::move(ph);
-    c->pseg_h = std::move(pseg);
-    if (p->bath.kind == QUAPI_BATH_TABLE) {
-        c->tw_h.assign(p->bath.omega, p->bath.omega + p->bath.n_tab);
-        c->tJ_h.assign(p->bath.J, p->bath.J + p->bath.n_tab);
-    } else {
-        c->tw_h.assign(1, 0.0);
-        c->tJ_h.assign(1, 0.0);
+    // a persistent-path context needs the two events of a batch, any other one
+    // its side streams too
+    const bool side_ok =
+        c->small != 0 && c->n_H == 0 && !one_stream
+            ? hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess &&
+                  hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) == hipSuccess
+            : ensure_side(c) == QUAPI_OK;
+    if (!side_ok) {
+        release(c);
+        return fail(nullptr, QUAPI_ERR_DEVICE, "side stream / event creation failed");
     }
-    gauss_legendre(kGL, c->glx_h, c->glw_h);
-
-    auto up = [&](size_t off, const void *src, size_t bytes) {
-        return hipMemcpyAsync(w + off, src, bytes, hipMemcpyHostToDevice, c->stream);
+    // one upload (a copy per input took 16 of them, 3 us of the GPU and about 10
+    // of the host each)
+    std::vector<char> &up = c->up_h;
+    up.resize(lay.up_bytes);
+    auto put = [&](size_t off, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(up.data() + (off - lay.off_s), src, bytes);
     };
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = up(lay.off_s, c->s_h.data(), (size_t)M * 8);
-    if (e == hipSuccess) e = up(lay.off_H, c->H_h.data(), (size_t)M * M * 16);
-    if (e == hipSuccess && c->n_H > 0) e = up(lay.off_Ht, c->Ht_h.data(), c->Ht_h.size() * 8);
-    if (e == hipSuccess) e = up(lay.off_rho0, c->rho0_h.data(), (size_t)N * 16);
-    if (e == hipSuccess && !c->blk3_h.empty()) e = up(lay.off_blk3, c->blk3_h.data(), c->blk3_h.size() * sizeof(int));
-    if (e == hipSuccess && (int)c->low3_h.size() != lay.n_low3) e = hipErrorInvalidValue;
-    if (e == hipSuccess && !c->low3_h.empty()) e = up(lay.off_low3, c->low3_h.data(), c->low3_h.size() * sizeof(int));
-    if (e == hipSuccess && !c->blk2_h.empty()) e = up(lay.off_blk2, c->blk2_h.data(), c->blk2_h.size() * sizeof(int));
-    if (e == hipSuccess && (int)c->low2_h.size() != lay.n_low2) e = hipErrorInvalidValue;
-    if (e == hipSuccess && !c->low2_h.empty()) e = up(lay.off_low2, c->low2_h.data(), c->low2_h.size() * sizeof(int));
-    if (e == hipSuccess && !c->blk1_h.empty()) e = up(lay.off_blk1, c->blk1_h.data(), c->blk1_h.size() * sizeof(int));
-    if (e == hipSuccess && (int)c->low1_h.size() != lay.n_low1) e = hipErrorInvalidValue;
-    if (e == hipSuccess && !c->low1_h.empty()) e = up(lay.off_low1, c->low1_h.data(), c->low1_h.size() * sizeof(int));
-    if (e == hipSuccess) e = up(lay.off_pa, c->pa_h.data(), c->pa_h.size() * 8);
-    if (e == hipSuccess) e = up(lay.off_ph, c->ph_h.data(), c->ph_h.size() * 8);
-    if (e == hipSuccess) e = up(lay.off_pseg, c->pseg_h.data(), c->pseg_h.size() * 4);
-    if (e == hipSuccess) e = up(lay.off_tw, c->tw_h.data(), c->tw_h.size() * 8);
-    if (e == hipSuccess) e = up(lay.off_tJ, c->tJ_h.data(), c->tJ_h.size() * 8);
-    if (e == hipSuccess) e = up(lay.off_glx, c->glx_h.data(), kGL * 8);
-    if (e == hipSuccess) e = up(lay.off_glw, c->glw_h.data(), kGL * 8);
+    put(lay.off_s, c->s_h.data(), (size_t)M * 8);
+    put(lay.off_H, p->H, (size_t)M * M * 16);
+    if (c->n_H > 0) put(lay.off_Ht, p->H_t, (size_t)c->n_H * M * M * 16);
+    put(lay.off_rho0, c->rho0_h.data(), (size_t)N * 16);
+    put(lay.off_pa, pa.data(), pa.size() * 8);
+    put(lay.off_ph, ph.data(), ph.size() * 8);
+    put(lay.off_pseg, pseg.data(), pseg.size() * 4);
+    if (p->bath.kind == QUAPI_BATH_TABLE) {
+        put(lay.off_tw, p->bath.omega, (size_t)p->bath.n_tab * 8);
+        put(lay.off_tJ, p->bath.J, (size_t)p->bath.n_tab * 8);
+    }
+    std::vector<double> glx, glw;
+    gauss_legendre(kGL, glx, glw);
+    put(lay.off_glx, glx.data(), kGL * 8);
+    put(lay.off_glw, glw.data(), kGL * 8);
+    const bool lists_ok = (int)low3.size() == lay.n_low3 && (int)low2.size() == lay.n_low2 &&
+                          (int)low1.size() == lay.n_low1;
+    if (lists_ok) {
+        put(lay.off_blk3, blk3.data(), blk3.size() * sizeof(int));
+        put(lay.off_low3, low3.data(), low3.size() * sizeof(int));
+        put(lay.off_blk2, blk2.data(), blk2.size() * sizeof(int));
+        put(lay.off_low2, low2.data(), low2.size() * sizeof(int));
+        put(lay.off_blk1, blk1.data(), blk1.size() * sizeof(int));
+        put(lay.off_low1, low1.data(), low1.size() * sizeof(int));
+    }
+    hipError_t e = lists_ok ? hipMemcpyAsync(w + lay.off_s, up.data(), up.size(), hipMemcpyHostToDevice, c->stream)
+                            : hipErrorInvalidValue;
     if (e != hipSuccess) {
         release(c);
         return fail(nullptr, QUAPI_ERR_DEVICE, "input upload failed: %s", hipGetErrorString(e));
@@ -2641,6 +2650,8 @@ quapi_status quapi_set_fused_steps(quapi_ctx *ctx, int steps) {
                     "3: N = 4, L >= 4)", steps, N, L);
     BusyGuard guard(ctx);
     if (!guard.ok) return fail(ctx, QUAPI_ERR_STATE, "context in use by another call");
+    if (pinned)                 // leaves the persistent path
+        if (quapi_status st = ensure_side(ctx); st != QUAPI_OK) return st;
     ctx->fuse = steps;
     ctx->fuse_pinned = pinned;
     return QUAPI_OK;
@@ -2660,6 +2671,8 @@ quapi_status quapi_set_mirror(quapi_ctx *ctx, int enable) {
     BusyGuard guard(ctx);       // the graphs destroyed below must not be replayed meanwhile
     if (!guard.ok) return fail(ctx, QUAPI_ERR_STATE, "context in use by another call");
     if (enable == ctx->mirror) return QUAPI_OK;
+    if (enable == 2)            // leaves the persistent path
+        if (quapi_status st = ensure_side(ctx); st != QUAPI_OK) return st;
     // the captured graphs hold the launches of the old mode
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     for (auto &row : ctx->graph3)
@@ -2767,7 +2780,7 @@ quapi_status quapi_set_timing(quapi_ctx *ctx, int enable) {
 quapi_status quapi_get_timing(quapi_ctx *ctx, quapi_timing *out) {
     if (!ctx || !out) return fail(nullptr, QUAPI_ERR_INVALID, "NULL argument");
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->side));
+    if (ctx->side) HIP_TRY(ctx, hipStreamSynchronize(ctx->side));
     for (auto &r : ctx->recs) {
         float ms = 0.0f;
         if (hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
