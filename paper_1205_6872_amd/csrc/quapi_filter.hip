@@ -101,6 +101,27 @@ __global__ void __launch_bounds__(kFB) filter_plan_kernel(const FilterPlanArgs a
         a.t[2 * idx] = p;
         a.t[2 * idx + 1] = pf;
     }
+    // Which rows o of a level are exactly one, interior and final-point alike
+    // (the diagonal new points, in every level without K): one word per level
+    // after the tables, for the step to leave those factors out.
+    if (blockIdx.x != 0) return;
+    __shared__ unsigned s_ones[8];
+    if (threadIdx.x < 8) s_ones[threadIdx.x] = 0;
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < a.n_lv * N; idx += kFB) {
+        const int l = idx / N, o = idx % N;
+        const int j0 = l == 0 ? 0 : D0 + (l - 1) * D, j1 = l == 0 ? D0 : j0 + D;
+        bool r = true;
+        for (int j = j0; j < a.nd && j < j1; ++j)
+            for (int i = 0; i < N; ++i) {
+                const double2 p = a.bank[(size_t)a.tab[j] * (N * N) + o * N + i];
+                const double2 pf = a.bank[(size_t)a.tabf[j] * (N * N) + o * N + i];
+                r = r && p.x == 1.0 && p.y == 0.0 && pf.x == 1.0 && pf.y == 0.0;
+            }
+        if (r) atomicOr(&s_ones[l], 1u << o);
+    }
+    __syncthreads();
+    if (threadIdx.x < 8) ((unsigned *)(a.t + 2 * total))[threadIdx.x] = s_ones[threadIdx.x];
 }
 
 // ------------------------------------------------------------------- step
@@ -113,22 +134,41 @@ __device__ __forceinline__ unsigned long long seg_of(unsigned long long key, boo
 __device__ __forceinline__ unsigned long long lanes_below(int lane) { return (1ull << lane) - 1ull; }
 
 // The count (COUNT) or write pass of one step; see the top of the file.
-// Dynamic LDS (RHO): each thread's rho sums, [o][thread].
+// Bound by latency: each round is a chain of LDS and L2 reads per segment, so
+// its time follows the waves in flight.  At N <= 4 the registers are held to
+// four waves per SIMD (the complex128 write pass at three: 300 us, at four
+// 242), the candidates of a segment are requested only where the staged keys
+// show them to be its own, and a level's rows of ones (half of the new points)
+// are left out.  M = 2, L = 15, theta = 1e-10, 1.6e7 kept, rho every step, per
+// step: complex128 640 -> 566 us, complex64/FP32 552 -> 477, complex64/FP64
+// 666 -> 533; L = 11, theta = 1e-8: 71 -> 58, 76 -> 60, 83 -> 62.
+// Dynamic LDS (RHO, !filter_acc_reg): each thread's rho sums, [o][thread].
+
+// N <= 4 with complex64 storage: the staged values leave LDS for three blocks
+// of a compute unit with the rho sums there, so they are held in registers
+// (L = 15 as above: complex64/FP64 575 -> 533, complex64/FP32 540 -> 477 with
+// four waves; complex128, whose values are not staged, 567 -> 586: in LDS).
+template <int N, typename S> constexpr bool filter_acc_reg() { return N <= 4 && sizeof(S) == 4; }
+template <int N> constexpr int kFilterWaves = N <= 4 ? 4 : 1;
+
 template <int N, typename S, typename T, bool COUNT, bool RHO>
-__global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a) {
+__global__ void __launch_bounds__(kFB, kFilterWaves<N>) filter_step_kernel(const FilterStepArgs a) {
     using C = typename Cx<T>::type;
     using CS = typename Cx<S>::type;
     using LV = FilterLevel<N>;
     static_assert(N <= 16, "keep masks are 16 bits");
-    // the outputs of a segment run unrolled at N <= 4 (their loads overlap);
-    // at N = 9, 16 one at a time (unrolled, they spill)
-    constexpr int kOutUnroll = 1;
+    // the outputs of a segment run one at a time (unrolled, their loads take a
+    // wave per SIMD, at N = 9, 16 they spill), except where the rho sums are
+    // registers, which have to be named: there a memory clobber per output
+    // keeps the loads apart
+    constexpr bool kAccReg = filter_acc_reg<N, S>() && COUNT && RHO;
+    constexpr int kOutUnroll = kAccReg ? N : 1;
+    double2 acc_r[kAccReg ? N : 1]{};
     // N <= 4: the upper factor levels of a segment are multiplied for every o
     // at once, before the outputs, so that their loads are in flight together
-    // (not in the FP64 count pass with rho, where the 2N held products cost a
-    // wave per SIMD: M = 2, L = 15, theta = 1e-10, complex128 step 0.670 ->
-    // 0.624 ms)
-    constexpr bool kHoist = N <= 4 && !(COUNT && RHO && sizeof(T) == 8);
+    // (not in the count pass with rho, where the 2N held products cost a wave
+    // per SIMD: L = 15 as above, complex64/FP32 598 against 475 us per step)
+    constexpr bool kHoist = N <= 4 && !(COUNT && RHO);
     // entries past a tile that a segment starting in it may reach
     constexpr int kExt = N - 1;
     // values staged with the keys (complex64 storage); complex128 values are
@@ -164,7 +204,7 @@ __global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a
     }
     if (a.n_lv > 0)
         for (int idx = t; idx < 2 * LV::S0 * N; idx += kFB) s_t0[idx] = a.t[idx];
-    if (RHO)
+    if (RHO && !kAccReg)
         for (int o = 0; o < N; ++o) s_acc[o * kFB + t] = make_double2(0.0, 0.0);
     if (t < N) {
         if (COUNT) s_cnt[t] = 0;
@@ -226,6 +266,13 @@ __global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a
         }
         s_hi[2 * idx] = p;
         s_hi[2 * idx + 1] = pf;
+    }
+    // the rows of ones of levels 0 and 1 (a factor left out is exactly one)
+    unsigned ones0 = ~0u, ones1 = 0;
+    if (a.n_lv > 0) {
+        const unsigned *w = (const unsigned *)(a.t + 2 * (size_t)N * (LV::S0 + (size_t)(a.n_lv - 1) * LV::S));
+        ones0 = w[0];
+        ones1 = w[1];
     }
     if (lo < hi) fetch(lo);
     __syncthreads();
@@ -297,19 +344,21 @@ __global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a
                 if (full) {
                     // the segment's values by oldest digit (the dropped ones are zero)
                     if constexpr (!kStageVals && N <= 4) {
-                        // all N candidates requested at once; those of the next segments are ignored
+                        // the segment's values requested at once; entry e has
+                        // an oldest digit of e or more (-1: not the segment's)
                         CS vv[N];
-#pragma unroll
-                        for (int e = 0; e < N; ++e)
-                            vv[e] = base + h + e < n_in ? vin[kh + e] : CS{};
+                        int io[N];
 #pragma unroll
                         for (int e = 0; e < N; ++e) {
                             const unsigned long long key = s_key[1 + h + e];
-                            if (seg_of<N>(key, true) != m) continue;
-                            const int i = (int)(key % N);
+                            io[e] = seg_of<N>(key, true) == m ? (int)(key % N) : -1;
+                            if (io[e] >= 0) vv[e] = vin[kh + e];
+                        }
 #pragma unroll
-                            for (int ii = 0; ii < N; ++ii)
-                                if (ii == i) x[ii] = conv<C>(vv[e]);
+                        for (int e = 0; e < N; ++e) {
+#pragma unroll
+                            for (int ii = e; ii < N; ++ii)
+                                if (ii == io[e]) x[ii] = conv<C>(vv[e]);
                         }
                     } else {
                         for (int e = 0; e < N; ++e) {
@@ -350,31 +399,29 @@ __global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a
             const unsigned long long hv = m / hdiv;
             const int hc = hv >= hv_lo && hv - hv_lo < (unsigned long long)n_hi ? (int)(hv - hv_lo) : -1;
             const int l_end = hc >= 0 ? 2 : LV::kMax;   // the global levels are 1 .. l_end - 1
-            double2 up[kHoist ? N : 1], upf[kHoist ? N : 1];
+            double2 up[kHoist ? N : 1];
             if constexpr (kHoist) {
 #pragma unroll
-                for (int o = 0; o < N; ++o) up[o] = upf[o] = make_double2(1.0, 0.0);
+                for (int o = 0; o < N; ++o) up[o] = make_double2(1.0, 0.0);
 #pragma unroll
                 for (int l = 1; l < LV::kMax; ++l) {
                     if (l < a.n_lv && l < l_end && active) {
                         const double2 *q = a.t + 2 * (((size_t)LV::S0 + (size_t)(l - 1) * LV::S + lv[l]) * N);
 #pragma unroll
                         for (int o = 0; o < N; ++o) {
+                            if (l == 1 && (ones1 >> o & 1u)) continue;
                             up[o] = cmul(up[o], q[2 * o]);
-                            if (RHO) upf[o] = cmul(upf[o], q[2 * o + 1]);
                         }
                     }
                 }
                 if (hc >= 0 && active) {
 #pragma unroll
-                    for (int o = 0; o < N; ++o) {
-                        up[o] = cmul(up[o], s_hi[2 * (hc * N + o)]);
-                        if (RHO) upf[o] = cmul(upf[o], s_hi[2 * (hc * N + o) + 1]);
-                    }
+                    for (int o = 0; o < N; ++o) up[o] = cmul(up[o], s_hi[2 * (hc * N + o)]);
                 }
             }
 #pragma unroll kOutUnroll
             for (int o = 0; o < N; ++o) {
+                if constexpr (kAccReg) asm volatile("" ::: "memory");
                 const bool want = active && (COUNT || ((mask >> o) & 1u));
                 unsigned long long place = 0;
                 if (!COUNT) {
@@ -384,24 +431,20 @@ __global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a
                 }
                 if (want) {
                     double2 p = make_double2(1.0, 0.0), pf = p;
-                    if (a.n_lv > 0) {
+                    if (!(ones0 >> o & 1u)) {
                         p = s_t0[2 * (lv[0] * N + o)];
                         if (RHO) pf = s_t0[2 * (lv[0] * N + o) + 1];
                     }
                     if constexpr (kHoist) {
-                        double2 u = up[0], uf = upf[0];
+                        double2 u = up[0];
 #pragma unroll
                         for (int oo = 1; oo < N; ++oo)
-                            if (oo == o) {
-                                u = up[oo];
-                                uf = upf[oo];
-                            }
+                            if (oo == o) u = up[oo];
                         p = cmul(p, u);
-                        if (RHO) pf = cmul(pf, uf);
                     } else {
 #pragma unroll
                         for (int l = 1; l < LV::kMax; ++l) {
-                            if (l < a.n_lv && l < l_end) {
+                            if (l < a.n_lv && l < l_end && !(l == 1 && (ones1 >> o & 1u))) {
                                 const double2 *q =
                                     a.t + 2 * (((size_t)LV::S0 + (size_t)(l - 1) * LV::S + lv[l]) * N + o);
                                 p = cmul(p, q[0]);
@@ -448,7 +491,7 @@ __global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a
                         if (squared ? mag2 > theta2 : sqrt(mag2) > a.theta) mask |= 1u << o;
                         if (RHO) {
                             const double2 w = cmul(pf, to_d2(sumf));
-                            double2 &acc = s_acc[o * kFB + t];
+                            double2 &acc = kAccReg ? acc_r[kAccReg ? o : 0] : s_acc[o * kFB + t];
                             acc.x += w.x;
                             acc.y += w.y;
                         }
@@ -481,8 +524,9 @@ __global__ void __launch_bounds__(kFB) filter_step_kernel(const FilterStepArgs a
         __syncthreads();
         if (t < N) a.bofs[(size_t)t * gridDim.x + blockIdx.x] = s_cnt[t];
         if (RHO) {
+#pragma unroll
             for (int o = 0; o < N; ++o) {
-                double2 v = s_acc[o * kFB + t];
+                double2 v = kAccReg ? acc_r[kAccReg ? o : 0] : s_acc[o * kFB + t];
                 for (int off = 32; off > 0; off >>= 1) {
                     v.x += __shfl_xor(v.x, off, 64);
                     v.y += __shfl_xor(v.y, off, 64);
@@ -570,8 +614,9 @@ __global__ void filter_init_kernel(const double2 *rho0, const double2 *bank, int
 template <int N, typename S, typename T>
 hipError_t launch_filter_step_t(const FilterStepArgs &a, bool count, bool rho, hipStream_t st) {
     const dim3 g(kFilterStepBlocks), b(kFB);
+    const size_t lds = filter_acc_reg<N, S>() ? 0 : filter_step_lds_bytes(N, true);
     if (count && rho)
-        hipLaunchKernelGGL((filter_step_kernel<N, S, T, true, true>), g, b, filter_step_lds_bytes(N, true), st, a);
+        hipLaunchKernelGGL((filter_step_kernel<N, S, T, true, true>), g, b, lds, st, a);
     else if (count) hipLaunchKernelGGL((filter_step_kernel<N, S, T, true, false>), g, b, 0, st, a);
     else hipLaunchKernelGGL((filter_step_kernel<N, S, T, false, false>), g, b, 0, st, a);
     return hipGetLastError();

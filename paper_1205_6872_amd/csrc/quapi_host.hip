@@ -510,7 +510,7 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_fctr = take(filtered ? 8 * 8 : 0);          // entry counts of both buffers, overflow flag
     l.off_fpart = take(filtered ? (size_t)kFilterStepBlocks * N * 16 : 0);
     l.fplan_entries = filtered ? std::max<size_t>(1, filter_plan_entries(N, L - 1)) : 0;
-    l.off_fplan = take(l.fplan_entries * 2 * 16);
+    l.off_fplan = take((l.fplan_entries + 1) * 2 * 16);
     l.total = off;
     return l;
 }

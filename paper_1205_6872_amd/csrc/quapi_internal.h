@@ -367,7 +367,7 @@ struct FilterPlanArgs {
     const double2 *bank;
     int N, nd, n_lv;
     int16_t tab[kMaxL], tabf[kMaxL];
-    double2 *t;
+    double2 *t;                 // the level tables, then one word per level: its rows of ones
 };
 struct FilterStepArgs {
     const double2 *bank;
@@ -379,7 +379,7 @@ struct FilterStepArgs {
     unsigned short *masks;      // [entries] keep bits of a segment's N outputs, at its head entry
     unsigned long long *bofs;   // [N][kFilterStepBlocks] kept outputs per (o, block), then their offsets
     double2 *partials;          // [kFilterStepBlocks][N] block partial sums of rho (count pass)
-    const double2 *t;           // factor-product levels, (interior, final) pairs
+    const double2 *t;           // factor-product levels, (interior, final) pairs, and their rows of ones
     unsigned long long capacity;
     unsigned long long stride_new;   // N^(L-1) (full window) or N^n (growth step n)
     double theta;

@@ -253,3 +253,33 @@ def test_tiny_theta_equals_theta_zero():
     a, ka = gpu_filtered(w, 30, 0.0)
     b, kb = gpu_filtered(w, 30, 1e-200)
     assert np.array_equal(a, b) and np.array_equal(ka, kb)
+
+
+# Rows of ones: levels with equal coordinates give more of them than the
+# diagonal points (a factor that is exactly one is left out of the product).
+# L = 4, 5, 10 put K into level 1, into level 1 with a full level 0, and into
+# level 2.  Tolerances as above.
+def _equal_levels():
+    rng = np.random.default_rng(11)
+    w1 = W.spin_boson_l7()
+    H3 = W.random_hermitian(rng, 3)
+    return [("m2_equal_l5", w1.with_(s=np.array([0.5, 0.5]), L=5, rho0=RHO_MIXED), 12, 1e-3),
+            ("m2_l4", w1.with_(L=4, rho0=RHO_MIXED), 12, 1e-3),
+            ("m2_l10", w1.with_(L=10, rho0=RHO_MIXED), 13, 1e-5),
+            ("m3_two_equal_l5", w1.with_(M=3, s=np.array([1.0, -0.5, 1.0]), H=H3, L=5, xi=0.3,
+                                         rho0=np.diag([0.5, 0.25, 0.25]).astype(complex)), 12, 1e-5)]
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64", "c64f64"])
+@pytest.mark.parametrize("name,w,n,theta", _equal_levels(), ids=[c[0] for c in _equal_levels()])
+def test_rows_of_ones_are_left_out(name, w, n, theta, dtype):
+    print(f"case {name} {dtype}: M={w.M} L={w.L} steps={n} theta={theta:g}", flush=True)
+    ro, ko, margin = orun.oracle_run_filtered(w, n, theta)
+    rg, kg = gpu_filtered(w, n, theta, dtype=dtype)
+    if dtype == "c128":
+        assert margin > 1e-6, margin
+        assert list(kg) == list(ko)
+        assert np.abs(rg - ro).max() <= 1e-12
+    else:
+        assert np.all(np.abs(kg - ko) <= 1e-3 * np.maximum(ko, 1) + 1), np.abs(kg - ko).max()
+        assert np.abs(rg - ro).max() <= 2e-5, np.abs(rg - ro).max()
