@@ -6,18 +6,16 @@ rho(t_n) extracted at every step ('allPoints').  Inputs are synthetic
 (seeded parameters, no dataset).
 
 A timed "step" is one full-window propagation step.  For M = 2 the library
-fuses consecutive steps into one kernel launch (at L = 15 three with
-complex128 and complex64, two with complex64 storage and FP64 arithmetic):
-it reads the tensor once, keeps the intermediate tensors in registers,
-writes the tensor of the group's last step once, and produces per-block
-partial sums of rho at every step of the group in the same pass; a small
-finalize kernel on a side stream sums them.  In mirror mode (on by default:
-rho0 is Hermitian) a launch reads and writes only the (N^L + M^L) / 2
-entries not above their mirror, the rest being their conjugates.  The
-groups are fixed by the global step number, so the warm-up is lengthened
-until the timed call starts on a group boundary (`warmup_steps_run`); a
-timed call of K steps then runs K // F whole groups and its last K % F steps
-as one shorter launch or singly (`roofline.other_launches`).  The growth
+runs up to four consecutive steps per pass over the tensor (F = 4): it reads
+the tensor once, keeps the intermediate tensors in registers, writes the
+tensor of the last step once, and produces per-block rows of rho at every
+step in the same pass, which extra blocks of the next pass sum.  In mirror
+mode (on by default: rho0 is Hermitian) a pass reads and writes only the
+(N^L + M^L) / 2 entries not above their mirror, the rest being their
+conjugates.  The passes are fixed by the global step number, so the warm-up
+is lengthened until the timed call starts on a pass boundary
+(`warmup_steps_run`); a timed call of K steps then runs K // F whole passes
+and its last K % F steps as one shorter pass.  The growth
 steps (n < L) and the device setup run first and are reported separately;
 after the timed call every tier runs on, untimed, to step 1000, so the
 complex64 tiers are compared with complex128 (max|drho| and trace drift)
@@ -27,8 +25,7 @@ over the whole workload whatever K is.  Three precisions run: complex128
 (`c64_storage_f64_math`).
 
 Metric: Gelem/s = N^L * K / seconds / 1e9 over the K timed steps, with the
-tensor resident in HBM.  `roofline` prices the dominant launch (the F-step
-launch, its mirror-mode group of three kernels counted as one launch)
+tensor resident in HBM.  `roofline` prices the dominant launch (a pass of F steps)
 against the HBM peak of 8 TB/s: `achieved` = the bytes the launch must
 move ((N^L + M^L) * sizeof(complex) in mirror mode, 2 * N^L * sizeof
 otherwise) / its mean duration from HIP events on the library's stream;
@@ -95,6 +92,9 @@ def aligned_warmup(warmup: int, F: int) -> int:
     return w
 
 
+PASS_STEPS = 4             # steps per pass over the tensor (M = 2, L >= 8, no pinned width)
+
+
 def run_tier(w, dtype: str, warmup: int, steps, total_steps: int):
     """Growth, aligned warm-up, K timed steps, then (untimed) the rest of the
     run up to total_steps so that every tier's rho is compared over it."""
@@ -109,7 +109,7 @@ def run_tier(w, dtype: str, warmup: int, steps, total_steps: int):
     ctx = Q.create_in_torch(p, stream=stream)
     setup_wall = time.perf_counter() - t0
     try:
-        F = ctx.fused_steps()
+        F = PASS_STEPS
         w_run = aligned_warmup(warmup, F)
         if steps is None:
             steps = total_steps - (L - 1) - w_run
@@ -127,9 +127,7 @@ def run_tier(w, dtype: str, warmup: int, steps, total_steps: int):
         ctx.set_timing(False)
         rest = total_steps - ctx.step_count()
         rho_rest = ctx.propagate(rest) if rest > 0 else np.zeros((0, w.M, w.M), complex)
-        # the fused kernels' mirror mode: the three-step kernel always, the
-        # two-step kernel above 2^22 entries (or at every size in mode 2)
-        mirror = bool(ctx.mirror()) and (F == 3 or (F == 2 and (ctx.mirror() == 2 or N ** L > 2 ** 22)))
+        mirror = bool(ctx.mirror())
     finally:
         ctx.destroy()
         del ctx
@@ -140,19 +138,15 @@ def run_tier(w, dtype: str, warmup: int, steps, total_steps: int):
     # written once; in mirror mode only the entries not above their mirror,
     # (N^L + M^L) / 2 of them
     bytes_per_launch = (entries + w.M ** L) * csize if mirror else 2 * entries * csize
-    # launches of the dominant width (F steps each), timed apart from the
-    # single or two-step launches at the ends of the call
-    launches = max(int(tm["width_launches"][F]), 1)
-    kernel_ms = tm["width_ms"][F] / launches
-    other = {str(k): {"launches": int(tm["width_launches"][k]),
-                      "ms_per_launch": round(tm["width_ms"][k] / tm["width_launches"][k], 4)}
-             for k in (1, 2, 3) if k != F and tm["width_launches"][k] > 0}
+    # every pass of the timed call moves the same bytes, also one of fewer than
+    # F steps at its end
+    launches = max(int(tm["step_launches"]), 1)
+    kernel_ms = tm["step_ms"] / launches
     achieved = bytes_per_launch / (kernel_ms * 1e-3) / 1e9
     rho = np.concatenate([rho_grow, rho_warm, rho_main, rho_rest])
     return dict(
         dtype=dtype, elapsed_s=elapsed, steps=steps, warmup_run=w_run, ms_per_step=elapsed * 1e3 / steps,
         gelem_s=entries * steps / elapsed / 1e9, kernel_ms=kernel_ms, kernel_launches=launches, F=F,
-        other_launches=other,
         finalize_ms=tm["finalize_ms"] / max(tm["finalize_launches"], 1), setup_ms=tm["setup_ms"],
         setup_wall_ms=setup_wall * 1e3, grow_ms=grow_ms, bytes_per_launch=bytes_per_launch,
         achieved_gbs=achieved, rho=rho, mirror=mirror, step_bytes=2 * entries * csize)
@@ -160,12 +154,8 @@ def run_tier(w, dtype: str, warmup: int, steps, total_steps: int):
 
 def kernel_name(tier: str, F: int, mirror: bool = False) -> str:
     st = {"c128": "double, double", "c64": "float, float", "c64f64": "float, double"}[tier]
-    half = ", the entries not above their mirror only (modes 1 + 2 + 3)" if mirror else ""
-    if F == 3:
-        return f"step3_kernel<{st}, rho{', mirror' if mirror else ''}> (three steps fused per launch{half})"
-    if F == 2:
-        return f"step2_kernel<{st}, rho{', mirror' if mirror else ''}> (two steps fused per launch{half})"
-    return f"step_kernel<4, {st}, rho, full-window>"
+    half = ", the entries not above their mirror only" if mirror else ""
+    return f"tile_kernel<{st}, rho{', mirror' if mirror else ''}> ({F} steps per pass{half})"
 
 
 def roofline(r, traffic):
@@ -185,20 +175,15 @@ def roofline(r, traffic):
             "step_equivalent_frac": round(step_eq / HBM_PEAK_GBS, 4),
             "step_equivalent_definition": ("F steps x 2 N^L sizeof(complex) (one read and one write of "
                                            "the whole tensor per unfused step) / launch time / 8 TB/s"),
-            "other_launches": r["other_launches"]}
-
-
-# The dominant kernel of each tier at M = 2, L = 15 (its sources' hash ties
-# the committed counter summary to the code: paper_1205_6872_amd.profsummary).
-TIER_KERNEL = {"c128": "step3", "c64": "step3", "c64f64": "step2"}
+            "steps_in_timed_launches": r["steps"]}
 
 
 def measured_traffic(tier: str):
-    """HBM bytes per launch of the tier's dominant kernel from the committed
+    """HBM bytes per launch of the tier's pass over the tensor from the committed
     rocprofv3 counter summary, or None when the kernel's sources changed since
     the counters were taken."""
     from paper_1205_6872_amd.profsummary import kernel_source_hash
-    kernel = TIER_KERNEL[tier]
+    kernel = "tile"
     path = os.path.join(ROOT, "profiles", f"{kernel}_kernel_traffic_spin_boson_l15.json")
     if not os.path.exists(path):
         return None
@@ -434,7 +419,7 @@ def main() -> int:
         r = res[t]
         log(f"bench: tier {t}: {r['ms_per_step']:.3f} ms/step, {r['gelem_s']:.1f} Gelem/s, "
             f"{r['F']}-step launch {r['kernel_ms']:.3f} ms = {r['achieved_gbs']:.0f} GB/s "
-            f"(warm-up {r['warmup_run']}, other launches {r['other_launches']})")
+            f"(warm-up {r['warmup_run']}, {r['kernel_launches']} passes)")
     main_t = "c128" if "c128" in res else tiers[0]
     r = res[main_t]
     out = {

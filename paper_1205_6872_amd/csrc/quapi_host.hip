@@ -132,9 +132,10 @@ int fusion_width(int N, int L, int prec) {
 
 // The four-step tile kernel (quapi_tile.hip) runs every full-window step past
 // n = L of a dense M = 2 context from L = kTileMinL that pins no
-// launch width.  Below, at N^L <= 2^14, the persistent path does better (L = 7:
-// 11 us per step, one launch); a tile needs the digits d0 .. d3, w0, w1 and at
-// least one more.
+// launch width (complex128, rho every step: L = 8 24 -> 2.8 us per step, L = 15
+// 1.19 -> 0.91 ms).  Below, at N^L <= 2^14, the persistent path takes one launch
+// per call (L = 7: 4.2 us per step); a tile needs the digits d0 .. d3, w0, w1
+// and at least one more.
 bool tile_ok(int N, int L) { return N == 4 && L >= kTileMinL; }
 // Its outer digits past w0, w1: the middle ones share a table of at most 256
 // values, the rest another.

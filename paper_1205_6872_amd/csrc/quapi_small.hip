@@ -10,9 +10,11 @@
 // while the window fills, then multiply by K and the new point's factors and
 // sum out the oldest point -- but the whole step sequence stays inside one
 // workgroup, so a step costs a barrier rather than three kernel launches.
-// The tensor ping-pongs between two LDS buffers when both fit (N^L up to
-// 4096 at complex128), else between the context's two global buffers, which
-// stay in the L2 cache at these sizes.
+// Two kernels: small_reg_kernel keeps the tensor of M = 2, L = 5..7 in the
+// block's registers (full-window steps); small_kernel runs everything else
+// (growth, other N and L), its tensor ping-ponging between two LDS buffers when
+// both fit (N^L up to 4096 at complex128), else between the context's two
+// global buffers, which stay in the L2 cache at these sizes.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

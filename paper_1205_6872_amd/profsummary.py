@@ -1,12 +1,12 @@
 """Text summaries of rocprofv3 output for the repository's profiles/ folder.
 
-    python -m paper_1205_6872_amd.profsummary traffic --fetch DIR --write DIR --kernel step3 \
+    python -m paper_1205_6872_amd.profsummary traffic --fetch DIR --write DIR --kernel tile \
         --tiers c128,c64 --cmd "..." --out NAME
     python -m paper_1205_6872_amd.profsummary trace --dir DIR --cmd "..." --out NAME [--match TEXT]
     python -m paper_1205_6872_amd.profsummary counters --dirs DIR,DIR,.. --match TEXT --cmd "..." --out NAME
 
 `traffic` turns two counter passes (FETCH_SIZE, then WRITE_SIZE, in KiB per
-dispatch) into HBM bytes per launch of a fused step kernel, scaled by what the
+dispatch) into HBM bytes per whole pass of the tile kernel, scaled by what the
 same counters read for the 16 GiB chunked copy of the run (its bytes are
 known), and writes NAME.json (read by bench.py for `roofline.traffic`, tied to
 a hash of the kernel's sources) and NAME.md.  `trace` writes the kernel-trace
@@ -27,9 +27,8 @@ from pathlib import Path
 PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 
-# The fused step kernels and the sources each is compiled from.
-KERNEL_SOURCES = {"step2": ("quapi_step2.hip", "quapi_device.h", "quapi_internal.h"),
-                  "step3": ("quapi_step3.hip", "quapi_device.h", "quapi_internal.h")}
+# The kernel of the full-window passes and the sources it is compiled from.
+KERNEL_SOURCES = {"tile": ("quapi_tile.hip", "quapi_step4.h", "quapi_device.h", "quapi_internal.h")}
 TIER_TYPES = {"c128": "double, double", "c64": "float, float", "c64f64": "float, double"}
 COPY_KERNEL = "copy_chunks_kernel"
 COPY_BYTES = 2 ** 34                     # bench.py's copy ceiling: 16 GiB read, 16 GiB written
@@ -76,13 +75,12 @@ def traffic(fetch_dir: str, write_dir: str, kernel: str, tiers, entries: int, M:
                               "bytes_written": COPY_BYTES, "FETCH_SIZE_KiB": f_copy, "WRITE_SIZE_KiB": w_copy,
                               "fetch_scale": fscale, "write_scale": wscale}}
     for tier in tiers:
-        name = f"{kernel}_kernel<{TIER_TYPES[tier]}, true"
+        name = f"{kernel}_kernel<{TIER_TYPES[tier]}, true, true, 0,"     # rho, mirror mode, a whole pass
         cs = 16 if tier == "c128" else 8
 
         def tot(rows):
             vals = [v for n, v in rows.values() if name in n]
-            groups = sum(1 for n, _ in rows.values() if name in n and (", true, 1>" in n or ", true, 0>" in n))
-            return sum(vals), groups
+            return sum(vals), len(vals)
 
         fsum, fgroups = tot(fetch)
         wsum, wgroups = tot(write)
@@ -91,7 +89,7 @@ def traffic(fetch_dir: str, write_dir: str, kernel: str, tiers, entries: int, M:
         fk, wk = fsum / fgroups, wsum / wgroups
         hbm = fk * 1024 * fscale + wk * 1024 * wscale
         alg = (entries + M ** L) * cs           # the kept half, read once and written once
-        out[tier] = {"kernel": f"{name}, 1> + <.., 3> (one mirror-mode group)", "launches": fgroups,
+        out[tier] = {"kernel": f"{name} ..>", "launches": fgroups,
                      "FETCH_SIZE_KiB": fk, "WRITE_SIZE_KiB": wk, "hbm_bytes_per_launch": int(round(hbm)),
                      "algorithmic_bytes_per_launch": alg, "ratio": hbm / alg}
     return out
@@ -106,10 +104,9 @@ def traffic_md(t: dict, kernel: str, cmds) -> str:
               f"FETCH_SIZE = {c['FETCH_SIZE_KiB']:.4g} KiB and WRITE_SIZE = {c['WRITE_SIZE_KiB']:.4g} KiB for 16 GiB "
               f"read and 16 GiB written, so HBM bytes = FETCH_SIZE * 1024 * {c['fetch_scale']:.4f} + "
               f"WRITE_SIZE * 1024 * {c['write_scale']:.4f}.", "",
-              "Mirror-mode launches are counted together (the mode-1 launch, whose tail runs the listed items of "
-              "the diagonal blocks, and the mode-3 launch of one group); algorithmic bytes = "
+              "Whole passes (four steps) in mirror mode; algorithmic bytes = "
               "(N^L + M^L) * sizeof(complex), the kept half read once and written once.", "",
-              "| precision | groups | FETCH_SIZE KiB (mean) | WRITE_SIZE KiB (mean) | HBM bytes / launch | "
+              "| precision | passes | FETCH_SIZE KiB (mean) | WRITE_SIZE KiB (mean) | HBM bytes / launch | "
               "algorithmic bytes / launch | ratio |", "|---|---|---|---|---|---|---|"]
     for tier in ("c128", "c64", "c64f64"):
         if tier in t:
