@@ -546,6 +546,9 @@ struct quapi_ctx {
     bool side_ready = false;      // both and their events exist (ensure_side)
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     bool fin_pending[kSlots] = {};
+    // rho rows of the last mirror-mode single step, summed by the next step's
+    // launch or rho_flush (rows 0: none)
+    int pend_slot = 0, pend_rows = 0;
     int next_slot = 0;
     char *ws = nullptr;
     bool own_ws = false;
@@ -930,8 +933,20 @@ quapi_status ensure_side(quapi_ctx *c) {
     return QUAPI_OK;
 }
 
-// Order the main stream after every finalize still running on the side stream.
+// Sum the rho rows that the last mirror-mode single step left, on the stream.
+quapi_status rho_flush(quapi_ctx *c) {
+    if (!c->pend_rows) return QUAPI_OK;
+    const int rows = c->pend_rows;
+    c->pend_rows = 0;
+    hipError_t e = launch_rho_finalize(c->N, c->partials[c->pend_slot], rows, c->pairs, c->sink, c->stream);
+    if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "rho finalize launch: %s", hipGetErrorString(e));
+    return QUAPI_OK;
+}
+
+// Order the main stream after every finalize still running on the side stream,
+// and finish the rho of the last step.
 quapi_status join_side(quapi_ctx *c) {
+    if (quapi_status st = rho_flush(c); st != QUAPI_OK) return st;
     for (int k = 0; k < kSlots; ++k) {
         quapi_status st = wait_slot(c, k);
         if (st != QUAPI_OK) return st;
@@ -952,6 +967,7 @@ quapi_status ensure_full(quapi_ctx *c) {
 // Finalize the rho partials of `slots` (in order) on the side stream, after
 // the step kernel that wrote them.
 quapi_status finalize_side(quapi_ctx *c, const int *slots, int n, int grid) {
+    if (quapi_status st = rho_flush(c); st != QUAPI_OK) return st;
     if (c->one_stream) {
         for (int k = 0; k < n; ++k) {
             hipError_t e = launch_rho_finalize(c->N, c->partials[slots[k]], grid, c->pairs, c->sink, c->stream);
@@ -1036,6 +1052,18 @@ quapi_status enqueue_step(quapi_ctx *c, int n, bool rho) {
         e1 = take_event(c);
         if (e0) (void)hipEventRecord(e0, c->stream);
     }
+    // A mirror-mode step of a large tensor leaves its rho rows to the next one's
+    // launch: on the side stream a step's two events keep the next step's launch
+    // back by about 10 us (rho every step, per step: M = 3, L = 8, complex128
+    // 176 -> 165 us; M = 4, L = 6, complex64 37 -> 31).  Smaller tensors replay
+    // graphs, which hold a finalize of their own.
+    if (half && c->pend_rows) {
+        a.prev = c->partials[c->pend_slot];
+        a.prev_rows = c->pend_rows;
+        a.n_prev = c->N;
+        a.sink = c->sink;
+        c->pend_rows = 0;
+    }
     int rows = sp.split.grid;
     hipError_t e = sp.grow ? launch_step(c->N, c->prec, rho, true, a, sp.split.grid, c->stream)
                            : launch_full_step(c, rho, a, sp.split.grid, &rows);
@@ -1044,7 +1072,12 @@ quapi_status enqueue_step(quapi_ctx *c, int n, bool rho) {
         (void)hipEventRecord(e1, c->stream);
         c->recs.push_back({sp.grow ? 1 : 0, e0, e1, sp.grow ? 0 : 1, sp.grow ? 0 : 1});
     }
-    if (rho) {
+    if (rho && half && rows <= kDirectRows && (size_t)ipow_ll(c->N, c->L) > kGraphMaxEntries) {
+        // the sink takes the steps in order: what the side stream still sums comes first
+        if ((st = join_side(c)) != QUAPI_OK) return st;
+        c->pend_slot = slot;
+        c->pend_rows = rows;
+    } else if (rho) {
         st = finalize_side(c, &slot, 1, rows);
         if (st != QUAPI_OK) return st;
     }
@@ -1835,6 +1868,7 @@ quapi_status propagate_impl(quapi_ctx *c, int n_steps, const int *sel, int n_sel
     if (small_on(c)) return propagate_small(c, n_steps, sel, n_sel, dev_out, host_out);
     const int N = c->N, L = c->L;
     c->tile_pending.n = 0;               // an earlier call that failed may have left its own
+    c->pend_rows = 0;
     int si = 0;          // next selection entry
     int written = 0;     // outputs delivered so far
     int staged = 0;      // outputs in the staging buffer (blocking call)

@@ -74,6 +74,11 @@ struct StepArgs {
     const int *blk_hi;
     const int *low_list;
     int n_blk, n_canon, n_diag, parts, q_span, mode, n_low;
+    // Mirror mode: n_prev = N blocks ahead of the others (0: none) sum the
+    // prev_rows rows of rho that an earlier launch left at prev into the sink.
+    const double2 *prev;
+    int prev_rows, n_prev;
+    struct RhoSink *sink;
     // N = 16 full-window steps (L >= 2) with the new points grouped by their
     // oldest-point rows (cls_on): the row of o is F_self(o) times the
     // influence row of the oldest point, which depends on o = (a, b) only
@@ -249,6 +254,8 @@ hipError_t launch_step(int N, int prec, bool with_rho, bool grow, const StepArgs
                        hipStream_t st);
 // Where finalized rho values go: rho of the k-th finalize after a reset is
 // written to base + k*N (k counted per point).  Device-resident, so graph replays need no new arguments.
+// A row set of up to kDirectRows rows is summed by a block per point.
+constexpr int kDirectRows = 8192;
 struct RhoSink {
     double2 *base;
     unsigned long long count[kMaxN];         // per point o

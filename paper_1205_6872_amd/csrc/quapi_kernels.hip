@@ -648,31 +648,20 @@ __device__ __forceinline__ void step_body(const StepArgs &a, const int bid) {
                     s.y -= s_red[w * N + tb].y;
                 }
             }
-            a.partials[(size_t)blockIdx.x * N + t] = s;
+            a.partials[(size_t)((int)blockIdx.x - a.n_prev) * N + t] = s;
         }
     }
-}
-
-template <int N, typename S, typename T, bool RHO, bool GROW>
-__global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
-    step_body<N, S, T, RHO, GROW, 0>(a, (int)blockIdx.x);
-}
-// Mirror mode in one launch: the blocks of mode 1 (at N = 9 with their listed
-// tail, which is then all of the diagonal values' items below their mirror),
-// those of mode 2 (N = 4), then those of mode 3.
-template <int N, typename S, typename T, bool RHO>
-__global__ void __launch_bounds__(kBlock) step_mirror_kernel(const StepArgs a) {
-    const int n2 = a.n_diag * a.parts, b = (int)blockIdx.x - a.n_canon;
-    if (b < (N == 9 ? n2 : 0)) step_body<N, S, T, RHO, false, 1>(a, (int)blockIdx.x);
-    else if (N != 9 && b < n2) step_body<N, S, T, RHO, false, 2>(a, b);
-    else step_body<N, S, T, RHO, false, 3>(a, b - n2);
 }
 
 // rho(t_n)[o] = sum over the step's block partials, compensated, in a fixed
 // order (each launch boundary makes the previous writes visible without
 // device-scope fences), to sink->base + sink->count[o] * N + o; block o advances
 // its own count, so a captured graph can replay the launch unchanged.
-//   up to kDirectRows rows  rho_direct_kernel: one launch, a block per o;
+//   up to kDirectRows rows  rho_direct_kernel: one launch, a block per o (32
+//                           rows a thread); after a mirror-mode step of a large
+//                           tensor these blocks ride in the next step's launch
+//                           (StepArgs::prev), since a launch on another stream
+//                           costs two events per step;
 //   more                    rho_slice_kernel: kSlices blocks, block b a
 //                           contiguous share of the rows, a (sum, compensation)
 //                           pair per o; then rho_final_kernel, a block per o.
@@ -681,7 +670,6 @@ __global__ void __launch_bounds__(kBlock) step_mirror_kernel(const StepArgs a) {
 // that took the points one after the other, each through a tree of barriers,
 // ran 36 us at N = 16 and 8 us at N = 4, now 5.
 constexpr int kSlices = kRhoSlices;
-constexpr int kDirectRows = 8192;        // 32 rows per thread
 
 // The block's (sum, compensation) pairs (re in r, im in i) combined in a fixed
 // order; the total lands in thread 0.
@@ -712,9 +700,9 @@ __device__ __forceinline__ void sink_put(RhoSink *sink, int N, int o, double2 r,
     sink->count[o] = k + 1;
 }
 
-__global__ void __launch_bounds__(kBlock) rho_direct_kernel(const double2 *__restrict__ partials, int rows,
-                                                            RhoSink *sink) {
-    const int o = blockIdx.x, N = gridDim.x;
+// Point o's sum over the rows, by one block.
+__device__ __forceinline__ void rho_rows(const double2 *__restrict__ partials, int rows, int N, int o,
+                                         RhoSink *sink) {
     double2 r = make_double2(0.0, 0.0), i = r;
     constexpr int U = 8;                  // rows in flight per thread
     int k = threadIdx.x;
@@ -735,6 +723,30 @@ __global__ void __launch_bounds__(kBlock) rho_direct_kernel(const double2 *__res
     }
     block_combine_pairs(r, i);
     if (threadIdx.x == 0) sink_put(sink, N, o, r, i);
+}
+
+__global__ void __launch_bounds__(kBlock) rho_direct_kernel(const double2 *partials, int rows, RhoSink *sink) {
+    rho_rows(partials, rows, (int)gridDim.x, (int)blockIdx.x, sink);
+}
+
+template <int N, typename S, typename T, bool RHO, bool GROW>
+__global__ void __launch_bounds__(kBlock) step_kernel(const StepArgs a) {
+    step_body<N, S, T, RHO, GROW, 0>(a, (int)blockIdx.x);
+}
+// Mirror mode in one launch: the blocks of mode 1 (at N = 9 with their listed
+// tail, which is then all of the diagonal values' items below their mirror),
+// those of mode 2 (N = 4), then those of mode 3.
+template <int N, typename S, typename T, bool RHO>
+__global__ void __launch_bounds__(kBlock) step_mirror_kernel(const StepArgs a) {
+    const int blk = (int)blockIdx.x - a.n_prev;
+    if (blk < 0) {
+        rho_rows(a.prev, a.prev_rows, N, (int)blockIdx.x, a.sink);
+        return;
+    }
+    const int n2 = a.n_diag * a.parts, b = blk - a.n_canon;
+    if (b < (N == 9 ? n2 : 0)) step_body<N, S, T, RHO, false, 1>(a, blk);
+    else if (N != 9 && b < n2) step_body<N, S, T, RHO, false, 2>(a, b);
+    else step_body<N, S, T, RHO, false, 3>(a, b - n2);
 }
 
 // One point o per thread and kBlock / N row lanes: a row's N values are read by
@@ -1166,7 +1178,11 @@ __global__ void __launch_bounds__(kBlock, RHO ? 3 : 1) step16_mfma_kernel(const 
 // a launch of their own and only the other two share one.
 template <typename S, typename T, bool RHO, bool CLS, bool ALL>
 __global__ void __launch_bounds__(kBlock, ALL ? (RHO ? 3 : 4) : 1) step16_mirror_kernel(const StepArgs a) {
-    const int row = (int)blockIdx.x + (ALL ? 0 : a.n_canon);
+    const int row = (int)blockIdx.x - a.n_prev + (ALL ? 0 : a.n_canon);
+    if ((int)blockIdx.x < a.n_prev) {
+        rho_rows(a.prev, a.prev_rows, 16, (int)blockIdx.x, a.sink);
+        return;
+    }
     const int n2 = a.n_diag * a.parts, b = row - a.n_canon;
     if (ALL && b < 0) step16_body<S, T, RHO, 1, CLS>(a, row, row);
     else if (b < n2) step16_body<S, T, RHO, 2, CLS>(a, b, row);
@@ -1181,12 +1197,13 @@ hipError_t launch_step16_c(const StepArgs &a, int grid, hipStream_t st) {
     if (a.mode == 0) {
         hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, CLS, 0>), dim3(grid), b, lay.total, st, a);
     } else if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL((step16_mirror_kernel<S, T, RHO, CLS, true>), dim3(a.n_blk), b, lay.total, st, a);
+        hipLaunchKernelGGL((step16_mirror_kernel<S, T, RHO, CLS, true>), dim3(a.n_prev + a.n_blk), b, lay.total, st,
+                           a);
     } else {
         if (a.n_canon > 0)
             hipLaunchKernelGGL((step16_mfma_kernel<S, T, RHO, CLS, 1>), dim3(a.n_canon), b, lay.total, st, a);
-        hipLaunchKernelGGL((step16_mirror_kernel<S, T, RHO, CLS, false>), dim3(a.n_blk - a.n_canon), b, lay.total, st,
-                           a);
+        hipLaunchKernelGGL((step16_mirror_kernel<S, T, RHO, CLS, false>), dim3(a.n_prev + a.n_blk - a.n_canon), b,
+                           lay.total, st, a);
     }
     return hipGetLastError();
 }
@@ -1207,7 +1224,7 @@ hipError_t launch_step_t(const StepArgs &a, int grid, hipStream_t st) {
     const dim3 b(kBlock);
     if constexpr ((N == 4 || N == 9) && !GROW) {
         if (a.mode != 0) {
-            hipLaunchKernelGGL((step_mirror_kernel<N, S, T, RHO>), dim3(a.n_blk), b, lay.total, st, a);
+            hipLaunchKernelGGL((step_mirror_kernel<N, S, T, RHO>), dim3(a.n_prev + a.n_blk), b, lay.total, st, a);
             return hipGetLastError();
         }
     } else {

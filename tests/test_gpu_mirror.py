@@ -376,3 +376,26 @@ def test_driven_context_runs_mirror_single_steps():
         ctx.set_mirror(2)                  # L = 6 is below the default size
         rho = ctx.propagate(30, list(range(31)))
     assert rel_err_per_step(rho, orun.oracle_run(w, 30)).max() <= TOL_C128
+
+
+# Large single-step tensors leave the rho rows of a step to the next step's
+# launch; with gaps in the selection, at the end of a call and after growth
+# steps (whose rho is summed on the side stream) the values and their order are
+# those of one call, bit for bit (single steps: any split gives the same bits).
+@pytest.mark.parametrize("M,L,dtype", [(4, 6, "c64"), (4, 6, "c128"), (3, 8, "c128")])
+def test_rho_rows_left_to_the_next_launch(M, L, dtype):
+    rng = np.random.default_rng(17)
+    w = W.spin_boson_l7().with_(M=M, L=L, s=np.linspace(-1, 1, M), H=W.random_hermitian(rng, M), xi=0.2,
+                                rho0=np.diag([1.0] + [0.0] * (M - 1)).astype(complex), dtype=dtype)
+    n = L + 8
+    print(f"M={M} L={L} {dtype}", flush=True)
+    with Q.create(Q.params_from(w)) as c:
+        assert c.mirror()
+        rho = c.propagate(n)
+    assert np.abs(np.trace(rho, axis1=1, axis2=2) - 1).max() <= (1e-6 if dtype == "c64" else 1e-12)
+    with Q.create(Q.params_from(w)) as c:
+        a = c.propagate(L + 1, [2, L, L + 1])
+        b = c.propagate(4, [L + 3, L + 4])
+        d = c.propagate(3)
+    for got, steps in ((a, [2, L, L + 1]), (b, [L + 3, L + 4]), (d, [L + 6, L + 7, L + 8])):
+        assert np.array_equal(got, rho[np.array(steps) - 1])
