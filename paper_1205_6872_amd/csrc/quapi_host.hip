@@ -2260,7 +2260,7 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
             c->small = small_lds_bytes(N, c->prec, L, true) <= (size_t)lds_max ? 1
                        : small_lds_bytes(N, c->prec, L, false) <= (size_t)lds_max ? 2 : 0;
             c->reg = N == 4 && L >= kRegMinL && L <= kRegMaxL &&
-                     small_reg_lds_bytes(L, c->prec) <= (size_t)lds_max;
+                     small_reg_lds_bytes(L) <= (size_t)lds_max;
         }
     }
     // a persistent-path context needs the two events of a batch, any other one

@@ -305,7 +305,7 @@ hipError_t launch_small(int N, int prec, bool in_lds, const SmallBatchArgs &b, i
 // The full-window steps past n = L of M = 2, L = 5 .. 7 with the tensor in a
 // block's registers (step0 >= L for every context, all of one L).
 constexpr int kRegMinL = 5, kRegMaxL = 7;
-size_t small_reg_lds_bytes(int L, int prec);
+size_t small_reg_lds_bytes(int L);
 hipError_t launch_small_reg(int prec, int L, const SmallBatchArgs &b, int n_ctx, hipStream_t st);
 // Fill every entry above its mirror (N = 4, 9 or 16) with the conjugate of the mirror.
 hipError_t launch_mirror_complete(int N, int prec, void *a, long long entries, hipStream_t st);
@@ -320,7 +320,7 @@ size_t step2_lds_bytes(int prec, bool with_rho, int R, int Q);
 constexpr int kTileSteps = 4;
 constexpr int kTileSets = 4 * kTileSteps;            // factor tables: (stage, class, o in {1, 2})
 constexpr int kTileMinL = 8;
-constexpr int kTileCoefK = 80;                       // coefficients in the compute precision, then
+constexpr int kTileCoefK = 80;                       // coefficients (see quapi_step4.h), then
 constexpr int kTileCoefCount = kTileCoefK + 64;      // 16 of K per stage in FP64
 constexpr int kTileBlocks = 1024;                    // blocks of a pass (rho rows of a step)
 struct TilePlanArgs {

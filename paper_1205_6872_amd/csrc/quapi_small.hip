@@ -335,12 +335,12 @@ constexpr int kRegSets = 8;              // (stage, class, o in {1, 2})
 // A thread stands for U of the 4^(L-2) columns of 16 entries.  U = 2 at L = 7: 1024
 // threads leave 128 registers each, of which FP64 values alone take 64 (spilled:
 // 17.3 us per step).
-template <int L, int CSIZE> struct SmallReg {
+template <int L> struct SmallReg {
     static constexpr int cols = 1 << (2 * (L - 2)), U = L == 7 ? 2 : 1;
     static constexpr int threads = cols / U, waves = threads / 64;
     static constexpr int hi = 1 << (2 * (L - 4));            // values of the column's digits above the lowest two
     static constexpr unsigned buf = cols * 16 * 8;           // exchange: 8 bytes per slot
-    static constexpr unsigned lds = buf + kRegSets * (16 + hi) * CSIZE + 2 * 2 * waves * 8 * 8;
+    static constexpr unsigned lds = buf + kRegSets * (16 + hi) * 16 + 2 * 2 * waves * 8 * 8;
 };
 // The slot of entry y (canonical index) is y ^ reg_bits(y): consecutive lanes'
 // 8-byte accesses cover the banks both at y = c + columns r (written) and at
@@ -348,16 +348,16 @@ template <int L, int CSIZE> struct SmallReg {
 __device__ __forceinline__ constexpr int reg_bits(int y) { return (y >> 5) & 15; }
 
 template <int L, typename S, typename T>
-__global__ void __launch_bounds__((SmallReg<L, 2 * sizeof(T)>::threads)) small_reg_kernel(const SmallBatchArgs args) {
+__global__ void __launch_bounds__(SmallReg<L>::threads) small_reg_kernel(const SmallBatchArgs args) {
     using C = typename Cx<T>::type;
     using CS = typename Cx<S>::type;
     using X = XSlot<C>;
-    using R = SmallReg<L, 2 * sizeof(T)>;
+    using R = SmallReg<L>;
     constexpr int TH = R::threads, U = R::U;
     extern __shared__ __align__(16) unsigned char smem[];
     typename X::type *s_x = (typename X::type *)smem;
-    C *s_lo = (C *)(smem + R::buf);                          // [set][16]
-    C *s_hi = s_lo + kRegSets * 16;                          // [set][hi]
+    double2 *s_lo = (double2 *)(smem + R::buf);              // [set][16]
+    double2 *s_hi = s_lo + kRegSets * 16;                          // [set][hi]
     double *s_red = (double *)(s_hi + kRegSets * R::hi);     // [pair parity][stage][wave][8]
     const SmallCtxArgs &a = args.c[blockIdx.x];
     int t = threadIdx.x;
@@ -365,7 +365,7 @@ __global__ void __launch_bounds__((SmallReg<L, 2 * sizeof(T)>::threads)) small_r
     const BankLayout B{L};
     const T *coef = (const T *)a.coef;
     // factors over the thread's digits d2 .. d_(L-1), the lowest two (with the
-    // prefix) and the others, formed in FP64 and rounded once
+    // prefix) and the others, in FP64
     for (int idx = t; idx < kRegSets * (16 + R::hi); idx += TH) {
         const bool lo = idx < kRegSets * 16;
         const int k = lo ? idx : idx - kRegSets * 16, q = lo ? k / 16 : k / R::hi;
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__((SmallReg<L, 2 * sizeof(T)>::threads)) small_r
         double2 p = lo ? prefix4(a.bank, a.eta, a.s, L, o, cls, st) : make_double2(1.0, 0.0);
         for (int j = lo ? 0 : 2; j < (lo ? 2 : L - 2); ++j, v >>= 2)
             p = cmul(p, tab4(a.bank, tile_tab(B, L - 2 - j + st, cls), o, v & 3));
-        (lo ? s_lo : s_hi)[k] = from_d2<C>(p);
+        (lo ? s_lo : s_hi)[k] = p;
     }
     // the previous point of a pair's first step is the highest digit of the column
     auto prev_k = [&](int c, double2 &k0, double2 &k3) {
@@ -418,8 +418,8 @@ __global__ void __launch_bounds__((SmallReg<L, 2 * sizeof(T)>::threads)) small_r
         par ^= 1;
     };
     // the wave's sums of one step: rows v0.x, v0.y, v1.x, v1.y (s0) and v2, v3 (s1)
-    auto add_rho = [&](int st, int c, C tf1, C tf2, double2 v0, double2 v3, double &s0, double &s1) {
-        const double2 v1 = to_d2(cmul(factor(4 * st + 2, c), tf1)), v2 = to_d2(cmul(factor(4 * st + 3, c), tf2));
+    auto add_rho = [&](int st, int c, double2 tf1, double2 tf2, double2 v0, double2 v3, double &s0, double &s1) {
+        const double2 v1 = cmul(factor(4 * st + 2, c), tf1), v2 = cmul(factor(4 * st + 3, c), tf2);
         s0 = row_add(s0, v0.x, 0, lane);
         s0 = row_add(s0, v0.y, 1, lane);
         s0 = row_add(s0, v1.x, 2, lane);
@@ -448,8 +448,7 @@ __global__ void __launch_bounds__((SmallReg<L, 2 * sizeof(T)>::threads)) small_r
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c = t + TH * u;
-            C tf1, tf2;
-            double2 rd0, rd3, k0{}, k3{};
+            double2 tf1, tf2, rd0, rd3, k0{}, k3{};
             __builtin_amdgcn_sched_barrier(0);
             if (ST == 0) prev_k(c, k0, k3);
             if (sel) {
@@ -508,7 +507,7 @@ __global__ void __launch_bounds__((SmallReg<L, 2 * sizeof(T)>::threads)) small_r
 
 template <int L, typename S, typename T>
 hipError_t launch_small_reg_t(const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
-    using R = SmallReg<L, 2 * sizeof(T)>;
+    using R = SmallReg<L>;
     hipLaunchKernelGGL((small_reg_kernel<L, S, T>), dim3(n_ctx), dim3(R::threads), R::lds, st, b);
     return hipGetLastError();
 }
@@ -552,9 +551,8 @@ size_t small_lds_bytes(int N, int prec, int L, bool in_lds) {
     return small_lds_layout(N, cs, cc, L, in_lds).total;
 }
 
-size_t small_reg_lds_bytes(int L, int prec) {
-    if (prec == kPrecC64) return L == 5 ? SmallReg<5, 8>::lds : L == 6 ? SmallReg<6, 8>::lds : SmallReg<7, 8>::lds;
-    return L == 5 ? SmallReg<5, 16>::lds : L == 6 ? SmallReg<6, 16>::lds : SmallReg<7, 16>::lds;
+size_t small_reg_lds_bytes(int L) {
+    return L == 5 ? SmallReg<5>::lds : L == 6 ? SmallReg<6>::lds : SmallReg<7>::lds;
 }
 
 hipError_t launch_small_reg(int prec, int L, const SmallBatchArgs &b, int n_ctx, hipStream_t st) {

@@ -18,13 +18,20 @@ namespace {
 //   sum_p = cos(theta) (x0 + x3) -+ i sin(theta) (x0 - x3) + e^{-+g} x1 + e^{+-g} x2,
 // 8 real multiply-adds instead of 16, and x0 + x3 serves the diagonal rows too.
 //
-// Coefficients in the compute precision, read by scalar loads: cos, sin,
-// e^{-g}, e^{g} of the oldest point (lag L; interior, final class) and of the
-// group digit at lag L-1 (stages 0 and 2, "pair 0"); for the group digit e at
-// lag 1, with K (stages 1 and 3, "pair 1"), per stage and e the complex factors
-// of o = 1, 2 (interior), then the final class; then per stage and e K[0][e],
-// K[3][e], in FP64 in every tier (from the kTileCoefK-th double).  The stages
-// differ in K for a driven system only.
+// Coefficients, read by scalar loads, 8 bytes of room each: cos, sin, e^{-g},
+// e^{g} of the oldest point (lag L; interior, final class) in the compute
+// precision, packed from the start; then in FP64 in every tier, at their index:
+// the same of the group digit at lag L-1 (stages 0 and 2, "pair 0"); for the
+// group digit e at lag 1, with K (stages 1 and 3, "pair 1"), per stage and e the
+// complex factors of o = 1, 2 (interior), then the final class; then per stage
+// and e K[0][e], K[3][e].  The stages differ in K for a driven system only.
+//
+// With FP32 arithmetic an entry's whole factor (outer digits, thread digits,
+// group digit) is formed in FP64 and rounded once, and a lane's rho terms are
+// FP64 products and sums of FP32 values: every rounding of a factor acts again
+// at each step.  rms of rho against complex128 over 120 steps, factors and terms
+// in FP32 -> this: L = 8 .. 11 9.9e-8 -> 7.6e-8 (the two-step kernel 8.8e-8),
+// L = 5 .. 7 7.8e-8 -> 5.4e-8; it takes 6% of a step at L = 15.
 constexpr int kTcOld = 0, kTcOldf = 4, kTcE = 8, kTcEf = 12, kTcLag1 = 16;
 __device__ __forceinline__ constexpr int tc_lag1(int stage) { return kTcLag1 + 32 * (stage >> 1); }
 __device__ __forceinline__ constexpr int tc_k(int stage) { return kTileCoefK + 16 * stage; }
@@ -128,20 +135,14 @@ __device__ __forceinline__ void coef_k(const T *coef, int stage, int prev, doubl
 // terms of the diagonal points (REAL: their real parts only).
 template <typename T, bool RHO, bool REAL, int STAGE, typename CI>
 __device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::type (&w)[16],
-                                           const T *coef, typename Cx<T>::type c1,
-                                           typename Cx<T>::type c2, double2 kp0, double2 kp3,
-                                           typename Cx<T>::type &tf1,
-                                           typename Cx<T>::type &tf2, double2 &rd0, double2 &rd3) {
+                                           const T *coef, double2 c1, double2 c2, double2 kp0, double2 kp3,
+                                           double2 &tf1, double2 &tf2, double2 &rd0, double2 &rd3) {
     using C = typename Cx<T>::type;
     constexpr int PAIR = STAGE % 2;
     constexpr int SI = PAIR == 0 ? 1 : 4, SE = PAIR == 0 ? 4 : 1;
     const T *co = fresh_t(coef);
     double2 all = make_double2(0.0, 0.0);
-    if (RHO) {
-        tf1 = C{};
-        tf2 = C{};
-        rd0 = rd3 = make_double2(0.0, 0.0);
-    }
+    if (RHO) tf1 = tf2 = rd0 = rd3 = make_double2(0.0, 0.0);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         __builtin_amdgcn_sched_barrier(0);      // a group at a time: fewer live registers
@@ -191,31 +192,30 @@ __device__ __forceinline__ void tile_stage(const CI (&in)[16], typename Cx<T>::t
         }
         // e's own factor: for pair 0 the four-coefficient form of the row
         auto factor_e = [&](int o, bool fin) {
-            C f;
+            const double *cd = (const double *)ce;
+            double2 f;
             if (PAIR == 0) {
                 const int k = fin ? kTcEf : kTcE;
-                f.x = coef_s(ce, e == 1 || e == 2 ? k + ((e == 1) == (o == 1) ? 2 : 3) : k);
-                f.y = (e == 0) == (o == 1) ? -coef_s(ce, k + 1) : coef_s(ce, k + 1);
+                f.x = coef_s(cd, e == 1 || e == 2 ? k + ((e == 1) == (o == 1) ? 2 : 3) : k);
+                f.y = (e == 0) == (o == 1) ? -coef_s(cd, k + 1) : coef_s(cd, k + 1);
             } else {
                 const int k = tc_lag1(STAGE) + 8 * e + 2 * (o - 1) + (fin ? 4 : 0);
-                f.x = coef_s(ce, k);
-                f.y = coef_s(ce, k + 1);
+                f.x = coef_s(cd, k);
+                f.y = coef_s(cd, k + 1);
             }
             return f;
         };
         constexpr bool kRealE = PAIR == 0;            // factors of e = 1, 2 are real
-        auto with_e = [&](C c, int o) {
-            const C f = factor_e(o, false);
-            if (!(kRealE && (e == 1 || e == 2))) return cmul(c, f);
-            c.x *= f.x;
-            c.y *= f.x;
-            return c;
+        auto with_e = [&](double2 c, int o) {
+            const double2 f = factor_e(o, false);
+            if (!(kRealE && (e == 1 || e == 2))) return from_d2<C>(cmul(c, f));
+            return from_d2<C>(make_double2(c.x * f.x, c.y * f.x));
         };
-        auto add_e = [&](C &sum, C v, int o) {        // sum += factor * v (final class)
-            const C f = factor_e(o, true);
+        auto add_e = [&](double2 &sum, C s, int o) {  // sum += factor * s (final class)
+            const double2 f = factor_e(o, true), v = to_d2(s);
             if (kRealE && (e == 1 || e == 2)) {
-                sum.x = fma_t(v.x, f.x, sum.x);
-                sum.y = fma_t(v.y, f.x, sum.y);
+                sum.x = fma(v.x, f.x, sum.x);
+                sum.y = fma(v.y, f.x, sum.y);
             } else {
                 cmac(sum, v, f);
             }

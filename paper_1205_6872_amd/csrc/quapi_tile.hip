@@ -74,7 +74,7 @@ __device__ __forceinline__ int tile_hi(int idx, int k, bool mirror, bool *self) 
 
 // ------------------------------------------------------------------ tables
 // set q = (s * 2 + cls) * 2 + (o - 1): t_w[q][w0 + 4 w1], t_u[q][u0 + 4 u1],
-// t_mid[q][v], t_top[q][v], all FP64; coef in the compute precision.
+// t_mid[q][v], t_top[q][v], all FP64; coef as quapi_step4.h has it.
 template <typename T>
 __global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs a) {
     const BankLayout B{a.L};
@@ -102,10 +102,9 @@ __global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs 
                 const double2 f = tab(B.k_lag1(), k / 2 % 2 * 3, (k - kTileCoefK) / 4 % 4);
                 v = k % 2 ? f.y : f.x;
                 if (sizeof(T) == 4) v = (float)v;           // exact: the diagonal rows of K are FP32 values
-                ((double *)a.coef)[k] = v;
-                continue;
             }
-            ((T *)a.coef)[k] = (T)v;
+            if (k < kTcE) ((T *)a.coef)[k] = (T)v;
+            else ((double *)a.coef)[k] = v;
             continue;
         }
         int q, v, j0, nd;
@@ -176,7 +175,7 @@ __global__ void __launch_bounds__(kBlock) tile_drive_kernel(const TileDriveArgs 
         if (idx < 64) {
             const int st = 1 + idx / 32 * 2, k = idx % 32, e = k / 8, cls = k / 4 % 2, o = 1 + k / 2 % 2;
             const double2 f = kf(st, cls, o, e);
-            ((T *)a.coef)[tc_lag1(st) + k] = (T)(k % 2 ? f.y : f.x);
+            ((double *)a.coef)[tc_lag1(st) + k] = k % 2 ? f.y : f.x;
         } else if (idx < 128) {
             const int k = idx - 64, st = k / 16;
             const double2 f = kf(st, -1, k / 2 % 2 * 3, k / 4 % 4);
@@ -301,8 +300,8 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
     using C = typename Cx<T>::type;
     using CS = typename Cx<S>::type;
     __shared__ __align__(16) unsigned char s_buf[kWaves][1024 * 8];
-    __shared__ C s_u[kSets * 16];
-    __shared__ C s_w[kWaves][64];              // [w1][set][w0]
+    __shared__ double2 s_u[kSets * 16];
+    __shared__ double2 s_w[kWaves][64];              // [w1][set][w0]
     double2 *const s_red = (double2 *)s_buf;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     if ((int)blockIdx.x >= a.n_work) {
@@ -402,15 +401,15 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         C w[16];
         if (!AHEAD) read_tile(hi, self, lane);
         if (idx == (int)blockIdx.x) {
-            s_u[t] = from_d2<C>(a.t_u[t]);         // once, behind the first tile's loads
+            s_u[t] = a.t_u[t];         // once, behind the first tile's loads
             __syncthreads();
         }
         // lane set * 4 + w0 forms the factor of its set for the wave's w1.  The
         // sets of stages 0 and 1 (lanes 0 .. 31) are read by this wave only;
         // those of stages 2 and 3 by every wave, after the exchange's barriers
-        C tile_f;
+        double2 tile_f;
         {
-            tile_f = from_d2<C>(cmul(cmul(top, mid), tw));
+            tile_f = cmul(cmul(top, mid), tw);
             wave_fence();
             if (lane < 32) s_w[wave][lane] = tile_f;
             wave_fence();
@@ -421,9 +420,9 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         };
         const int wl = wa + 4 * wave;
         // one stage's rho terms into the running sums
-        auto add_rho = [&](int s, int wl, int ul, C tf1, C tf2, double2 v0, double2 v3) {
-            const double2 v1 = to_d2(cmul(factor(4 * s + 2, wl, ul), tf1));
-            const double2 v2 = to_d2(cmul(factor(4 * s + 3, wl, ul), tf2));
+        auto add_rho = [&](int s, int wl, int ul, double2 tf1, double2 tf2, double2 v0, double2 v3) {
+            const double2 v1 = cmul(factor(4 * s + 2, wl, ul), tf1);
+            const double2 v2 = cmul(factor(4 * s + 3, wl, ul), tf2);
             if constexpr (MIRROR) {
                 // a tile below its mirror also stands for the mirrored tile
                 // (conjugate, points 1 and 2 swapped); rho[2] = conj(rho[1])
@@ -443,8 +442,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
                 acc[s][1] = row_add(acc[s][1], v3.y, 3, lane);
             }
         };
-        C tf1, tf2;
-        double2 rd0, rd3;
+        double2 tf1, tf2, rd0, rd3;
         // storage narrower than the arithmetic: the values are rounded to it where
         // a call may end without changing the result, after the pairs (n, n+1)
         // and (n+2, n+3), or for a driven system after every step
