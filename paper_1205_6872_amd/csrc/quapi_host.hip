@@ -579,7 +579,7 @@ struct quapi_ctx {
     // LDS, 2 tensor in the context's global buffers
     int small = 0;
     // its full-window steps run with the tensor in registers (M = 2, L = 5 .. 7)
-    bool reg = false, reg_coef_ready = false;
+    bool reg = false;
     // Mirror mode of the full-window kernels: they read and write only the
     // entries not above their mirror; half_cur says A[cur] holds only those.
     bool mirror_ok = false;       // M = 2, 3, 4, L >= 2, rho0 exactly Hermitian
@@ -1711,22 +1711,6 @@ bool small_on(const quapi_ctx *c) {
     return c->small != 0 && c->n_H == 0 && !c->fuse_pinned && c->mirror != 2;
 }
 
-// The coefficients of the register kernel, once per context.
-quapi_status reg_prepare(quapi_ctx *c) {
-    if (!c->reg || c->reg_coef_ready) return QUAPI_OK;
-    TilePlanArgs pa{};
-    pa.bank = c->bank;
-    pa.eta = c->eta;
-    pa.s = (const double *)(c->ws + c->lay.off_s);
-    pa.L = c->L;
-    pa.coef_only = 1;
-    pa.coef = c->tcoef;
-    const hipError_t e = launch_tile_tables(c->prec, pa, c->stream);
-    if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "coefficient kernel launch: %s", hipGetErrorString(e));
-    c->reg_coef_ready = true;
-    return QUAPI_OK;
-}
-
 // Steps of a run of k that the register kernel does not take: up to n = L.
 int reg_head(const quapi_ctx *c, int k) { return c->reg ? std::min(k, std::max(0, c->L - c->step)) : k; }
 
@@ -1783,7 +1767,6 @@ quapi_status propagate_small(quapi_ctx *c, int n_steps, const int *sel, int n_se
     }
     quapi_status st = join_side(c);
     if (st == QUAPI_OK) st = ensure_full(c);
-    if (st == QUAPI_OK) st = reg_prepare(c);
     if (st != QUAPI_OK) return st;
     auto flush = [&]() -> quapi_status {
         if (!staged) return QUAPI_OK;
@@ -2259,7 +2242,7 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
         if (ent <= (size_t)kSmallMaxEntries && !filtered) {
             c->small = small_lds_bytes(N, c->prec, L, true) <= (size_t)lds_max ? 1
                        : small_lds_bytes(N, c->prec, L, false) <= (size_t)lds_max ? 2 : 0;
-            c->reg = N == 4 && L >= kRegMinL && L <= kRegMaxL &&
+            c->reg = N == 4 && L >= kRegMinL && L <= kRegMaxL && p->n_H <= 0 &&
                      small_reg_lds_bytes(L) <= (size_t)lds_max;
         }
     }
@@ -2348,6 +2331,7 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
     ta.eta = c->eta;
     ta.bank = c->bank;
     ta.bank_f = c->bank_f;
+    ta.coef = c->reg ? c->tcoef : nullptr;
     ta.k_trace_exact = c->prec == kPrecC64;            // FP32 arithmetic: keep the trace exact per step
     c->drive_ta = ta;
     // U = exp(-i H dt): for a driven system every interval's, once, in
@@ -2600,7 +2584,6 @@ quapi_status quapi_propagate_batch(quapi_ctx *const *ctxs, int n_ctx, const int 
         quapi_ctx *c = ctxs[k];
         quapi_status st = join_side(c);
         if (st == QUAPI_OK) st = ensure_full(c);
-        if (st == QUAPI_OK) st = reg_prepare(c);
         if (st != QUAPI_OK) return st;
         if (k > 0) {
             HIP_TRY(c, hipEventRecord(c->ev_fork, c->stream));

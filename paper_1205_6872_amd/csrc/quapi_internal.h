@@ -238,6 +238,7 @@ struct TablesArgs {
     double2 *eta;               // out: 4L+2 classes
     double2 *bank;              // out: BankLayout{L}.count() tables
     float2 *bank_f;             // out (if not NULL): the same tables rounded to complex64
+    void *coef;                 // out (if not NULL): the register kernel's kTileCoefCount coefficients
     int k_trace_exact;          // K rows (a, a) chosen on the FP32 grid with exact column sums
     int k_only;                 // rewrite only the tables that carry K (driven H: per step); eta, U untouched
     const double2 *U_given;     // U (M x M) from launch_u_stack
@@ -327,7 +328,6 @@ struct TilePlanArgs {
     const double2 *bank, *eta;
     const double *s;
     int L, d_mid, d_top;
-    int coef_only;                                   // the coefficients only (the persistent kernel's)
     double2 *t_w, *t_u, *t_mid, *t_top;              // [set][16], [set][16], [set][4^d_mid], [set][4^d_top]
     void *coef;                                      // kTileCoefCount reals (8 bytes each)
 };

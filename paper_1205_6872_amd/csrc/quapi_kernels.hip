@@ -17,6 +17,7 @@
 
 #include "quapi_device.h"
 #include "quapi_internal.h"
+#include "quapi_step4.h"
 
 namespace quapi {
 namespace {
@@ -278,9 +279,7 @@ __global__ void __launch_bounds__(kBlock) tables_kernel(const TablesArgs a) {
         return tb == B.K() || tb == B.k_lag1() || tb == B.k_init1() || tb == B.k_fin1() ||
                tb == B.k_fin_init1() || (L == 1 && tb >= B.old_main() && tb <= B.oldf_first());
     };
-    for (int idx = blockIdx.x * kBlock + t; idx < n_tab * NN; idx += gridDim.x * kBlock) {
-        const int tb = idx / NN, o = (idx / N) % N, p = idx % N;
-        if (a.k_only && !carries_k(tb)) continue;
+    auto entry = [&](int tb, int o, int p) {
         const int oa = o / M, ob = o % M, pc = p / M, pd = p % M;
         const double2 Kop = [&] {
             if (a.k_trace_exact && oa == ob) return sKd[oa * N + p];
@@ -308,6 +307,17 @@ __global__ void __launch_bounds__(kBlock) tables_kernel(const TablesArgs a) {
             v = cmul(self, influence(sS, M, o, p, e));
             v = cmul(v, L == 1 ? Kop : one);
         }
+        return v;
+    };
+    const int n_ent = n_tab * NN, total = n_ent + (a.coef ? kTileCoefCount : 0);
+    for (int idx = blockIdx.x * kBlock + t; idx < total; idx += gridDim.x * kBlock) {
+        if (idx >= n_ent) {
+            put_coef(a.coef, idx - n_ent, L, sEta, sS, entry, a.k_trace_exact != 0);
+            continue;
+        }
+        const int tb = idx / NN;
+        if (a.k_only && !carries_k(tb)) continue;
+        const double2 v = entry(tb, (idx / N) % N, idx % N);
         a.bank[idx] = v;
         if (a.bank_f) a.bank_f[idx] = make_float2((float)v.x, (float)v.y);
     }
@@ -1288,7 +1298,7 @@ hipError_t launch_u_stack(const double2 *H_t, int n_H, int M, double dt, double2
 hipError_t launch_tables(const TablesArgs &a, hipStream_t st) {
     // an entry or two per thread (one block took 42 us for the 35 tables of
     // 16 x 16 at M = 4, L = 6)
-    const int total = BankLayout{a.L}.count() * a.M * a.M * a.M * a.M;
+    const int total = BankLayout{a.L}.count() * a.M * a.M * a.M * a.M + (a.coef ? kTileCoefCount : 0);
     hipLaunchKernelGGL(tables_kernel, dim3(std::min(64, (total + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, a);
     return hipGetLastError();
 }

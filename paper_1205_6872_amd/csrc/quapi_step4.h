@@ -38,18 +38,44 @@ __device__ __forceinline__ constexpr int tc_k(int stage) { return kTileCoefK + 1
 
 __device__ __forceinline__ constexpr int mirror_d(int d) { return d == 1 ? 2 : d == 2 ? 1 : d; }
 
-__device__ int tile_tab(const BankLayout &B, int lag, int cls) {
+__device__ __forceinline__ int tile_tab(const BankLayout &B, int lag, int cls) {
     if (lag == 1) return cls ? B.k_fin1() : B.k_lag1();
     return cls ? B.fin(lag) : B.lag(lag);
 }
 // F(mirror(o), mirror(p)) = conj(F(o, p)) bit for bit (the bank's K has it to
 // rounding), so that an entry and its mirror come out exactly conjugate.
-__device__ __forceinline__ double2 tab4(const double2 *bank, int t, int row, int col) {
-    const int k = row * 4 + col, km = mirror_d(row) * 4 + mirror_d(col);
-    double2 v = bank[(size_t)t * 16 + (km < k ? km : k)];
+// entry(t, o, p): the bank's table t.
+template <typename Entry>
+__device__ __forceinline__ double2 tab4_of(Entry entry, int t, int row, int col) {
+    const int k = row * 4 + col, km = mirror_d(row) * 4 + mirror_d(col), kk = km < k ? km : k;
+    double2 v = entry(t, kk / 4, kk % 4);
     if (km < k) v.y = -v.y;
     if (km == k) v.y = 0.0;
     return v;
+}
+__device__ __forceinline__ double2 tab4(const double2 *bank, int t, int row, int col) {
+    return tab4_of([&](int tb, int o, int p) { return bank[(size_t)tb * 16 + o * 4 + p]; }, t, row, col);
+}
+// Coefficient k (see above) into coef; fp32: the compute precision.
+template <typename Entry>
+__device__ __forceinline__ void put_coef(void *coef, int k, int L, const double2 *eta, const double *s, Entry entry,
+                                         bool fp32) {
+    const BankLayout B{L};
+    double v;
+    if (k < kTcLag1) {
+        const double2 et = eta[1 + (k / 4 % 2 ? 2 * L : 0) + (k < kTcE ? L : L - 1)];
+        const double D = s[0] - s[1], th = D * D * et.y, g = D * D * et.x;
+        v = k % 4 == 0 ? cos(th) : k % 4 == 1 ? sin(th) : exp(k % 4 == 2 ? -g : g);
+    } else {
+        const bool infl = k < kTileCoefK;               // lag 1, or the diagonal rows of K
+        const double2 f = tab4_of(entry, infl ? tile_tab(B, 1, k / 4 % 2) : B.k_lag1(),
+                                  infl ? 1 + k / 2 % 2 : k / 2 % 2 * 3,
+                                  infl ? (k - kTcLag1) / 8 % 4 : (k - kTileCoefK) / 4 % 4);
+        v = k % 2 ? f.y : f.x;
+        if (!infl && fp32) v = (float)v;                // exact: the diagonal rows of K are FP32 values
+    }
+    if (k < kTcE && fp32) ((float *)coef)[k] = (float)v;
+    else ((double *)coef)[k] = v;
 }
 // What the thread's factor of point o carries besides its digits' tables: the
 // self factor and the phases e^{-+i phi} of the oldest point and (pair 0) of the

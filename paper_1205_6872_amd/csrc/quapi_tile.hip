@@ -83,28 +83,13 @@ __global__ void __launch_bounds__(kBlock) tile_tables_kernel(const TilePlanArgs 
     // exactly conjugate under the mirror: a pass may read an entry or its mirror,
     // and its results do not depend on which it read
     auto tab = [&](int t, int row, int col) { return tab4(a.bank, t, row, col); };
-    const long long n_tab = a.coef_only ? 0 : (long long)kSets * (32 + n_mid + n_top);
+    const long long n_tab = (long long)kSets * (32 + n_mid + n_top);
     const long long total = n_tab + kTileCoefCount;
     for (long long idx = (long long)blockIdx.x * kBlock + threadIdx.x; idx < total;
          idx += (long long)gridDim.x * kBlock) {
         if (idx >= n_tab) {
-            const int k = (int)(idx - n_tab);
-            double v;
-            if (k < kTcLag1) {
-                const double2 eta = a.eta[1 + (k / 4 % 2 ? 2 * L : 0) + (k < kTcE ? L : L - 1)];
-                const double D = a.s[0] - a.s[1], th = D * D * eta.y, g = D * D * eta.x;
-                v = k % 4 == 0 ? cos(th) : k % 4 == 1 ? sin(th) : exp(k % 4 == 2 ? -g : g);
-            } else if (k < kTileCoefK) {
-                const int e = (k - kTcLag1) / 8 % 4, cls = k / 4 % 2, o = 1 + k / 2 % 2;
-                const double2 f = tab(tile_tab(B, 1, cls), o, e);
-                v = k % 2 ? f.y : f.x;
-            } else {
-                const double2 f = tab(B.k_lag1(), k / 2 % 2 * 3, (k - kTileCoefK) / 4 % 4);
-                v = k % 2 ? f.y : f.x;
-                if (sizeof(T) == 4) v = (float)v;           // exact: the diagonal rows of K are FP32 values
-            }
-            if (k < kTcE) ((T *)a.coef)[k] = (T)v;
-            else ((double *)a.coef)[k] = v;
+            put_coef(a.coef, (int)(idx - n_tab), L, a.eta, a.s,
+                     [&](int tb, int o, int p) { return a.bank[(size_t)tb * 16 + o * 4 + p]; }, sizeof(T) == 4);
             continue;
         }
         int q, v, j0, nd;
@@ -638,7 +623,7 @@ hipError_t launch_tile_rho(const TileRho &r, hipStream_t st) {
 
 hipError_t launch_tile_tables(int prec, const TilePlanArgs &a, hipStream_t st) {
     const long long total =
-        (a.coef_only ? 0 : (long long)kSets * (32 + (1LL << (2 * a.d_mid)) + (1LL << (2 * a.d_top)))) + kTileCoefCount;
+        (long long)kSets * (32 + (1LL << (2 * a.d_mid)) + (1LL << (2 * a.d_top))) + kTileCoefCount;
     const dim3 g((unsigned)std::min<long long>(1024, (total + kBlock - 1) / kBlock)), b(kBlock);
     if (prec == kPrecC64) hipLaunchKernelGGL(tile_tables_kernel<float>, g, b, 0, st, a);
     else hipLaunchKernelGGL(tile_tables_kernel<double>, g, b, 0, st, a);

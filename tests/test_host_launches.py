@@ -1,0 +1,70 @@
+"""The launches of the library's host code, on the CPU: the library runs in a
+process of its own on a HIP runtime that only logs kernel names
+(tests/fake_hip.c); no kernel runs, so nothing here looks at values."""
+import os
+import subprocess
+import sys
+import textwrap
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parent.parent
+LIB = ROOT / "paper_1205_6872_amd" / "_lib" / "libquapi.so"
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    """run(code): code as a program with `Q`, `W`, `np`, launched(call) -- the
+    kernels that call() launches, as (name, blocks, threads) -- and fake, the
+    runtime."""
+    d = tmp_path_factory.mktemp("fake_hip")
+    (d / "v.map").write_text("hip_4.2 { global: *; };\nhip_4.3 { global: hipGraph*; hipStreamBeginCapture; "
+                             "hipStreamEndCapture; } hip_4.2;\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", str(d / "libamdhip64.so.7"), "-Wl,-soname,libamdhip64.so.7",
+                    f"-Wl,--version-script={d / 'v.map'}", str(ROOT / "tests" / "fake_hip.c")], check=True)
+    head = textwrap.dedent(f"""
+        import ctypes, re, sys
+        import numpy as np
+        sys.path.insert(0, {str(ROOT)!r})
+        fake = ctypes.CDLL({str(d / 'libamdhip64.so.7')!r})
+        fake.fake_log.restype = ctypes.c_char_p
+        from paper_1205_6872_amd import quapi as Q, workloads as W
+        def short(name):
+            m = re.match(r"_ZN5quapi(?:12_GLOBAL__N_1)?(\\d+)", name)
+            k = int(m.group(1))
+            return name[m.end():m.end() + k]
+        def launched(call):
+            fake.fake_reset()
+            call()
+            return [(short(l.split()[0]), int(l.split()[1]), int(l.split()[2]))
+                    for l in fake.fake_log().decode().splitlines()]
+        def names(call):
+            return [n for n, _, _ in launched(call)]
+        """)
+
+    def go(code):
+        if not LIB.exists():
+            pytest.skip("the library is not built")
+        env = dict(os.environ, LD_LIBRARY_PATH=str(d))
+        r = subprocess.run([sys.executable, "-c", head + textwrap.dedent(code)], env=env, capture_output=True,
+                           text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return go
+
+
+def test_first_call_launches_what_later_calls_launch(run):
+    # the persistent path: everything a call needs beyond its own kernels is
+    # formed at create (a batch of fresh contexts, as the server's, would pay for
+    # it context by context)
+    run("""
+        for L in range(2, 8):
+            w = W.spin_boson_l7().with_(L=L)
+            ctxs = [Q.create(Q.params_from(w, dtype="c64")) for _ in range(24)]
+            buf = np.zeros((24, 40, 8))
+            call = lambda: Q.propagate_batch(ctxs, [30] * 24, [1] * 24, [b.ctypes.data for b in buf])
+            first = names(call)
+            assert set(first) <= {"small_kernel", "small_reg_kernel"} and len(first) <= 2, (L, first)
+            with Q.create(Q.params_from(w)) as c:
+                assert set(names(lambda: c.propagate(L + 9))) <= {"small_kernel", "small_reg_kernel"}
+        """)
