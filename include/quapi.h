@@ -242,7 +242,8 @@ quapi_status quapi_propagate_static(const quapi_params *p, int n_steps, const in
  * otherwise in the context's two buffers in HBM, which stay in the L2 cache
  * at these sizes; a step costs a workgroup barrier instead of kernel
  * launches.  For M = 2, dk_max = 5 .. 7, the steps past dk_max run in a second
- * launch with the tensor in the workgroup's registers.  Not for driven contexts, contexts whose launch width is pinned
+ * launch with the tensor in the workgroup's registers.  Not for driven
+ * contexts, contexts whose launch width is pinned
  * (quapi_set_fused_steps != 0) or mirror mode 2.  Results do not depend on
  * how a run is split into calls or batched.
  *   quapi_persistent:  *mode = 0 (multi-block kernels), 1 (persistent, tensor
@@ -255,7 +256,9 @@ quapi_status quapi_persistent(const quapi_ctx *ctx, int *mode);
  * in a parameter, Sec. IV).  Every context must be on the persistent path
  * (quapi_persistent != 0), and all must have the same M and dtype (their
  * memory lengths, baths, Hamiltonians and step counts may differ); one
- * workgroup runs one context, up to 32 contexts per launch.  Context k
+ * workgroup runs one context, up to 32 contexts per launch, side by side
+ * whatever their memory lengths (dk_max = 5 .. 7 after a launch of their growth
+ * steps; where both buffers do not fit LDS, that launch is another).  Context k
  * advances n_steps[k] >= 0 steps and writes rho to device memory
  * rho_out_dev[k] (caller-owned, complex128, N values per output):
  *   rho_mode[k] = 0 none, 1 every step (n_steps[k] outputs, 'allPoints'),

@@ -1809,7 +1809,7 @@ quapi_status propagate_small(quapi_ctx *c, int n_steps, const int *sel, int n_se
             if (e0) (void)hipEventRecord(e0, c->stream);
         }
         hipError_t e = head > 0 ? launch_small(N, c->prec, c->small == 1, b, 1, c->L, c->stream) : hipSuccess;
-        if (e == hipSuccess && head < k) e = launch_small_reg(c->prec, c->L, br, 1, c->stream);
+        if (e == hipSuccess && head < k) e = launch_small_reg(c->prec, br, 1, c->stream);
         if (e != hipSuccess) return fail(c, QUAPI_ERR_DEVICE, "persistent step launch: %s", hipGetErrorString(e));
         if (c->timing && e0 && e1) {
             (void)hipEventRecord(e1, c->stream);
@@ -2243,7 +2243,7 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
             c->small = small_lds_bytes(N, c->prec, L, true) <= (size_t)lds_max ? 1
                        : small_lds_bytes(N, c->prec, L, false) <= (size_t)lds_max ? 2 : 0;
             c->reg = N == 4 && L >= kRegMinL && L <= kRegMaxL && p->n_H <= 0 &&
-                     small_reg_lds_bytes(L) <= (size_t)lds_max;
+                     small_reg_lds_bytes(L, c->prec) <= (size_t)lds_max;
         }
     }
     // a persistent-path context needs the two events of a batch, any other one
@@ -2590,48 +2590,37 @@ quapi_status quapi_propagate_batch(quapi_ctx *const *ctxs, int n_ctx, const int 
             HIP_TRY(c0, hipStreamWaitEvent(bs, c->ev_fork, 0));
         }
     }
-    for (int mode = 1; mode <= 2; ++mode) {
-        SmallBatchArgs b;
-        int nb = 0, L_max = 1;
-        auto launch = [&]() -> quapi_status {
-            if (!nb) return QUAPI_OK;
-            hipError_t e = launch_small(c0->N, c0->prec, mode == 1, b, nb, L_max, bs);
-            if (e != hipSuccess) return fail(c0, QUAPI_ERR_DEVICE, "persistent batch launch: %s", hipGetErrorString(e));
-            nb = 0;
-            L_max = 1;
-            return QUAPI_OK;
-        };
+    // Steps past n = L of the M = 2 contexts whose tensor fits registers run in a
+    // launch of their own, after the others; shorter memory lengths ride along
+    // in it, so that a batch of several lengths has no launch after it to wait for.
+    bool any_reg = false;
+    for (int k = 0; k < n_ctx; ++k) any_reg = any_reg || (ctxs[k]->reg && reg_head(ctxs[k], n_steps[k]) < n_steps[k]);
+    auto rides = [&](const quapi_ctx *c) { return any_reg && c->N == 4 && c->L < kRegMinL && c->small == 1; };
+    SmallBatchArgs b;
+    int nb = 0, L_max = 1;
+    auto launch = [&](int mode) -> quapi_status {       // 1, 2: small_kernel's modes; 0: the register kernel
+        if (!nb) return QUAPI_OK;
+        const hipError_t e = mode ? launch_small(c0->N, c0->prec, mode == 1, b, nb, L_max, bs)
+                                  : launch_small_reg(c0->prec, b, nb, bs);
+        if (e != hipSuccess) return fail(c0, QUAPI_ERR_DEVICE, "persistent batch launch: %s", hipGetErrorString(e));
+        nb = 0;
+        L_max = 1;
+        return QUAPI_OK;
+    };
+    for (int mode : {1, 2, 0}) {
         for (int k = 0; k < n_ctx; ++k) {
             quapi_ctx *c = ctxs[k];
-            const int head = reg_head(c, n_steps[k]);
-            if (c->small != mode || head == 0) continue;
-            SmallCtxArgs rest;
-            split_small(small_args(c, n_steps[k], rho_mode[k], (double2 *)rho_out_dev[k]), head, &b.c[nb++], &rest);
+            const bool ride = rides(c);
+            const int head = ride ? 0 : reg_head(c, n_steps[k]);
+            if (mode ? c->small != mode || head == 0 : head == n_steps[k]) continue;
+            SmallCtxArgs first, rest;
+            split_small(small_args(c, n_steps[k], rho_mode[k], (double2 *)rho_out_dev[k]), head, &first, &rest);
+            b.c[nb++] = mode ? first : rest;
             L_max = std::max(L_max, c->L);
             if (nb == kMaxSmallBatch)
-                if (quapi_status st = launch(); st != QUAPI_OK) return st;
+                if (quapi_status st = launch(mode); st != QUAPI_OK) return st;
         }
-        if (quapi_status st = launch(); st != QUAPI_OK) return st;
-    }
-    // the steps past n = L of the M = 2 contexts whose tensor fits registers, a
-    // launch per memory length
-    for (int L = kRegMaxL; L >= kRegMinL; --L) {
-        SmallBatchArgs b;
-        int nb = 0;
-        for (int k = 0; k <= n_ctx; ++k) {
-            if (nb == kMaxSmallBatch || (k == n_ctx && nb > 0)) {
-                hipError_t e = launch_small_reg(c0->prec, L, b, nb, bs);
-                if (e != hipSuccess)
-                    return fail(c0, QUAPI_ERR_DEVICE, "persistent batch launch: %s", hipGetErrorString(e));
-                nb = 0;
-            }
-            if (k == n_ctx) break;
-            quapi_ctx *c = ctxs[k];
-            const int head = reg_head(c, n_steps[k]);
-            if (!c->reg || c->L != L || head == n_steps[k]) continue;
-            SmallCtxArgs first;
-            split_small(small_args(c, n_steps[k], rho_mode[k], (double2 *)rho_out_dev[k]), head, &first, &b.c[nb++]);
-        }
+        if (quapi_status st = launch(mode); st != QUAPI_OK) return st;
     }
     for (int k = 0; k < n_ctx; ++k) small_advance(ctxs[k], n_steps[k]);
     // later work on every other context's stream waits for the launches

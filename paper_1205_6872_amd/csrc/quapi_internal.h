@@ -304,10 +304,11 @@ size_t small_lds_bytes(int N, int prec, int L, bool in_lds);
 hipError_t launch_small(int N, int prec, bool in_lds, const SmallBatchArgs &b, int n_ctx, int L_max,
                         hipStream_t st);
 // The full-window steps past n = L of M = 2, L = 5 .. 7 with the tensor in a
-// block's registers (step0 >= L for every context, all of one L).
+// block's registers (step0 >= L), and M = 2 contexts of L < 5 whole (any step0,
+// tensor in LDS).
 constexpr int kRegMinL = 5, kRegMaxL = 7;
-size_t small_reg_lds_bytes(int L);
-hipError_t launch_small_reg(int prec, int L, const SmallBatchArgs &b, int n_ctx, hipStream_t st);
+size_t small_reg_lds_bytes(int L, int prec);
+hipError_t launch_small_reg(int prec, const SmallBatchArgs &b, int n_ctx, hipStream_t st);
 // Fill every entry above its mirror (N = 4, 9 or 16) with the conjugate of the mirror.
 hipError_t launch_mirror_complete(int N, int prec, void *a, long long entries, hipStream_t st);
 hipError_t launch_step3_coef(const Coef3Args &a, hipStream_t st);

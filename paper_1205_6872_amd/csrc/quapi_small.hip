@@ -11,12 +11,14 @@
 // sum out the oldest point -- but the whole step sequence stays inside one
 // workgroup, so a step costs a barrier rather than three kernel launches.
 // Two kernels: small_reg_kernel keeps the tensor of M = 2, L = 5..7 in the
-// block's registers (full-window steps); small_kernel runs everything else
-// (growth, other N and L), its tensor ping-ponging between two LDS buffers when
+// block's registers (full-window steps; in a mixed batch it also takes shorter
+// memory lengths); small_kernel runs everything else (growth, other N and L),
+// its tensor ping-ponging between two LDS buffers when
 // both fit (N^L up to 4096 at complex128), else between the context's two
 // global buffers, which stay in the L2 cache at these sizes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "quapi_internal.h"
@@ -112,14 +114,13 @@ __device__ double2 small_digit_product(const double2 *__restrict__ bank, TabOf t
     return p;
 }
 
-template <int N, typename S, typename T, bool IN_LDS>
-__global__ void __launch_bounds__(SmallBlock<N>::threads) small_kernel(const SmallBatchArgs args) {
-    constexpr int kSB = SmallBlock<N>::threads, kSW = SmallBlock<N>::waves;
+// One context's steps by a block of kSB threads.
+template <int N, typename S, typename T, bool IN_LDS, int kSB>
+__device__ __forceinline__ void small_body(const SmallCtxArgs &a, unsigned char *smem) {
+    constexpr int kSW = kSB / 64;
     using C = typename Cx<T>::type;
     using CS = typename Cx<S>::type;
     constexpr int M = N == 1 ? 1 : N == 4 ? 2 : N == 9 ? 3 : 4;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const SmallCtxArgs a = args.c[blockIdx.x];
     const int L = a.L;
     const BankLayout B{L};
     const SmallLds lay = small_lds_layout(N, (int)sizeof(CS), (int)sizeof(C), L, IN_LDS);
@@ -313,6 +314,13 @@ __global__ void __launch_bounds__(SmallBlock<N>::threads) small_kernel(const Sma
     }
 }
 
+template <int N, typename S, typename T, bool IN_LDS>
+__global__ void __launch_bounds__(SmallBlock<N>::threads) small_kernel(const SmallBatchArgs args) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const SmallCtxArgs a = args.c[blockIdx.x];
+    small_body<N, S, T, IN_LDS, SmallBlock<N>::threads>(a, smem);
+}
+
 // ------------------------------------------------ the window in registers
 // Full-window steps n > L of an M = 2 context with L = 5, 6 or 7, all steps of a
 // call in one launch: the tensor stays in the registers of one block, 16 entries
@@ -348,18 +356,16 @@ template <int L> struct SmallReg {
 __device__ __forceinline__ constexpr int reg_bits(int y) { return (y >> 5) & 15; }
 
 template <int L, typename S, typename T>
-__global__ void __launch_bounds__(SmallReg<L>::threads) small_reg_kernel(const SmallBatchArgs args) {
+__device__ __forceinline__ void reg_body(const SmallCtxArgs &a, unsigned char *smem) {
     using C = typename Cx<T>::type;
     using CS = typename Cx<S>::type;
     using X = XSlot<C>;
     using R = SmallReg<L>;
     constexpr int TH = R::threads, U = R::U;
-    extern __shared__ __align__(16) unsigned char smem[];
     typename X::type *s_x = (typename X::type *)smem;
     double2 *s_lo = (double2 *)(smem + R::buf);              // [set][16]
     double2 *s_hi = s_lo + kRegSets * 16;                          // [set][hi]
     double *s_red = (double *)(s_hi + kRegSets * R::hi);     // [pair parity][stage][wave][8]
-    const SmallCtxArgs &a = args.c[blockIdx.x];
     int t = threadIdx.x;
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const BankLayout B{L};
@@ -505,19 +511,28 @@ __global__ void __launch_bounds__(SmallReg<L>::threads) small_reg_kernel(const S
         for (int r = 0; r < 16; ++r) dst[index(t + TH * u, r)] = conv<CS>(w[u][r]);
 }
 
-template <int L, typename S, typename T>
-hipError_t launch_small_reg_t(const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
-    using R = SmallReg<L>;
-    hipLaunchKernelGGL((small_reg_kernel<L, S, T>), dim3(n_ctx), dim3(R::threads), R::lds, st, b);
-    return hipGetLastError();
+// A block per context, each with the threads of its own memory length (the
+// waves beyond them end at once; a barrier waits for those that are left): one
+// launch takes as long as its slowest context.  In a batch of other lengths it
+// also runs, whole, the contexts of L < kRegMinL, whose full-window steps have
+// at most 64 items: one wave.  A call of 150 steps on 24 contexts, complex64, rho
+// at every step, a launch per length -> this: L = 5, 6 552 -> 354 us, L = 4, 5
+// 584 -> 378, L = 3 .. 6 814 -> 390; L = 7 alone 690 -> 719, complex128 766 -> 750
+// (a kernel per length allots each its own registers).
+constexpr int kRegThreads = SmallReg<kRegMaxL>::threads;
+constexpr int reg_threads(int L) {
+    return L == 7 ? SmallReg<7>::threads : L == 6 ? SmallReg<6>::threads : L == 5 ? SmallReg<5>::threads : 64;
 }
-template <int L>
-hipError_t launch_small_reg_l(int prec, const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
-    switch (prec) {
-    case kPrecC128: return launch_small_reg_t<L, double, double>(b, n_ctx, st);
-    case kPrecC64: return launch_small_reg_t<L, float, float>(b, n_ctx, st);
-    case kPrecC64F64: return launch_small_reg_t<L, float, double>(b, n_ctx, st);
-    default: return hipErrorInvalidValue;
+template <typename S, typename T>
+__global__ void __launch_bounds__(kRegThreads) small_reg_kernel(const SmallBatchArgs args) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const SmallCtxArgs &a = args.c[blockIdx.x];
+    if ((int)threadIdx.x >= reg_threads(a.L)) return;
+    switch (a.L) {
+    case 7: reg_body<7, S, T>(a, smem); break;
+    case 6: reg_body<6, S, T>(a, smem); break;
+    case 5: reg_body<5, S, T>(a, smem); break;
+    default: small_body<4, S, T, true, 64>(a, smem); break;
     }
 }
 
@@ -551,18 +566,29 @@ size_t small_lds_bytes(int N, int prec, int L, bool in_lds) {
     return small_lds_layout(N, cs, cc, L, in_lds).total;
 }
 
-size_t small_reg_lds_bytes(int L) {
+size_t small_reg_lds_bytes(int L, int prec) {
+    if (L < kRegMinL) return small_lds_bytes(4, prec, L, true);
     return L == 5 ? SmallReg<5>::lds : L == 6 ? SmallReg<6>::lds : SmallReg<7>::lds;
 }
 
-hipError_t launch_small_reg(int prec, int L, const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
+hipError_t launch_small_reg(int prec, const SmallBatchArgs &b, int n_ctx, hipStream_t st) {
     if (n_ctx < 1 || n_ctx > kMaxSmallBatch) return hipErrorInvalidValue;
-    switch (L) {
-    case 5: return launch_small_reg_l<5>(prec, b, n_ctx, st);
-    case 6: return launch_small_reg_l<6>(prec, b, n_ctx, st);
-    case 7: return launch_small_reg_l<7>(prec, b, n_ctx, st);
+    int threads = 0;
+    size_t lds = 0;
+    for (int k = 0; k < n_ctx; ++k) {
+        const int L = b.c[k].L;
+        if (L < 1 || L > kRegMaxL) return hipErrorInvalidValue;
+        threads = std::max(threads, reg_threads(L));
+        lds = std::max(lds, small_reg_lds_bytes(L, prec));
+    }
+    const dim3 g(n_ctx), t(threads);
+    switch (prec) {
+    case kPrecC128: hipLaunchKernelGGL((small_reg_kernel<double, double>), g, t, lds, st, b); break;
+    case kPrecC64: hipLaunchKernelGGL((small_reg_kernel<float, float>), g, t, lds, st, b); break;
+    case kPrecC64F64: hipLaunchKernelGGL((small_reg_kernel<float, double>), g, t, lds, st, b); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
 }
 
 hipError_t launch_small(int N, int prec, bool in_lds, const SmallBatchArgs &b, int n_ctx, int L_max,

@@ -68,3 +68,25 @@ def test_first_call_launches_what_later_calls_launch(run):
             with Q.create(Q.params_from(w)) as c:
                 assert set(names(lambda: c.propagate(L + 9))) <= {"small_kernel", "small_reg_kernel"}
         """)
+
+
+def test_mixed_batch_is_one_launch_after_the_growth_steps(run):
+    # contexts of every memory length side by side: the growth steps (a launch for
+    # each of the persistent path's two modes), then one launch for all the rest
+    run("""
+        for Ls in ((5, 6), (4, 5), (1, 2, 3, 4, 5, 6), (6, 7), (2, 4, 5, 6, 7)):
+            ctxs = [Q.create(Q.params_from(W.spin_boson_l7().with_(L=Ls[k % len(Ls)]))) for k in range(24)]
+            n = [30] * 23 + [0]
+            buf = np.zeros((24, 30, 8))
+            call = lambda: Q.propagate_batch(ctxs, n, [1] * 24, [b.ctypes.data for b in buf])
+            got = launched(call)
+            assert [g[0] for g in got] == ["small_kernel"] * (1 + (7 in Ls)) + ["small_reg_kernel"], (Ls, got)
+            assert got[-1][1] == 23
+            assert names(call) == ["small_reg_kernel"]                   # past the growth steps
+        # one length, or none that keeps its tensor in registers: as it was
+        for Ls in ((4,), (3, 4)):
+            ctxs = [Q.create(Q.params_from(W.spin_boson_l7().with_(L=Ls[k % len(Ls)]))) for k in range(40)]
+            buf = np.zeros((40, 30, 8))
+            got = launched(lambda: Q.propagate_batch(ctxs, [30] * 40, [1] * 40, [b.ctypes.data for b in buf]))
+            assert [g[:2] for g in got] == [("small_kernel", 32), ("small_kernel", 8)], got
+        """)
