@@ -1850,8 +1850,15 @@ quapi_status propagate_impl(quapi_ctx *c, int n_steps, const int *sel, int n_sel
     if (n_out > 0 && !dev_out && !host_out) return fail(c, QUAPI_ERR_INVALID, "rho_out is NULL");
     if (small_on(c)) return propagate_small(c, n_steps, sel, n_sel, dev_out, host_out);
     const int N = c->N, L = c->L;
-    c->tile_pending.n = 0;               // an earlier call that failed may have left its own
-    c->pend_rows = 0;
+    // rho still to be summed is this call's: one that fails leaves none of it to a
+    // later call, whose output buffers are others
+    struct Pending {
+        quapi_ctx *c;
+        ~Pending() {
+            c->tile_pending.n = 0;
+            c->pend_rows = 0;
+        }
+    } pending{c};
     int si = 0;          // next selection entry
     int written = 0;     // outputs delivered so far
     int staged = 0;      // outputs in the staging buffer (blocking call)

@@ -90,3 +90,29 @@ def test_mixed_batch_is_one_launch_after_the_growth_steps(run):
             got = launched(lambda: Q.propagate_batch(ctxs, [30] * 40, [1] * 40, [b.ctypes.data for b in buf]))
             assert [g[:2] for g in got] == [("small_kernel", 32), ("small_kernel", 8)], got
         """)
+
+
+@pytest.mark.parametrize("M,L", [(3, 7), (2, 8)])        # rho left to the next step's launch; to the next pass
+def test_a_failed_call_leaves_no_rho_to_later_ones(run, M, L):
+    # launches fail from the n-th of a call on: no sum of its rho runs after it
+    run(f"""
+        M, L = {M}, {L}
+        w = W.spin_boson_l7().with_(M=M, L=L, s=np.linspace(-1, 1, M), H=np.diag(np.arange(1.0, M + 1)),
+                                    rho0=np.eye(M) / M, H_t=np.stack([np.diag(np.arange(1.0, M + 1))] * 3))
+        rho0 = np.zeros(M * M, dtype=complex)
+        sums = lambda ns: [n for n in ns if n.startswith(("rho_", "tile_rho"))]
+        with Q.create(Q.params_from(w)) as c:
+            total = len(names(lambda: c.propagate(L + 6)))
+        for n in range(total):
+            with Q.create(Q.params_from(w)) as c:
+                fake.fake_fail_after(n)
+                try:
+                    c.propagate(L + 6)
+                    raise SystemExit("the call did not fail")
+                except Q.QuapiError as e:
+                    assert e.status == Q.ERR_DEVICE
+                fake.fake_fail_after(-1)
+                assert not sums(names(lambda: (c.restore(0, rho0), c.read_tensor(0, 1)))), n
+                got = launched(lambda: c.propagate(L + 6))
+                assert all(b in (M * M, 256, 1, 2, 3, 4) for k, b, _ in got if k.startswith(("rho_", "tile_rho")))
+        """)
