@@ -213,7 +213,7 @@ quapi_status quapi_filter_read(quapi_ctx *ctx, size_t first, size_t count, long 
  * propagation -- the setup of quapi_create, n_steps steps from step 0 and
  * rho at the selected steps, as quapi_propagate_async -- with its entire
  * working set (both tensors, the factor tables and the rho reduction
- * buffers) in a static device array of 64 MiB that the library holds on each
+ * buffers) in a static device array of 65 MiB that the library holds on each
  * GPU until the process ends.  It calls no hipMalloc or hipFree and creates
  * no streams or events: every kernel runs on hip_stream (NULL: the null
  * stream).
@@ -229,7 +229,8 @@ quapi_status quapi_filter_read(quapi_ctx *ctx, size_t first, size_t count, long 
  * serialized by the library, and a call must not overlap other work that
  * reads or writes it (there is none outside this call).
  * Errors: QUAPI_ERR_INVALID for malformed parameters or selection, NULL
- * rho_out_dev with outputs selected, or a working set (quapi_footprint)
+ * rho_out_dev with outputs selected, or a working set (quapi_footprint, less
+ * the fraction of a MiB of tables and rho rows of the four-step launches)
  * above 64 MiB (e.g. M = 2 beyond dk_max = 10 at complex128); QUAPI_ERR_DEVICE
  * for runtime or launch failures. */
 quapi_status quapi_propagate_static(const quapi_params *p, int n_steps, const int *sel, int n_sel,

@@ -324,6 +324,7 @@ struct Layout {
     // starts, scan partials, counters, rho partials, factor-level tables
     size_t off_fkeys[2], off_fvals[2], off_fmask, off_fbofs, off_fctr, off_fpart, off_fplan;
     size_t up_bytes;                 // bytes of the host's inputs, from off_s on
+    size_t side_bytes;               // of the buffers that the static scratch's limit leaves out
     size_t fplan_entries;            // entries of one factor-level table set
     size_t total;
     int n_panels, n_tables, partial_blocks;
@@ -456,7 +457,14 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_bank = take((size_t)l.n_tables * N * N * 16);
     l.off_bankf = take(p.dtype == QUAPI_C64 ? (size_t)l.n_tables * N * N * 8 : 0);
     l.off_g = take((size_t)(2 * L + 3) * 16);
-    l.off_gpart = take((size_t)(2 * L + 3) * quad_parts(n_panels) * 2 * 16);
+    // buffers that a working set of 64 MiB may hold beyond that (kStaticScratchBytes)
+    l.side_bytes = 0;
+    auto take_side = [&](size_t bytes) {
+        const size_t at = take(bytes);
+        l.side_bytes += off - at;
+        return at;
+    };
+    l.off_gpart = take_side((size_t)(2 * L + 3) * quad_parts(n_panels) * 2 * 16);
     l.off_eta = take((size_t)(4 * L + 2) * 16);
     l.off_U = take((size_t)M * M * 16);
     l.off_Ut = take((size_t)std::max(p.n_H, 0) * M * M * 16);
@@ -497,10 +505,10 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_plan3 = take(triple ? (size_t)6 * N * (s3.R + s3.Q + s3.grid) * 16 : 0);
     l.off_coef3 = take(triple ? (size_t)kC3Count * 16 : 0);
     const bool tile = !filtered && tile_ok(N, L);
-    l.off_ttab = take(tile ? tile_table_entries(L) * 16 : 0);
+    l.off_ttab = take_side(tile ? tile_table_entries(L) * 16 : 0);
     const bool reg = !filtered && N == 4 && L >= kRegMinL && L <= kRegMaxL;
-    l.off_tcoef = take(tile || reg ? (size_t)kTileCoefCount * 8 : 0);
-    l.off_trows = take(tile ? (size_t)2 * kTileSteps * tile_blocks(L) * N * 16 : 0);
+    l.off_tcoef = take_side(tile || reg ? (size_t)kTileCoefCount * 8 : 0);
+    l.off_trows = take_side(tile ? (size_t)2 * kTileSteps * tile_blocks(L) * N * 16 : 0);
     const size_t fc = filtered ? filter_cap : 0;
     for (int b = 0; b < 2; ++b) {
         l.off_fkeys[b] = take(fc * 8);
@@ -511,7 +519,7 @@ Layout make_layout(const quapi_params &p, int n_panels, size_t filter_cap = 0) {
     l.off_fctr = take(filtered ? 8 * 8 : 0);          // entry counts of both buffers, overflow flag
     l.off_fpart = take(filtered ? (size_t)kFilterStepBlocks * N * 16 : 0);
     l.fplan_entries = filtered ? std::max<size_t>(1, filter_plan_entries(N, L - 1)) : 0;
-    l.off_fplan = take((l.fplan_entries + 1) * 2 * 16);
+    l.off_fplan = take(filtered ? (l.fplan_entries + 1) * 2 * 16 : 0);
     l.total = off;
     return l;
 }
@@ -2382,8 +2390,11 @@ quapi_status create_ctx(const quapi_params *p, void *hip_stream, void *workspace
 // every GPU the library runs on, held until the process ends.  In host code
 // the array's name is not a device address: kernels and copies get the
 // address hipGetSymbolAddress returns on the current device.
-constexpr size_t kStaticScratchBytes = size_t(64) << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// A call is taken when its working set without the four-step kernel's tables and
+// rho rows and the quadrature's parts (side_bytes, at most 0.4 MB at any
+// parameters that fit) is 64 MiB or less.
+constexpr size_t kStaticScratchBytes = size_t(64) << 20, kStaticSideBytes = size_t(1) << 20;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticSideBytes];
 
 namespace {
 constexpr int kMaxStaticDevices = 64;
@@ -2489,8 +2500,9 @@ quapi_status quapi_propagate_static(const quapi_params *p, int n_steps, const in
     const std::string msg = validate(p);
     if (!msg.empty()) return fail(nullptr, QUAPI_ERR_INVALID, "%s", msg.c_str());
     if (n_steps < 0) return fail(nullptr, QUAPI_ERR_INVALID, "n_steps must be >= 0");
-    const size_t need = make_layout(*p, count_panels(*p)).total;
-    if (need > kStaticScratchBytes)
+    const Layout lay = make_layout(*p, count_panels(*p));
+    const size_t need = lay.total - lay.side_bytes;
+    if (need > kStaticScratchBytes || lay.side_bytes > kStaticSideBytes)
         return fail(nullptr, QUAPI_ERR_INVALID,
                     "the working set needs %zu bytes; the static scratch holds %zu (use quapi_create)", need,
                     kStaticScratchBytes);
@@ -2507,7 +2519,7 @@ quapi_status quapi_propagate_static(const quapi_params *p, int n_steps, const in
         g_static_ptr[dev] = ptr;
     }
     quapi_ctx *c = nullptr;
-    quapi_status st = create_ctx(p, hip_stream, g_static_ptr[dev], kStaticScratchBytes, true, &c);
+    quapi_status st = create_ctx(p, hip_stream, g_static_ptr[dev], kStaticScratchBytes + kStaticSideBytes, true, &c);
     if (st != QUAPI_OK) return st;
     int n_out = 0;
     st = check_selection(c, n_steps, sel, n_sel, &n_out);

@@ -59,7 +59,7 @@ err_t hipLaunchKernel(const void *fn, dim3_t g, dim3_t b, void **args, size_t sh
 err_t hipGetLastError(void) { err_t e = g_last; g_last = kOk; return e; }
 const char *hipGetErrorString(err_t e) { return e ? "failed as asked" : "no error"; }
 
-err_t hipMalloc(void **p, size_t n) { *p = calloc(n ? n : 1, 1); return *p ? kOk : 2; }
+err_t hipMalloc(void **p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256 + 256); return *p ? kOk : 2; }
 err_t hipFree(void *p) { free(p); return kOk; }
 err_t hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)kind; memcpy(d, s, n); return kOk; }
 err_t hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *st) {
@@ -73,7 +73,7 @@ err_t hipDeviceGetAttribute(int *v, int attr, int dev) { (void)attr; (void)dev; 
 err_t hipGetSymbolAddress(void **p, const void *sym) {
     (void)sym;
     static void *mem;
-    if (!mem) mem = calloc((size_t)96 << 20, 1);
+    if (!mem) mem = aligned_alloc(256, (size_t)96 << 20);
     *p = mem;
     return mem ? kOk : 2;
 }

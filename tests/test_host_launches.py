@@ -116,3 +116,21 @@ def test_a_failed_call_leaves_no_rho_to_later_ones(run, M, L):
                 got = launched(lambda: c.propagate(L + 6))
                 assert all(b in (M * M, 256, 1, 2, 3, 4) for k, b, _ in got if k.startswith(("rho_", "tile_rho")))
         """)
+
+
+def test_static_calls_at_the_limit_of_their_scratch(run):
+    # 64 MiB without the four-step kernel's tables and rho rows and the
+    # quadrature's parts: the longest stacks of Hamiltonians that are taken
+    run("""
+        for M, L, dtype, most in ((2, 10, "c128", 254604), (2, 10, "c64", 385624), (2, 8, "c128", 505940),
+                                  (2, 6, "c64", 522144), (2, 3, "c128", 523348), (3, 6, "c128", 170739),
+                                  (4, 4, "c64", 127134), (4, 5, "c128", 63706)):
+            for n, taken in ((most, True), (most + 1, False)):
+                p = Q.params(M=M, s=np.arange(M), H=np.eye(M), rho0=np.eye(M) / M, kT=0.2, dt=0.1, L=L, dtype=dtype,
+                             xi=0.1, omega_c=5.0, H_t=np.broadcast_to(np.eye(M), (n, M, M)))
+                try:
+                    Q.propagate_static(p, 1, [], 0)
+                    assert taken, (M, L, dtype, n)
+                except Q.QuapiError as e:
+                    assert not taken and e.status == Q.ERR_INVALID, (M, L, dtype, n)
+        """)
