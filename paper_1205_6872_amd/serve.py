@@ -74,11 +74,10 @@ def est_work_s(w) -> float:
 
 def _group_steps(w, ctx) -> int:
     """Steps of a launch group past the growth phase: a chunk that ends inside
-    one takes an extra pass over the tensor (M = 2 from L = 8 on runs four
-    steps per pass, grouped from step L + 1), and one that ends inside a fused
-    group rounds differently from one call of all steps."""
-    f = ctx.fused_steps()
-    return 4 if f > 1 and w.L >= 8 else f
+    one takes an extra pass over the tensor (M = 2 from L = 8 on, driven or not,
+    runs four steps per pass, grouped from step L + 1), and one that ends inside
+    a fused group rounds differently from one call of all steps."""
+    return 4 if w.M == 2 and w.L >= 8 else ctx.fused_steps()
 
 
 @dataclass

@@ -134,3 +134,22 @@ def test_static_calls_at_the_limit_of_their_scratch(run):
                 except Q.QuapiError as e:
                     assert not taken and e.status == Q.ERR_INVALID, (M, L, dtype, n)
         """)
+
+
+def test_server_chunks_are_whole_passes(run):
+    # chunks that end on the server's group of steps take no part of a pass
+    run("""
+        from paper_1205_6872_amd import serve
+        for L, dtype, driven in ((8, "c128", False), (13, "c64", False), (9, "c64f64", True), (8, "c128", True)):
+            H_t = np.stack([np.diag([1.0, -1.0])] * 3) if driven else None
+            w = W.spin_boson_l7().with_(L=L, dtype=dtype, H_t=H_t)
+            with Q.create(Q.params_from(w)) as c:
+                k = serve._group_steps(w, c)
+                c.propagate(L, sel=[])
+                got = names(lambda: [c.propagate(n, sel=[]) for n in (k, 2 * k, k)])
+                assert got.count("tile_kernel") == k, (L, dtype, driven, k, got)
+        for M, L, dtype in ((2, 7, "c128"), (2, 6, "c64"), (3, 8, "c128")):
+            w = W.spin_boson_l7().with_(M=M, L=L, dtype=dtype, s=np.arange(M), H=np.eye(M), rho0=np.eye(M) / M)
+            with Q.create(Q.params_from(w)) as c:
+                assert serve._group_steps(w, c) == c.fused_steps()
+        """)
