@@ -272,16 +272,22 @@ __global__ void __launch_bounds__(kBlock) tile_rho_kernel(const TileRho r) {
 // by the same operations whatever the ranges a group is run in.
 // PART: kWhole all four stages; kFront some of stages 0 and 1 (no exchange);
 // kBack any other range (one kernel for all of them holds more registers than
-// there are: M = 2, L = 15, complex128, 3.70 -> 4.18 ms a whole pass).
+// there are: M = 2, L = 15, complex128, 3.70 -> 4.18 ms a whole pass).  S0: the
+// first stage, which decides where a register's entry lies; in a tile below its
+// mirror that also says which entries are read or stored at their mirror, so
+// that their addresses are two bases plus uniform offsets (mirrored entry by
+// entry in 64 bits -> this, L = 15, rho at every step: stages 0 to 2 complex128
+// 4.06 -> 3.52 ms, complex64/FP32 2.79 -> 2.12; stage 0 3.45 -> 3.38, 2.06 -> 1.73).
 // AHEAD (FP64 arithmetic): a tile is read after the first stage of the tile
 // before it, which frees the registers; with the reads in flight under the
 // other stages and ahead of the stores two waves per SIMD do better than three
 // without them (L = 15, complex128, 3.90 -> 3.66 ms a pass, against 3.47 ms for
 // the reads and stores alone), but only where a block has several tiles.
 enum { kWhole, kFront, kBack };
-template <typename S, typename T, bool RHO, bool MIRROR, int PART, bool AHEAD>
+template <typename S, typename T, bool RHO, bool MIRROR, int PART, int S0, bool AHEAD>
 __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileArgs a) {
     constexpr bool WHOLE = PART == kWhole;
+    static_assert(S0 == 0 || !WHOLE, "a whole pass begins at stage 0");
     using C = typename Cx<T>::type;
     using CS = typename Cx<S>::type;
     __shared__ __align__(16) unsigned char s_buf[kWaves][1024 * 8];
@@ -295,6 +301,13 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         tile_rho_sum((const double *)a.prev.rows[k], a.prev.n_rows, (double *)a.prev.out[k], s_red);
         return;
     }
+    // Block of the pass.  Parts at complex128 give neighbouring blocks, whose tiles
+    // are neighbours in memory, to one XCD (L = 15, stages 2 and 3 3.98 -> 3.65 ms,
+    // stages 0 and 1 3.63 -> 3.45; a whole pass 3.70 -> 3.72 and complex64 parts
+    // 1.79 -> 1.83 ms the other way: they keep the order of the launch)
+    const int blk = PART != kWhole && sizeof(S) == 8 && a.n_work % 8 == 0
+                        ? (int)(blockIdx.x & 7) * (a.n_work >> 3) + (int)(blockIdx.x >> 3)
+                        : (int)blockIdx.x;
     const T *coef = (const T *)a.coef;
     // layout A: lane (d2, d3, w0); layout B: lane (w0, o0, o1); w1 = wave
     double acc[RHO ? kTileSteps : 1][MIRROR ? 1 : 2];
@@ -302,7 +315,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
     for (int s = 0; s < (RHO ? kTileSteps : 1); ++s)
 #pragma unroll
         for (int k = 0; k < (MIRROR ? 1 : 2); ++k) acc[s][k] = 0.0;
-    const int s0 = a.s0, s1 = a.s1;
+    const int s1 = a.s1;
     const CS *__restrict__ ain = (const CS *)a.a_in;
     CS *__restrict__ aout = (CS *)a.a_out;
     const long long mc = a.m_count;
@@ -311,11 +324,22 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
     CS x[16];                              // as stored (converting waits for the read)
     double2 top, mid;
     const double2 tw = a.t_w[(lane >> 2) * 16 + (lane & 3) + 4 * wave];
+    // part of a group: the index of the thread's entry of registers zero ...
+    auto part_in = [&](int hi, int ua, int wa) {
+        return ((long long)hi * 16 + 4 * wave + wa) * a.in_m + (ua & 3) * a.in_d[2] + (ua >> 2) * a.in_d[3];
+    };
+    // ... and whether register r's entry of a tile below its mirror is: the points
+    // of this group's earlier stages, in the place of d0, d1, d2, are its highest
+    // digits, and the tile's come next
+    auto in_direct = [](int r, int ua) {
+        const int rm = (int)mirror4(r), d2 = ua & 3;
+        return !MIRROR || (S0 == 1 ? (r & 3) != 2 : S0 == 2 ? r <= rm : r <= rm ? d2 != 2 : d2 == 1);
+    };
     auto read_tile = [&](int hi, bool self, int lane) {
         const int set = lane >> 2, ua = lane & 15, wa = lane >> 4;
         top = a.t_top[((size_t)set << (2 * a.d_top)) + (hi >> (2 * a.d_mid))];
         mid = a.t_mid[((size_t)set << (2 * a.d_mid)) + (hi & ((1 << (2 * a.d_mid)) - 1))];
-        if constexpr (WHOLE) {
+        if constexpr (S0 == 0) {
             // a tile that is its own mirror: the entries above their mirror hold
             // no valid value, their mirror's conjugate (of the same tile) does
             const int b = (wa + 4 * wave) * 256 + 16 * ua, bm = MIRROR ? (int)mirror4(b) : b;
@@ -335,33 +359,49 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
                 asm volatile("" ::: "memory");
             }
         } else {
-            // part of a group: any entry, by its index (an entry above its
-            // mirror through the mirror)
-            const long long x0 = ((long long)hi * 16 + 4 * wave + wa) * a.in_m + (ua & 3) * a.in_d[2] +
-                                 (ua >> 2) * a.in_d[3];
-            const long long x0m = MIRROR ? mirror4(x0) : x0;
+            // part of a group: an entry above its mirror through the mirror
+            const long long x0 = part_in(hi, ua, wa), x0m = MIRROR ? mirror4(x0) : x0;
             long long da = a.in_d[0], db = a.in_d[1];
             asm volatile("" : "+s"(da), "+s"(db));     // their multiples are not kept over the tiles
+            if (!self) {
+                const CS *const pd = ain + x0, *const pm = ain + x0m;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int rm = (int)mirror4(r);
-                const long long i = x0 + (r & 3) * da + (r >> 2) * db;
-                const long long im = MIRROR ? x0m + (rm & 3) * da + (rm >> 2) * db : i;
-                x[r] = ain[im < i ? im : i];
-                if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                for (int r = 0; r < 16; ++r) {
+                    const int rm = (int)mirror4(r);
+                    const long long off = (r & 3) * da + (r >> 2) * db, offm = (rm & 3) * da + (rm >> 2) * db;
+                    x[r] = *(in_direct(r, ua) ? pd + off : pm + offm);
+                    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+                asm volatile("" ::: "memory");
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int rm = (int)mirror4(r);
+                    const long long i = x0 + (r & 3) * da + (r >> 2) * db;
+                    const long long im = x0m + (rm & 3) * da + (rm >> 2) * db;
+                    x[r] = ain[im < i ? im : i];
+                    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+                asm volatile("" ::: "memory");
             }
         }
     };
     // the conjugates of the entries that were read at their mirror
     auto fix_tile = [&](int hi, bool self, int lane) {
+        if (!MIRROR) return;
         const int ua = lane & 15, wa = lane >> 4;
-        if (WHOLE ? !self : !MIRROR) return;
-        const long long x0 = WHOLE ? (wa + 4 * wave) * 256 + 16 * ua
-                                   : ((long long)hi * 16 + 4 * wave + wa) * a.in_m + (ua & 3) * a.in_d[2] +
-                                         (ua >> 2) * a.in_d[3];
+        if (!self) {
+            if constexpr (S0 > 0) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (!in_direct(r, ua)) x[r].y = -x[r].y;
+            }
+            return;
+        }
+        const long long x0 = S0 == 0 ? (wa + 4 * wave) * 256 + 16 * ua : part_in(hi, ua, wa);
         const long long x0m = mirror4(x0);
-        long long da = WHOLE ? 1 : a.in_d[0], db = WHOLE ? 4 : a.in_d[1];
-        if (!WHOLE) asm volatile("" : "+s"(da), "+s"(db));
+        long long da = S0 == 0 ? 1 : a.in_d[0], db = S0 == 0 ? 4 : a.in_d[1];
+        if (S0 > 0) asm volatile("" : "+s"(da), "+s"(db));
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int rm = (int)mirror4(r);
@@ -373,9 +413,9 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
     };
     const int k_hi = a.d_mid + a.d_top;
     bool self, self_next = false;
-    int hi = tile_hi(blockIdx.x, k_hi, MIRROR, &self), hi_next = 0;
+    int hi = tile_hi(blk, k_hi, MIRROR, &self), hi_next = 0;
     if (AHEAD) read_tile(hi, self, lane);
-    for (int idx = blockIdx.x; idx < a.n_tiles; idx += a.n_work, hi = hi_next, self = self_next) {
+    for (int idx = blk; idx < a.n_tiles; idx += a.n_work, hi = hi_next, self = self_next) {
         // opaque per tile: what the lane's position gives (LDS slots, offsets)
         // is formed again for each tile rather than held in registers
         int lane = t & 63;
@@ -385,7 +425,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         const int wb = lane & 15, ub = (lane >> 4) + 4 * wave;
         C w[16];
         if (!AHEAD) read_tile(hi, self, lane);
-        if (idx == (int)blockIdx.x) {
+        if (idx == blk) {
             s_u[t] = a.t_u[t];         // once, behind the first tile's loads
             __syncthreads();
         }
@@ -438,7 +478,9 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             }
         };
         fix_tile(hi, self, lane);
-        if (s0 <= 0) {
+        // (a.s0 is S0: the branch keeps the stage's registers apart from the read's,
+        // 119 instead of 136 of them in a whole pass of FP32 arithmetic)
+        if (S0 == 0 && a.s0 <= 0) {
             const int prev = hi >> (2 * (k_hi - 1));                   // point n-1
             double2 k0, k3;
             coef_k(coef, 0, prev, k0, k3);
@@ -454,25 +496,37 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             hi_next = tile_hi(idx + a.n_work, k_hi, MIRROR, &self_next);
             if (AHEAD) read_tile(hi_next, self_next, lane);
         }
-        if (s0 <= 1 && s1 > 1) {
+        if (S0 <= 1 && s1 > 1) {
             tile_stage<T, RHO, MIRROR, 1>(w, w, coef, factor(4, wl, ua), factor(5, wl, ua), double2{}, double2{}, tf1, tf2, rd0, rd3);
             if (RHO) add_rho(RHO ? 1 : 0, wl, ua, tf1, tf2, rd0, rd3);
             round_to_storage(true);
         }
-        // the 16 entries y0 + (r % 4) da + (r / 4) db of a part of a group (at the
-        // mirrored address, conjugated, when above their mirror; a tile that is
-        // its own mirror stores only those not above it)
-        auto store_part = [&](long long y0, long long da, long long db) {
+        // the 16 entries y0 + (r % 4) da + (r / 4) db of a part of a group: in a tile
+        // below its mirror at the mirrored address, conjugated, unless direct(r); a
+        // tile that is its own mirror stores only those not above it
+        auto store_part = [&](long long y0, long long da, long long db, auto direct) {
             asm volatile("" : "+s"(da), "+s"(db));     // their multiples are not kept over the tiles
             const long long y0m = MIRROR ? mirror4(y0) : y0;
+            if (!self) {
+                CS *const pd = aout + y0, *const pm = aout + y0m;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int rm = (int)mirror4(r);
+                    const long long off = (r & 3) * da + (r >> 2) * db, offm = (rm & 3) * da + (rm >> 2) * db;
+                    const bool dir = !MIRROR || direct(r, rm);
+                    C v = w[r];
+                    if (!dir) v.y = -v.y;
+                    *(dir ? pd + off : pm + offm) = conv<CS>(v);
+                    if (r % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                return;
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int rm = (int)mirror4(r);
                 const long long y = y0 + (r & 3) * da + (r >> 2) * db;
-                const long long ym = MIRROR ? y0m + (rm & 3) * da + (rm >> 2) * db : y;
-                C v = w[r];
-                if (ym < y) v.y = -v.y;
-                if (!(ym < y && self)) aout[ym < y ? ym : y] = conv<CS>(v);
+                const long long ym = y0m + (rm & 3) * da + (rm >> 2) * db;
+                if (!(ym < y)) aout[y] = conv<CS>(w[r]);
                 if (r % 2 == 1) __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -498,16 +552,21 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         if constexpr (PART == kFront) {
             // the digits that follow each other in memory are the lane's: d2, d3,
             // w0 after stage 1, and d1, d2 after stage 0
-            const bool odd = s1 == 1;
-            if (odd) rotate();
-            store_part(((long long)hi * 16 + 4 * wave + wa) * a.out_m + (ua & 3) * a.out_d[odd ? 1 : 2] +
-                           (ua >> 2) * a.out_d[odd ? 2 : 3],
-                       a.out_d[0], a.out_d[odd ? 3 : 1]);
+            // (the highest digits of an output are o0, or o1 and o0, in the registers)
+            const long long m = (long long)hi * 16 + 4 * wave + wa;
+            if (S0 == 0 && s1 == 1) {
+                rotate();
+                store_part(m * a.out_m + (ua & 3) * a.out_d[1] + (ua >> 2) * a.out_d[2], a.out_d[0], a.out_d[3],
+                           [](int r, int) { return (r & 3) != 2; });
+            } else {
+                store_part(m * a.out_m + (ua & 3) * a.out_d[2] + (ua >> 2) * a.out_d[3], a.out_d[0], a.out_d[1],
+                           [](int r, int rm) { return r <= rm; });
+            }
         } else {
         exchange(w, s_buf, xl, [&]() {
             if (lane >= 32) s_w[wave][lane] = tile_f;
         });
-        if (s0 <= 2 && s1 > 2) {
+        if (S0 <= 2 && s1 > 2) {
             double2 k0, k3;
             coef_k(coef, 2, wave, k0, k3);
             tile_stage<T, RHO, MIRROR, 2>(w, w, coef, factor(8, wb, ub), factor(9, wb, ub), k0, k3, tf1, tf2, rd0, rd3);
@@ -519,12 +578,12 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             if (RHO) add_rho(RHO ? 3 : 0, wb, ub, tf1, tf2, rd0, rd3);
         }
         const long long m = (long long)hi * 16 + wb;        // layout B's m
+        const int ubm = mirror_d(ub & 3) + 4 * mirror_d(ub >> 2);
         if (WHOLE) {
             // an output above its mirror goes to the mirrored address as its
             // conjugate (the entry the mirrored tile, which does not run, owns);
             // a tile that is its own mirror forms those entries too, and stores
             // only the ones not above their mirror
-            const int ubm = mirror_d(ub & 3) + 4 * mirror_d(ub >> 2);
             CS *const pd = aout + m + mc * ub;
             CS *const pm = aout + mirror4(m) + mc * ubm;
 #pragma unroll
@@ -545,9 +604,11 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             rotate();                              // lane (d3, w0, o0), registers (o2, w1)
             store_part(((long long)hi * 16 + (wb >> 2)) * a.out_m + (wb & 3) * a.out_d[3] +
                            (ub & 3) * a.out_d[0] + (ub >> 2) * a.out_d[1],
-                       a.out_d[2], 4 * a.out_m);
+                       a.out_d[2], 4 * a.out_m,
+                       [&](int r, int) { return (r & 3) == 1 || ((r & 3) != 2 && ub <= ubm); });
         } else {
-            store_part(m * a.out_m + (ub & 3) * a.out_d[0] + (ub >> 2) * a.out_d[1], a.out_d[2], a.out_d[3]);
+            store_part(m * a.out_m + (ub & 3) * a.out_d[0] + (ub >> 2) * a.out_d[1], a.out_d[2], a.out_d[3],
+                       [&](int r, int rm) { return r < rm || (r == rm && ub <= ubm); });
         }
         }
     }
@@ -575,7 +636,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
             if (MIRROR) v = q == 0 ? sum(0, 0) : q == 6 ? sum(0, 1) : q == 2 || q == 4 ? sum(0, 2)
                           : q == 3 ? sum(0, 3) : q == 5 ? -sum(0, 3) : 0.0;
             else v = sum(q / 4, q % 4);
-            ((double *)a.rows)[((size_t)s * a.n_work + blockIdx.x) * 8 + q] = v;
+            ((double *)a.rows)[((size_t)s * a.n_work + blk) * 8 + q] = v;
         }
     }
 }
@@ -583,10 +644,16 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
 template <typename S, typename T, bool RHO, bool MIRROR, bool AHEAD>
 hipError_t launch_tile_w(const TileArgs &a, hipStream_t st) {
     const dim3 g(a.n_work + a.prev.n), b(kBlock);
-    if (a.s1 - a.s0 == kTileSteps)
-        hipLaunchKernelGGL((tile_kernel<S, T, RHO, MIRROR, kWhole, AHEAD>), g, b, 0, st, a);
-    else if (a.s1 <= 2) hipLaunchKernelGGL((tile_kernel<S, T, RHO, MIRROR, kFront, AHEAD>), g, b, 0, st, a);
-    else hipLaunchKernelGGL((tile_kernel<S, T, RHO, MIRROR, kBack, AHEAD>), g, b, 0, st, a);
+    if (a.s0 < 0 || a.s0 >= a.s1 || a.s1 > kTileSteps) return hipErrorInvalidValue;
+#define QUAPI_TILE(PART, S0) hipLaunchKernelGGL((tile_kernel<S, T, RHO, MIRROR, PART, S0, AHEAD>), g, b, 0, st, a)
+    if (a.s1 - a.s0 == kTileSteps) QUAPI_TILE(kWhole, 0);
+    else if (a.s1 <= 2 && a.s0 == 0) QUAPI_TILE(kFront, 0);
+    else if (a.s1 <= 2) QUAPI_TILE(kFront, 1);
+    else if (a.s0 == 0) QUAPI_TILE(kBack, 0);
+    else if (a.s0 == 1) QUAPI_TILE(kBack, 1);
+    else if (a.s0 == 2) QUAPI_TILE(kBack, 2);
+    else QUAPI_TILE(kBack, 3);
+#undef QUAPI_TILE
     return hipGetLastError();
 }
 template <typename S, typename T>
