@@ -57,3 +57,20 @@ def test_store_rule(s1):
                 y = (16 * hi + c) * sm + a * sd[0] + b * sd[1] + q * sd[2] + p * sd[3]
                 direct = r < rm or (r == rm and ok)
         assert direct == (y < _mirror(y))
+
+
+def test_rows_of_four_real_coefficients():
+    # the oldest point's row of the off-diagonal points: the phase e^{-i phi} in
+    # the thread's factor, the rest on sums and differences of the four entries
+    import numpy as np
+    rng = np.random.default_rng(8)
+    for _ in range(50):
+        s, eta, x = rng.normal(size=2), complex(*rng.normal(size=2)), rng.normal(size=4) + 1j * rng.normal(size=4)
+        D = s[0] - s[1]
+        phi, th, g = D * eta.imag * (s[0] + s[1]), D * D * eta.imag, D * D * eta.real
+        p, q = x[0] + x[3], x[0] - x[3]
+        row1 = np.cos(th) * p - 1j * np.sin(th) * q + np.exp(-g) * x[1] + np.exp(g) * x[2]
+        row2 = np.cos(th) * p + 1j * np.sin(th) * q + np.exp(-g) * x[2] + np.exp(g) * x[1]
+        for (a, b), got in (((0, 1), np.exp(-1j * phi) * row1), ((1, 0), np.exp(1j * phi) * row2)):
+            F = [np.exp(-(s[a] - s[b]) * (eta * s[c] - np.conj(eta) * s[d])) for c in (0, 1) for d in (0, 1)]
+            assert abs(got - np.dot(F, x)) <= 1e-13 * np.abs(F).max() * np.abs(x).sum()
