@@ -159,7 +159,12 @@ quapi_status quapi_create(const quapi_params *p, void *hip_stream, void *workspa
  * multiple of F (otherwise the steps of a split group run one by one, or as
  * one two-step launch when a call ends two steps into a three-step group, and
  * round differently, within 1e-15).  F is chosen as quapi_set_fused_steps
- * describes. */
+ * describes.  An M = 2 context with dk_max >= 8 that pins no width runs four
+ * steps per pass over the tensor, in groups (L+1 .. L+4), (L+5 .. L+8), ...,
+ * and a call that ends inside one takes a pass for its part of it: calls of
+ * whole groups of four are the fastest.  At dk_max >= 14, where a pass is bound
+ * by memory, calls of three steps take 1.5 times as long as with
+ * quapi_set_fused_steps(ctx, 3), and calls of one 1.1 times as with 1. */
 quapi_status quapi_propagate(quapi_ctx *ctx, int n_steps, const int *sel, int n_sel,
                              double *rho_out);
 
@@ -346,9 +351,9 @@ quapi_status quapi_set_fused_steps(quapi_ctx *ctx, int steps);
  * (a, b) -> (b, a)) -- about half the bytes.  rho at every step is unchanged
  * up to rounding.  On by default where available.  The single step and the
  * two-step kernel use it for tensors above 2^22 entries only (smaller steps
- * are bound by their launches, and mirror mode takes three); the three-step
- * and four-step kernels always.  The entries above their mirror are filled in (one pass
- * over the tensor) before anything that reads the whole tensor: a kernel
+ * are bound by their launches more than by their bytes); the three-step and
+ * four-step kernels always.  The entries above their mirror are filled in (one
+ * pass over the tensor) before anything that reads the whole tensor: a kernel
  * that does not take mirror mode, quapi_read_tensor.
  *   quapi_mirror:      *enabled = the mode: 0 off, 1 on (default), 2 on at every size.
  *   quapi_set_mirror:  enable = 0, 1 or 2 as above.
@@ -362,17 +367,21 @@ quapi_status quapi_set_mirror(quapi_ctx *ctx, int enable);
 typedef struct {
     double setup_ms;          /* device time of the setup kernels in quapi_create */
     double step_ms;           /* summed duration of full-window step kernels (n >= L) */
-    long long step_launches;  /* number of those launches (in mirror mode: of their groups of three) */
+    long long step_launches;  /* number of those launches (in mirror mode a launch may be two kernels) */
     long long step_steps;     /* full-window steps they covered (a fused launch covers two to four) */
     double grow_ms;           /* summed duration of growth-step kernels (n < L) */
     long long grow_launches;
-    double finalize_ms;       /* summed duration of the kernels that sum rho over blocks (the four-step
-                                 launches sum it themselves: no record) */
+    double finalize_ms;       /* summed duration of the kernels that sum rho over blocks (the next launch
+                                 does it for a four-step launch and for a mirror-mode single step
+                                 above 2^22 entries: no record) */
     long long finalize_launches;
-    /* step_ms / step_launches split by the full-window steps a launch covers:
-     * index 1 single steps, 2 two-step launches, 3 three-step launches (index
-     * 0 unused).  A launch in mirror mode counts its group of three kernels; one
-     * over more steps than a group counts as its groups and the rest. */
+    /* step_ms and step_steps split by width: index 1 single steps, 2 two-step
+     * launches, 3 three-step launches (index 0 unused).  A launch over more
+     * steps than quapi_fused_steps (M = 2, dk_max >= 8, no pinned width) is not
+     * counted as one: its steps are booked as whole groups of
+     * quapi_fused_steps and the rest, with its time shared out by steps, so
+     * that width_ms sums to step_ms and steps times counts to step_steps; what
+     * ran are step_launches.  With a pinned width every count is of launches. */
     double width_ms[4];
     long long width_launches[4];
 } quapi_timing;

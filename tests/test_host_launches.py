@@ -153,3 +153,29 @@ def test_server_chunks_are_whole_passes(run):
             with Q.create(Q.params_from(w)) as c:
                 assert serve._group_steps(w, c) == c.fused_steps()
         """)
+
+
+def test_timing_counts_the_launches_that_run(run):
+    # step_launches and step_steps are launches and their steps; the split by width
+    # shares a four-step pass out over groups of quapi_fused_steps and the rest,
+    # so its sums are those of the totals, and its counts only where no pass ran
+    run("""
+        kernels = ("step_kernel", "step_mirror_kernel", "step2_kernel", "step3_kernel", "tile_kernel")
+        for L, dtype, pin, n, launches in ((13, "c128", 0, 8, 3), (13, "c64", 0, 12, 4), (9, "c64f64", 0, 8, 3),
+                                           (13, "c128", 3, 7, 3), (12, "c64", 2, 7, 4), (9, "c128", 1, 5, 5)):
+            w = W.spin_boson_l7().with_(L=L)
+            with Q.create(Q.params_from(w, dtype=dtype)) as c:
+                c.set_fused_steps(pin)
+                c.propagate(L - 1, sel=[])
+                c.set_timing(True)
+                c.get_timing()
+                got = [k for k in names(lambda: c.propagate(n, sel=[])) if k in kernels]
+                t = c.get_timing()
+                assert (t["step_launches"], t["step_steps"]) == (launches, n), (L, dtype, pin, t)
+                if pin == 0:
+                    assert got == ["step_kernel" if L < 12 else "step_mirror_kernel"] + ["tile_kernel"] * (launches - 1)
+                k = t["width_launches"]
+                assert sum(i * k[i] for i in range(4)) == n, (L, dtype, pin, t)
+                assert abs(sum(t["width_ms"]) - t["step_ms"]) < 1e-9, (L, dtype, pin, t)
+                assert pin == 0 or sum(k) == launches, (L, dtype, pin, t)
+        """)
