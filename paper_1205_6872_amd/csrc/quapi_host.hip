@@ -132,10 +132,12 @@ int fusion_width(int N, int L, int prec) {
 
 // The four-step tile kernel (quapi_tile.hip) runs every full-window step past
 // n = L of a dense M = 2 context from L = kTileMinL that pins no
-// launch width (complex128, rho every step: L = 8 24 -> 2.8 us per step, L = 15
-// 1.19 -> 0.91 ms).  Below, at N^L <= 2^14, the persistent path takes one launch
-// per call (L = 7: 4.2 us per step); a tile needs the digits d0 .. d3, w0, w1
-// and at least one more.
+// launch width (complex128, rho every step: L = 8 22.4 -> 2.9 us per step, L = 15
+// 1.18 -> 0.90 ms).  Below, at N^L <= 2^14, the persistent path takes a launch or
+// two per call and whole batches of contexts.  A tile would fit L = 7 (digits
+// d0 .. d3, w0, w1 and one more): 2.8 us per step against 4.3 on the persistent
+// path, but 769 us against 615 for a run of 100 steps from create on, whose
+// growth steps take two launches each there (300 steps: 1347 against 1425).
 bool tile_ok(int N, int L) { return N == 4 && L >= kTileMinL; }
 // Its outer digits past w0, w1: the middle ones share a table of at most 256
 // values, the rest another.
@@ -1005,12 +1007,14 @@ quapi_status finalize_side(quapi_ctx *c, const int *slots, int n, int grid) {
     return QUAPI_OK;
 }
 
-// Enqueue step n (1-based); with rho, also rho(t_n) into the sink's next slot.
-// The finalize runs on the side stream, overlapped with the next step.
 // The full-window single step runs in mirror mode (half of the entries) for
-// tensors above the graph size: smaller steps are bound by their launches,
-// and the three mirror launches then cost more than the bytes they save
-// (measured crossover: M = 2 at L = 11-12, M = 3 at L = 7, M = 4 at L = 5-6).
+// tensors above the graph size.  At that size and below steps replay graphs and
+// are bound by their launches: with mode 2 there, us per step (rho every step /
+// at the last), full -> mirror: M = 2, L = 10, complex128 22.5 -> 19.9 / 15.7 ->
+// 11.2; M = 3, L = 6 23.2 -> 20.0 / 12.4 -> 11.4; L = 5 24.6 -> 24.8 / 6.2 -> 7.9;
+// M = 4, L = 5 24.7 -> 30.1 / 13.2 -> 16.4, complex64 25.7 -> 25.9 / 9.1 -> 7.8;
+// L = 4, complex128 11.1 -> 17.4 / 10.0 -> 12.3.  Above it: M = 3, L = 7 62.4 ->
+// 32.2 / 28.6 -> 19.5; M = 2, L = 12 113.8 -> 49.8 / 109.5 -> 48.5.
 bool single_mirror_on(const quapi_ctx *c) {
     return c->mirror != 0 && single_mirror_ok(c->N, c->L, c->lay.main_split) &&
            (c->mirror == 2 || (size_t)ipow_ll(c->N, c->L) > kGraphMaxEntries);
@@ -1038,6 +1042,8 @@ hipError_t launch_full_step(quapi_ctx *c, bool rho, StepArgs a, int grid, int *r
     return launch_step(c->N, c->prec, rho, false, a, grid, c->stream);
 }
 
+// Enqueue step n (1-based); with rho, also rho(t_n) into the sink's next slot.
+// The finalize runs on the side stream, overlapped with the next step.
 quapi_status enqueue_step(quapi_ctx *c, int n, bool rho) {
     StepPlan sp;
     quapi_status st = prepare_step(c, n, rho, &sp);
@@ -1245,7 +1251,7 @@ quapi_status prepare_step2(quapi_ctx *c, bool rho, Step2Args *out) {
 }
 
 // The two-step kernel runs in mirror mode above the graph size, as the
-// single step does (the same launch-count trade-off).
+// single step does (its mirror mode takes two kernels).
 bool pair_mirror_on(const quapi_ctx *c) {
     return c->mirror != 0 && fused_ok(c->N, c->L) &&
            (c->mirror == 2 || (size_t)ipow_ll(c->N, c->L) > kGraphMaxEntries);
@@ -1712,8 +1718,8 @@ quapi_status check_selection(quapi_ctx *c, int n_steps, const int *sel, int n_se
 
 // ---------------------------------------------------------- persistent path
 // Small tensors (N^L <= 2^14) run every step of a call in one launch of the
-// persistent kernel, one block per context: a step costs a block barrier
-// instead of three launches.  Contexts that pin a launch width, force mirror
+// persistent kernel (M = 2, L = 5 .. 7: two), one block per context: a step costs a
+// block barrier instead of launches.  Contexts that pin a launch width, force mirror
 // mode at every size, or are driven use the multi-block kernels.
 bool small_on(const quapi_ctx *c) {
     return c->small != 0 && c->n_H == 0 && !c->fuse_pinned && c->mirror != 2;
@@ -2816,10 +2822,10 @@ quapi_status quapi_get_timing(quapi_ctx *ctx, quapi_timing *out) {
             if (r.kind == 0 && r.steps > r.width && r.width > 0) {
                 // a pass over more steps than a group: counted as its groups and the rest
                 const int rest = r.steps % r.width;
-                ctx->acc_width_ms[r.width] += ms * (r.steps - rest) / r.steps;
+                ctx->acc_width_ms[r.width] += (double)ms * (r.steps - rest) / r.steps;
                 ctx->acc_width_n[r.width] += r.steps / r.width;
                 if (rest) {
-                    ctx->acc_width_ms[rest] += ms * rest / r.steps;
+                    ctx->acc_width_ms[rest] += (double)ms * rest / r.steps;
                     ctx->acc_width_n[rest] += 1;
                 }
             } else if (r.kind == 0) {

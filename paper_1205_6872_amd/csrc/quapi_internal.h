@@ -255,12 +255,12 @@ hipError_t launch_step(int N, int prec, bool with_rho, bool grow, const StepArgs
                        hipStream_t st);
 // Where finalized rho values go: rho of the k-th finalize after a reset is
 // written to base + k*N (k counted per point).  Device-resident, so graph replays need no new arguments.
-// A row set of up to kDirectRows rows is summed by a block per point.
-constexpr int kDirectRows = 8192;
 struct RhoSink {
     double2 *base;
     unsigned long long count[kMaxN];         // per point o
 };
+// A row set of up to kDirectRows rows is summed by a block per point.
+constexpr int kDirectRows = 8192;
 
 // Sums the block partials of rho into the sink's next slot: one launch on st, or
 // for many rows two, using pairs (kRhoSlices * N * 2 complex) as scratch.

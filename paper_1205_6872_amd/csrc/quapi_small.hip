@@ -517,8 +517,8 @@ __device__ __forceinline__ void reg_body(const SmallCtxArgs &a, unsigned char *s
 // also runs, whole, the contexts of L < kRegMinL, whose full-window steps have
 // at most 64 items: one wave.  A call of 150 steps on 24 contexts, complex64, rho
 // at every step, a launch per length -> this: L = 5, 6 552 -> 354 us, L = 4, 5
-// 584 -> 378, L = 3 .. 6 814 -> 390; L = 7 alone 690 -> 719, complex128 766 -> 750
-// (a kernel per length allots each its own registers).
+// 584 -> 378, L = 3 .. 6 814 -> 390; one length alone the same (complex128, L = 7
+// 766 -> 750).
 constexpr int kRegThreads = SmallReg<kRegMaxL>::threads;
 constexpr int reg_threads(int L) {
     return L == 7 ? SmallReg<7>::threads : L == 6 ? SmallReg<6>::threads : L == 5 ? SmallReg<5>::threads : 64;
