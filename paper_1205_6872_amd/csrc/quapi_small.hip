@@ -335,7 +335,7 @@ __global__ void __launch_bounds__(SmallBlock<N>::threads) small_kernel(const Sma
 // the exchange.  Before, the tensor went through LDS, or at L = 7 through HBM
 // buffers (512 KB a step through one compute unit's L2 port), one item at a time.
 // One context, rho at every step / at the last, us per step, before -> now:
-//   L = 7  complex128 10.7 / 6.4 -> 4.2 / 2.8   complex64 7.8 / 4.3 -> 3.8 / 2.3
+//   L = 7  complex128 10.7 / 6.4 -> 4.3 / 2.9   complex64 7.8 / 4.3 -> 4.1 / 2.7
 //   L = 6              4.0 / 2.1 -> 1.5 / 1.0              3.0 / 1.4 -> 1.5 / 0.9
 //   L = 5              2.0 / 1.0 -> 1.3 / 0.8              1.9 / 0.9 -> 1.4 / 0.8
 // At L = 4 (16 columns, a quarter of a wave) a step would gain nothing.

@@ -16,20 +16,28 @@
 // after, "before" three steps per pass in one thread's registers from L = 13 at
 // complex128 and complex64/FP32 and two otherwise, with two launches for the
 // rho of every step):
-//   L = 15  complex128 1.19 -> 0.91 ms, complex64/FP32 0.65 -> 0.56,
-//           complex64/FP64 0.92 -> 0.68.  One pass of the kept half moves
+//   L = 15  complex128 1.18 -> 0.90 ms, complex64/FP32 0.66 -> 0.61,
+//           complex64/FP64 0.93 -> 0.68.  One pass of the kept half moves
 //           17.2 GB at complex128; reads and stores of the same pattern alone
-//           take 3.47 ms of the 3.63 ms pass, so complex128 is HBM bound;
-//           FP32 arithmetic is bound by its instructions (about 440 vector
-//           instructions per stage and wave, a quarter of them the exact FP64
-//           sums of the rows that carry the trace).
-//   L = 13  complex64/FP64 84 -> 44 us; L = 12 complex128 53 -> 17 us; L = 10
-//           29 -> 4.5 us; L = 8 24 -> 2.8 us: bound by the launch and by the
+//           take 3.47 ms of the 3.6 to 3.7 ms pass, so complex128 is HBM bound;
+//           FP32 arithmetic is bound by its instructions: 2240 vector
+//           instructions per tile and wave, 320 of them conversions (the exact FP64
+//           sums of the rows that carry the trace, factors and rho terms), which
+//           the vector units alone take 1.9 of the 2.4 ms for.
+//   L = 13  complex64/FP64 89 -> 40 us; L = 12 complex128 57 -> 16 us; L = 10
+//           28.6 -> 4.4 us; L = 8 22.4 -> 2.9 us: bound by the launch and by the
 //           latency of one tile's chain; one launch per four steps, the rho of a
 //           pass summed by extra blocks of the next.
-//   A driven system (complex128, L = 11, rho at the last step, 64 steps): 2281 ->
-//           383 us, a launch of tables and a pass per four steps where each step
+//   A driven system (complex128, L = 11, rho at the last step, 64 steps): 2310 ->
+//           362 us, a launch of tables and a pass per four steps where each step
 //           took three launches (tables, factor products, step).
+//   Calls that are not whole groups of four run parts of a pass, which move the
+//   same bytes for fewer steps.  L = 15, ms per step, calls of 1 / 2 / 3 / 6 / 9:
+//           complex128 3.33 / 2.79 / 1.19 / 1.19 / 1.19 -> 3.56 / 1.79 / 1.80 / 1.19 /
+//           1.20; complex64/FP32 1.67 / 1.40 / 0.67 / 0.66 / 0.66 -> 1.93 / 0.94 / 1.02 /
+//           0.70 / 0.74; complex64/FP64 1.76 / 0.94 / 1.20 / 0.93 / 1.02 -> 1.94 / 1.00 /
+//           1.08 / 0.77 / 0.81 (three-step launches fit calls of 3, 6 and 9; a group
+//           moved to where a call begins would give the call's steps other bits).
 //   16 consecutive entries per store (whole cache lines): with stores of 64 B
 //   from waves that run apart a pass takes 4.8 ms at L = 15; five points per
 //   tile would leave 64 B stores and takes 4.8 ms for the memory alone.
