@@ -33,10 +33,10 @@
 //           took three launches (tables, factor products, step).
 //   Calls that are not whole groups of four run parts of a pass, which move the
 //   same bytes for fewer steps.  L = 15, ms per step, calls of 1 / 2 / 3 / 6 / 9:
-//           complex128 3.33 / 2.79 / 1.19 / 1.19 / 1.19 -> 3.56 / 1.79 / 1.80 / 1.19 /
-//           1.20; complex64/FP32 1.67 / 1.40 / 0.67 / 0.66 / 0.66 -> 1.93 / 0.94 / 1.02 /
-//           0.70 / 0.74; complex64/FP64 1.76 / 0.94 / 1.20 / 0.93 / 1.02 -> 1.94 / 1.00 /
-//           1.08 / 0.77 / 0.81 (three-step launches fit calls of 3, 6 and 9; a group
+//           complex128 3.33 / 2.79 / 1.19 / 1.19 / 1.19 -> 3.53 / 1.78 / 1.77 / 1.20 /
+//           1.20; complex64/FP32 1.67 / 1.40 / 0.67 / 0.66 / 0.66 -> 1.87 / 0.94 / 0.97 /
+//           0.70 / 0.73; complex64/FP64 1.76 / 0.94 / 1.20 / 0.93 / 1.02 -> 1.88 / 1.00 /
+//           1.05 / 0.78 / 0.81 (three-step launches fit calls of 3, 6 and 9; a group
 //           moved to where a call begins would give the call's steps other bits).
 //   16 consecutive entries per store (whole cache lines): with stores of 64 B
 //   from waves that run apart a pass takes 4.8 ms at L = 15; five points per
@@ -332,17 +332,28 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
     CS x[16];                              // as stored (converting waits for the read)
     double2 top, mid;
     const double2 tw = a.t_w[(lane >> 2) * 16 + (lane & 3) + 4 * wave];
-    // part of a group: the index of the thread's entry of registers zero ...
-    auto part_in = [&](int hi, int ua, int wa) {
-        return ((long long)hi * 16 + 4 * wave + wa) * a.in_m + (ua & 3) * a.in_d[2] + (ua >> 2) * a.in_d[3];
+    // Part of a group: the index of the thread's entry of registers zero, in layout
+    // A or, for stage 3 alone, in layout B, which stage 3 works in (no exchange:
+    // L = 15, complex64 2.21 -> 1.99 ms; stages 2 and 3 read in it 1.99 -> 2.20).
+    // The points of the group's earlier stages, in the place of d0, d1, d2, are
+    // the highest digits, and the tile's come next: registers' digits planes
+    // apart, and after stages 0 and 2 the lowest digit in memory.
+    auto part_in = [&](int hi, int lane) {
+        const int wl = lane & 15, ul = (lane >> 4) + 4 * wave;
+        if (S0 < 3) return ((long long)hi * 16 + ul) * (S0 == 1 ? 64 : 16) + (S0 == 1 ? 4 : 1) * wl;
+        return ((long long)hi * 16 + wl) * 4 + (ul & 3) * (mc << 2) + (ul >> 2) * (mc << 4);
     };
-    // ... and whether register r's entry of a tile below its mirror is: the points
-    // of this group's earlier stages, in the place of d0, d1, d2, are its highest
-    // digits, and the tile's come next
-    auto in_direct = [](int r, int ua) {
-        const int rm = (int)mirror4(r), d2 = ua & 3;
-        return !MIRROR || (S0 == 1 ? (r & 3) != 2 : S0 == 2 ? r <= rm : r <= rm ? d2 != 2 : d2 == 1);
+    auto part_reg = [&](int r) {
+        return S0 == 2 ? (r & 3) * (mc << 4) + (r >> 2) * (mc << 6) : (r & 3) * (mc << 6) + (r >> 2);
     };
+    // stage 3: whether the lane's digits put its entries below their mirror, for
+    // the registers whose own highest digit leaves it open
+    auto lane_direct = [&](int lane) {
+        const int ul = (lane >> 4) + 4 * wave;
+        return !MIRROR || ul <= mirror_d(ul & 3) + 4 * mirror_d(ul >> 2);
+    };
+    auto by_lane = [](int r) { return MIRROR && S0 == 3 && ((r & 3) == 0 || (r & 3) == 3); };
+    constexpr bool kSwap = sizeof(S) == 4;
     auto read_tile = [&](int hi, bool self, int lane) {
         const int set = lane >> 2, ua = lane & 15, wa = lane >> 4;
         top = a.t_top[((size_t)set << (2 * a.d_top)) + (hi >> (2 * a.d_mid))];
@@ -367,26 +378,40 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
                 asm volatile("" ::: "memory");
             }
         } else {
-            // part of a group: an entry above its mirror through the mirror
-            const long long x0 = part_in(hi, ua, wa), x0m = MIRROR ? mirror4(x0) : x0;
-            long long da = a.in_d[0], db = a.in_d[1];
-            asm volatile("" : "+s"(da), "+s"(db));     // their multiples are not kept over the tiles
+            // a part: an entry above its mirror through the mirror.  In a tile below
+            // its mirror complex64 reads whole runs of the registers' lowest digit
+            // (stages 1 to 3 entry by entry 2.23 -> 2.03 ms; stage 1 alone, which has
+            // the time, 1.79 -> 1.83: entry by entry); where that is at the mirror
+            // for some lanes only, fix_tile puts them in order
+            const long long x0 = part_in(hi, lane), x0m = MIRROR ? mirror4(x0) : x0;
             if (!self) {
-                const CS *const pd = ain + x0, *const pm = ain + x0m;
+                const CS *const pd = ain + x0, *const pm = ain + x0m, *const pl = lane_direct(lane) ? pd : pm;
+                if constexpr (S0 == 2) {
+                    long long da = mc << 4, db = mc << 6;
+                    asm volatile("" : "+s"(da), "+s"(db));     // their multiples are not kept over the tiles
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int rm = (int)mirror4(r);
-                    const long long off = (r & 3) * da + (r >> 2) * db, offm = (rm & 3) * da + (rm >> 2) * db;
-                    x[r] = *(in_direct(r, ua) ? pd + off : pm + offm);
-                    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                    for (int r = 0; r < 16; ++r) {
+                        const int rm = (int)mirror4(r), rr = MIRROR && rm < r ? rm : r;
+                        x[r] = (MIRROR && rm < r ? pm : pd)[(rr & 3) * da + (rr >> 2) * db];
+                        if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {
+                    long long one = 1;
+                    if (PART == kFront) asm volatile("" : "+s"(one));
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const bool flip = MIRROR && g == 2;
+                        const CS *const q = (flip ? pm : S0 == 1 || g == 1 ? pd : pl) + (flip ? 1 : g) * (mc << 6);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            x[g + 4 * c] = q[(flip ? mirror_d(c) : kSwap || !by_lane(g) || lane_direct(lane) ? c : mirror_d(c)) * one];
+                    }
                 }
                 asm volatile("" ::: "memory");
             } else {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int rm = (int)mirror4(r);
-                    const long long i = x0 + (r & 3) * da + (r >> 2) * db;
-                    const long long im = x0m + (rm & 3) * da + (rm >> 2) * db;
+                    const long long i = x0 + part_reg(r), im = x0m + part_reg((int)mirror4(r));
                     x[r] = ain[im < i ? im : i];
                     if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                 }
@@ -396,25 +421,31 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
     };
     // the conjugates of the entries that were read at their mirror
     auto fix_tile = [&](int hi, bool self, int lane) {
-        if (!MIRROR) return;
+        if (!MIRROR || (S0 == 0 && !self)) return;
         const int ua = lane & 15, wa = lane >> 4;
         if (!self) {
-            if constexpr (S0 > 0) {
+            const bool d = lane_direct(lane);
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (!in_direct(r, ua)) x[r].y = -x[r].y;
+            for (int r = 0; r < 16; ++r) {
+                if (S0 == 2 ? (int)mirror4(r) < r : S0 > 0 && (r & 3) == 2) x[r].y = -x[r].y;
+                const int rm = (r & 3) + 4 * mirror_d(r >> 2);
+                if (!by_lane(r) || rm < r) continue;
+                const CS u = x[r], um = x[rm];
+                const CS v = kSwap ? um : u, vm = kSwap ? u : um;
+                x[r].x = d ? u.x : v.x;
+                x[r].y = d ? u.y : -v.y;
+                if (rm == r) continue;
+                x[rm].x = d ? um.x : vm.x;
+                x[rm].y = d ? um.y : -vm.y;
             }
             return;
         }
-        const long long x0 = S0 == 0 ? (wa + 4 * wave) * 256 + 16 * ua : part_in(hi, ua, wa);
+        const long long x0 = S0 == 0 ? (wa + 4 * wave) * 256 + 16 * ua : part_in(hi, lane);
         const long long x0m = mirror4(x0);
-        long long da = S0 == 0 ? 1 : a.in_d[0], db = S0 == 0 ? 4 : a.in_d[1];
-        if (S0 > 0) asm volatile("" : "+s"(da), "+s"(db));
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int rm = (int)mirror4(r);
-            const long long i = x0 + (r & 3) * da + (r >> 2) * db;
-            const long long im = x0m + (rm & 3) * da + (rm >> 2) * db;
+            const long long i = x0 + (S0 == 0 ? r : part_reg(r)), im = x0m + (S0 == 0 ? rm : part_reg(rm));
             if (im < i) x[r].y = -x[r].y;
             if (im == i) x[r].y = 0.0f;              // its own conjugate (another kernel's rounding aside)
         }
@@ -444,7 +475,7 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
         {
             tile_f = cmul(cmul(top, mid), tw);
             wave_fence();
-            if (lane < 32) s_w[wave][lane] = tile_f;
+            if (S0 < 2 && lane < 32) s_w[wave][lane] = tile_f;
             wave_fence();
         }
         // the factor of set q over the thread's fixed digits, w0 + 4 w1 = wl
@@ -571,9 +602,15 @@ __global__ void __launch_bounds__(kBlock, AHEAD ? 2 : 3) tile_kernel(const TileA
                            [](int r, int rm) { return r <= rm; });
             }
         } else {
-        exchange(w, s_buf, xl, [&]() {
+        if constexpr (S0 < 3) {
+            exchange(w, s_buf, xl, [&]() {
+                if (lane >= 32) s_w[wave][lane] = tile_f;
+            });
+        } else {                           // read in layout B
+            __syncthreads();               // the factors' last readers (of the tile before) are done
             if (lane >= 32) s_w[wave][lane] = tile_f;
-        });
+            __syncthreads();
+        }
         if (S0 <= 2 && s1 > 2) {
             double2 k0, k3;
             coef_k(coef, 2, wave, k0, k3);

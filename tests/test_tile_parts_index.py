@@ -28,10 +28,15 @@ TILES = [h for h in range(4 ** K) if h < _mirror(h)]
 @pytest.mark.parametrize("s0", [1, 2, 3])
 def test_read_rule(s0):
     sd, sm = _strides(s0, K)
-    for hi, w, d2, d3, r in itertools.product(TILES, range(16), range(4), range(4), range(16)):
-        i = (16 * hi + w) * sm + d2 * sd[2] + d3 * sd[3] + r % 4 * sd[0] + r // 4 * sd[1]
-        rm = _md(r % 4) + 4 * _md(r // 4)
-        direct = {1: r % 4 != 2, 2: r <= rm, 3: d2 != 2 if r <= rm else d2 == 1}[s0]
+    for hi, w, a, b, r in itertools.product(TILES, range(16), range(4), range(4), range(16)):
+        q, p = r % 4, r // 4
+        rm = _md(q) + 4 * _md(p)
+        if s0 == 3:      # lane (w0, w1, o0), wave o1, registers (o2, d3)
+            i = (16 * hi + w) * sm + a * sd[0] + b * sd[1] + q * sd[2] + p * sd[3]
+            direct = q == 1 or (q != 2 and a + 4 * b <= _md(a) + 4 * _md(b))
+        else:            # lane (d2, d3, w0), wave w1, registers (o0, d1) or (o0, o1)
+            i = (16 * hi + w) * sm + a * sd[2] + b * sd[3] + q * sd[0] + p * sd[1]
+            direct = q != 2 if s0 == 1 else r <= rm
         assert direct == (i < _mirror(i))
 
 
