@@ -1594,12 +1594,8 @@ quapi_status enqueue_tile(quapi_ctx *c, int n, int k, double2 *const *out) {
     a.a_in = c->A[c->cur];
     a.a_out = c->A[1 - c->cur];
     // after j stages: the points d_j .. d_3, the digits m, then o_0 .. o_(j-1)
-    auto strides = [&](int j, long long *sd, long long *sm) {
-        for (int p = 0; p < kTileSteps; ++p) sd[p] = p < j ? ipow_ll(N, L - j + p) : ipow_ll(N, p - j);
-        *sm = ipow_ll(N, kTileSteps - j);
-    };
-    strides(a.s0, a.in_d, &a.in_m);
-    strides(a.s1, a.out_d, &a.out_m);
+    for (int p = 0; p < kTileSteps; ++p) a.out_d[p] = p < a.s1 ? ipow_ll(N, L - a.s1 + p) : ipow_ll(N, p - a.s1);
+    a.out_m = ipow_ll(N, kTileSteps - a.s1);
     bool rho = false;
     for (int j = 0; j < k; ++j) rho = rho || out[j];
     if (rho) a.rows = c->trows + (size_t)c->trow_set * kTileSteps * tile_blocks(L) * N;

@@ -345,9 +345,9 @@ struct TileArgs {
     const void *coef;
     double2 *rows;                                   // [stage][n_work][4]
     long long m_count;                               // N^(L-4)
-    // strides of the entry index in the digits d0 .. d3 (replaced by o0 .. o3
-    // as their stages run) and m, as read and as written
-    long long in_d[4], in_m, out_d[4], out_m;
+    // strides of the written entry index in the digits d0 .. d3 (replaced by o0 ..
+    // o3 as their stages run) and m
+    long long out_d[4], out_m;
     int d_mid, d_top, n_tiles, n_work, s0, s1;
     int round_each;                                  // round to the storage type after every step
     TileRho prev;                                    // summed by extra blocks of this launch
