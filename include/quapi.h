@@ -163,8 +163,8 @@ quapi_status quapi_create(const quapi_params *p, void *hip_stream, void *workspa
  * steps per pass over the tensor, in groups (L+1 .. L+4), (L+5 .. L+8), ...,
  * and a call that ends inside one takes a pass for its part of it: calls of
  * whole groups of four are the fastest.  At dk_max >= 14, where a pass is bound
- * by memory, calls of three steps take 1.5 times as long as with
- * quapi_set_fused_steps(ctx, 3), and calls of one 1.1 times as with 1. */
+ * by memory, calls of three steps take up to 1.5 times as long as with
+ * quapi_set_fused_steps(ctx, 3), and calls of one up to 1.2 times as with 1. */
 quapi_status quapi_propagate(quapi_ctx *ctx, int n_steps, const int *sel, int n_sel,
                              double *rho_out);
 
